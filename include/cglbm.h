@@ -394,8 +394,9 @@ int cglbm_set_compact_variant(cglbm_handle *h, int32_t v, void *stream);
 int cglbm_set_graph(cglbm_handle *h, int32_t enable);
 
 /* Launch geometries of the fused kernel (all bitwise equivalent).
- * cglbm_num_variants: how many; cglbm_variant_info: info[0..3] = column
- * extent x, y, z chunk, minimum waves per SIMD; cglbm_set_variant selects one
+ * cglbm_num_variants: how many; cglbm_variant_info: info[0..3] = nominal
+ * column extent x, y, longest z chunk, minimum waves per SIMD (the column
+ * and the chunk are fitted to each box); cglbm_set_variant selects one
  * for every schedule (synchronizes the stream); cglbm_get_variant returns
  * the one loaded (the current schedule's: the autotuner keeps one for
  * schedules 0 and 1 and one for schedule 2). */

@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -407,9 +408,42 @@ int32_t pack_tiles(std::vector<TileEntry> &out, std::vector<TileEntry> &plain,
   return (int32_t)plain.size();
 }
 
-// z chunks [z0, z1) of a box: zc slabs each, except that a box with z walls
-// gets a chunk of `edge` slabs at each wall, so that the chunks between them
-// (whose stencils then stay clear of the walls) run without wall logic.
+// Column tile of an nx x ny box for a block of nt threads whose LDS rings
+// hold r3, r2 and r1 points of the tile + 3, + 2 and + 1 (0: no such ring):
+// of the shapes that fit, the one that covers the box with the fewest tiles,
+// counting 4 / w of a tile for its short rows (each row segment of w nodes
+// touches one more cache line than it fills); the nominal shape wins ties.
+// A fixed shape left most lanes of ragged boxes idle: a 70 x 70 layer takes
+// 18 tiles of 64 x 8 but 12 of 80 x 6.
+void fit_tile(int nx, int ny, int tx, int ty, int nt, int r3, int r2, int r1, TileShape &T) {
+  double best = 1e300;
+  auto consider = [&](int w, int h) {
+    if (w < 1 || h < 1 || w * h > nt || h > 48) return;
+    if (2 * (w + 2 + h) > nt || ((2 * w + 63) & ~63) + 2 * (h + 2) > nt) return;
+    if ((r3 && (w + 6) * (h + 6) > r3) || (r2 && (w + 4) * (h + 4) > r2)) return;
+    if ((w + 2) * (h + 2) > r1) return;
+    const double n = (double)((nx + w - 1) / w) * ((ny + h - 1) / h) * (1.0 + 4.0 / w);
+    if (n < best * (1.0 - 1e-9)) {
+      best = n;
+      T.w = w;
+      T.h = h;
+    }
+  };
+  consider(tx, ty);
+  for (int w = 8; w <= 128; w += 8)
+    for (int h = std::min(48, nt / w); h >= 1; --h) consider(w, h);
+  if (nx <= 128)
+    for (int h = std::min(48, nt / nx); h >= 1; --h) consider(nx, h);
+  T.d0 = make_fastdiv((uint32_t)T.w);
+  T.d2 = make_fastdiv((uint32_t)T.w + 2);
+  T.d4 = make_fastdiv((uint32_t)T.w + 4);
+  T.d6 = make_fastdiv((uint32_t)T.w + 6);
+}
+
+// z chunks [z0, z1) of a box: as few as zc slabs a chunk allow, of even
+// length, except that a box with z walls gets a chunk of `edge` slabs at each
+// wall, so that the chunks between them (whose stencils then stay clear of
+// the walls) run without wall logic.
 std::vector<std::pair<int, int>> z_chunks(const BoxDev &B, int zc, int edge) {
   std::vector<std::pair<int, int>> out;
   int lo = 0, hi = B.nz;
@@ -418,28 +452,71 @@ std::vector<std::pair<int, int>> z_chunks(const BoxDev &B, int zc, int edge) {
     lo = edge;
     hi = B.nz - edge;
   }
-  for (int z = lo; z < hi; z += zc) out.push_back({z, std::min(z + zc, hi)});
+  const int n = (hi - lo + zc - 1) / zc;
+  for (int k = 0; k < n; ++k)
+    out.push_back({lo + (int)((int64_t)(hi - lo) * k / n), lo + (int)((int64_t)(hi - lo) * (k + 1) / n)});
   if (hi < B.nz) out.push_back({hi, B.nz});
   return out;
+}
+
+// Longest chunk to cut the boxes into, at most zc and at least zc / 2: the
+// one with the least estimated time.  The blocks are assigned in order to the
+// places the GPU has for them (256 CUs of 1024 threads, the occupancy of the
+// tiled kernels); a block takes its slabs and `lead` more iterations, and an
+// iteration the longer the more of the places are taken: measured for the
+// compact fused kernel at 192^3, 4.1 us with 216 blocks and 6.3 us with 432
+// of 512 places, so a + b (places taken) with a : b = 2.1 : 4.6.
+int fit_chunk(const Layout &L, bool cpull, int zc, int nt, double lead) {
+  const size_t places = 256 * (size_t)(1024 / nt);
+  int best = zc;
+  double best_t = 1e300;
+  std::vector<double> busy;
+  for (int k = 0; k <= 8; ++k) {
+    const int z = std::max(1, zc - zc * k / 16);
+    size_t blocks = 0;
+    for (const BoxDev &B : L.boxes) {
+      const TileShape &T = cpull ? B.cs : B.fs;
+      blocks += (size_t)((B.nx + T.w - 1) / T.w) * ((B.ny + T.h - 1) / T.h) * ((B.nz + z - 1) / z);
+    }
+    if (blocks > 16 * places) return zc;  // many rounds: the last one matters little
+    busy.assign(places, 0.0);             // a min-heap of the places' end times
+    for (const BoxDev &B : L.boxes) {
+      const TileShape &T = cpull ? B.cs : B.fs;
+      const size_t cols = (size_t)((B.nx + T.w - 1) / T.w) * ((B.ny + T.h - 1) / T.h);
+      const int n = (B.nz + z - 1) / z;
+      const double len = (double)B.nz / n + lead;
+      for (size_t c = 0; c < cols * n; ++c) {
+        std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+        busy.back() += len;
+        std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+      }
+    }
+    const double t = *std::max_element(busy.begin(), busy.end()) *
+                     (2.1 + 4.6 * std::min(1.0, (double)blocks / places));
+    if (t < best_t * 0.98) {
+      best_t = t;
+      best = z;
+    }
+  }
+  return best;
 }
 
 // Tile lists of one kernel geometry: every (chunk, column) of every box,
 // split by tile_near_walls with the kernel's reach `halo`; `edge` slabs form
 // the chunks at z walls.
-void build_tiles(Layout &L, int tx, int ty, int zc, int halo, int edge,
-                 std::vector<TileEntry> &out, int32_t &nplain, bool cpull) {
+void build_tiles(Layout &L, int zc, int halo, int edge, std::vector<TileEntry> &out,
+                 int32_t &nplain, bool cpull) {
   std::vector<TileEntry> plain, near;
   for (size_t b = 0; b < L.boxes.size(); ++b) {
     BoxDev &B = L.boxes[b];
-    const int32_t ncx = (B.nx + tx - 1) / tx, ncy = (B.ny + ty - 1) / ty;
+    const TileShape &T = cpull ? B.cs : B.fs;
+    const int32_t ncx = (B.nx + T.w - 1) / T.w, ncy = (B.ny + T.h - 1) / T.h;
     if (cpull) {
-      B.ccol0 = 0;
       B.cncx = ncx;
       B.cncy = ncy;
       B.fccx = make_fastdiv((uint32_t)ncx);
       B.fccy = make_fastdiv((uint32_t)ncy);
     } else {
-      B.col0 = 0;
       B.ncx = ncx;
       B.ncy = ncy;
       B.fcx = make_fastdiv((uint32_t)ncx);
@@ -449,7 +526,7 @@ void build_tiles(Layout &L, int tx, int ty, int zc, int halo, int edge,
       for (int32_t cy = 0; cy < ncy; ++cy)
         for (int32_t cx = 0; cx < ncx; ++cx) {
           const TileEntry e = {(int32_t)b, cx + ncx * cy, zr.first, zr.second};
-          (tile_near_walls(B, cy * ty, ty, zr.first, zr.second, halo) ? near : plain).push_back(e);
+          (tile_near_walls(B, cy * T.h, T.h, zr.first, zr.second, halo) ? near : plain).push_back(e);
         }
   }
   nplain = pack_tiles(out, plain, near);
@@ -459,7 +536,9 @@ void build_tiles(Layout &L, int tx, int ty, int zc, int halo, int edge,
 // column and one slab beyond the chunk.
 void build_ccolumns(Layout &L, int v) {
   const CPullVariant &C = cpull_variant(v);
-  build_tiles(L, C.tx, C.ty, C.zc, 1, L.zedge ? 3 : 0, L.ccol_tiles, L.nccol_plain, true);
+  for (BoxDev &B : L.boxes) fit_tile(B.nx, B.ny, C.tx, C.ty, C.k->nt, 0, 0, C.k->r1, B.cs);
+  build_tiles(L, fit_chunk(L, true, C.zc, C.k->nt, 2.0), 1, L.zedge ? 3 : 0, L.ccol_tiles,
+              L.nccol_plain, true);
 }
 
 // Column table of fused variant v.  Its stencils reach three nodes around
@@ -467,7 +546,10 @@ void build_ccolumns(Layout &L, int v) {
 // loads run ahead (five below the chunk).
 void build_columns(Layout &L, int v) {
   const FusedVariant &F = fused_variant(v);
-  build_tiles(L, F.tx, F.ty, F.zc, 4, L.zedge ? 6 : 0, L.col_tiles, L.ncol_plain, false);
+  for (BoxDev &B : L.boxes)
+    fit_tile(B.nx, B.ny, F.tx, F.ty, F.k->nt, F.k->r3, F.k->r2, F.k->r1, B.fs);
+  build_tiles(L, fit_chunk(L, false, F.zc, F.k->nt, 6.0), 4, L.zedge ? 6 : 0, L.col_tiles,
+              L.ncol_plain, false);
   L.ncol = (int32_t)L.col_tiles.size();
 }
 
@@ -638,8 +720,8 @@ int launch_fused_compact(cglbm_handle *h, hipStream_t s) {
   float *aux = h->aux;
   void *dst = h->pop[1 - h->cur];
   int64_t plane = h->L.total;
-  const FusedFn *fn = storage_exact(h->storage) ? F.fcx : F.fc;
-  return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.tx * F.ty, s, boxes, cols, aux, dst,
+  const FusedFn *fn = storage_exact(h->storage) ? F.k->fcx : F.k->fc;
+  return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.k->nt, s, boxes, cols, aux, dst,
                       plane);
 }
 // rd: the wall stash this step's solid points emit from; the arrivals at
@@ -649,8 +731,8 @@ int launch_cpull(cglbm_handle *h, hipStream_t s, int rd = 0) {
   const bool x = storage_exact(h->storage);
   const int g = h->L.general ? 1 : 0;
   // the tiles away from walls, then those near them
-  const CPullFn fn[2] = {x ? C.fx[0] : C.fn[g][0],
-                         x ? C.fx[1] : C.fn[g][h->storage == CGLBM_FP32_PAIRS ? 2 : 1]};
+  const CPullFn fn[2] = {x ? C.k->fx[0] : C.k->fn[g][0],
+                         x ? C.k->fx[1] : C.k->fn[g][h->storage == CGLBM_FP32_PAIRS ? 2 : 1]};
   const int32_t n[2] = {h->L.nccol_plain, (int32_t)h->L.ccol_tiles.size() - h->L.nccol_plain};
   const bool both = (h->wmode & 2) && n[0] > 0 && n[1] > 0;
   if (both) {
@@ -659,7 +741,7 @@ int launch_cpull(cglbm_handle *h, hipStream_t s, int rd = 0) {
   }
   for (int w = 1; w >= 0; --w)
     if (n[w] > 0)
-      hipLaunchKernelGGL(fn[w], dim3((unsigned)n[w]), dim3(C.tx * C.ty), 0,
+      hipLaunchKernelGGL(fn[w], dim3((unsigned)n[w]), dim3((unsigned)C.k->nt), 0,
                          (both && w) ? h->side : s, h->d_boxes, h->d_ccol_tiles + (w ? n[0] : 0),
                          (const float *)h->pop[1 - h->cur], h->aux, h->L.total,
                          (const void *)h->cstash[rd], h->cstash[1 - rd], h->L.wtotal);
@@ -710,8 +792,8 @@ int launch_fused(cglbm_handle *h, hipStream_t s, int export_fields) {
   float *aux = h->aux;
   void *dst = h->pop[1 - h->cur];
   int64_t plane = h->L.total;
-  const FusedFn *fn = export_fields ? F.fx : F.fn[h->storage];
-  return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.tx * F.ty, s, boxes, cols, aux, dst,
+  const FusedFn *fn = export_fields ? F.k->fx : F.k->fn[h->storage];
+  return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.k->nt, s, boxes, cols, aux, dst,
                       plane);
 }
 

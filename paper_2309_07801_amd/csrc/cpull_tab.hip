@@ -1,17 +1,16 @@
-// cpull_tab.hip -- launch-geometry table of the compact schedule's pull (tables.hpp).
+// cpull_tab.hip -- launch geometries of the compact schedule's pull (tables.hpp).
 #include <hip/hip_runtime.h>
 
 #include "tables.hpp"
 
 namespace cglbm {
-#define CV_M(TX, TY, ZC, G)                                                              \
-  {k_cpull<TX, TY, ZC, false, StoreF32, G>, k_cpull<TX, TY, ZC, true, StoreF32, G>,      \
-   k_cpull<TX, TY, ZC, true, StoreF32P, G>}
-#define CV(TX, TY, ZC)                                                                   \
-  {TX, TY, ZC, {CV_M(TX, TY, ZC, false), CV_M(TX, TY, ZC, true)},                        \
-   {k_cpull<TX, TY, ZC, false, StoreF32X, false>, k_cpull<TX, TY, ZC, true, StoreF32X, false>}}
-const CPullVariant kCPullTable[5] = {CV(64, 8, 64), CV(64, 8, 32), CV(32, 8, 32), CV(64, 4, 32),
-                                     CV(32, 8, 64)};
-#undef CV
-#undef CV_M
+#define CK_M(G, GEN)                                                              \
+  {k_cpull<G, false, StoreF32, GEN>, k_cpull<G, true, StoreF32, GEN>,             \
+   k_cpull<G, true, StoreF32P, GEN>}
+#define CK(G)                                                                     \
+  {G::NT, G::R1, {CK_M(G, false), CK_M(G, true)},                                 \
+   {k_cpull<G, false, StoreF32X, false>, k_cpull<G, true, StoreF32X, false>}}
+const CPullKernels kCPull256 = CK(CG256), kCPull512 = CK(CG512);
+#undef CK
+#undef CK_M
 }  // namespace cglbm

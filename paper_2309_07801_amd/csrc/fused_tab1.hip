@@ -1,8 +1,8 @@
-// fused_tab1.hip -- part 1 of the fused kernel's launch-geometry table (tables.hpp).
+// fused_tab1.hip -- part 1 of the fused kernel's launch geometries (tables.hpp).
 #include <hip/hip_runtime.h>
 
 #include "tables.hpp"
 
 namespace cglbm {
-const FusedVariant kFusedPart1[4] = {CGLBM_FV(32, 16, 32, 4), CGLBM_FV(32, 16, 64, 4), CGLBM_FV(64, 4, 32, 4), CGLBM_FV(32, 4, 32, 4)};
+const FusedKernels kFusedPart1[2] = {CGLBM_FK(FG512, 4), CGLBM_FK(FG1024, 4)};
 }  // namespace cglbm

@@ -41,6 +41,14 @@ enum AuxPlane {
   A_QX = 17, A_QY = 18, A_QZ = 19, A_KAPPA = 20, A_COUNT = 21
 };
 
+// The column tile of a box in a z-marching kernel (k_fused, k_cpull): w x h
+// nodes, thread t of the block owning node (t mod w, t / w); threads past
+// w h own none.  d0, d2, d4, d6 divide by w, w + 2, w + 4 and w + 6.
+struct TileShape {
+  int32_t w, h;
+  FastDiv d0, d2, d4, d6;
+};
+
 // Per-box constants, filled on the host.
 struct BoxDev {
   int32_t nx, ny, nz;
@@ -52,8 +60,7 @@ struct BoxDev {
   int32_t tnx, tny;     // tiles along x, y
   FastDiv fdx, fdy;     // division by nx, ny
   FastDiv ftx, fty;     // division by tnx, tny
-  int32_t col0;         // unused (blocks carry their box and tile: TileEntry)
-  int32_t ncx, ncy;     // columns along x, y
+  int32_t ncx, ncy;     // k_fused columns along x, y
   FastDiv fcx, fcy;     // division by ncx, ncy
   float cs2r, cs2b;     // (c_s^k)^2 = xi (1 - alpha_k)
   float ir0r, ir0b;     // 1 / rho_k^0
@@ -74,10 +81,10 @@ struct BoxDev {
   int32_t d2q9;         // 1: two-dimensional box of the D2Q9 lattice (App. A)
   int32_t wbase, wn;    // wall-node slots of the box in the in-place stash
   int32_t wblk0;        // first block of the box in k_wall_copy
-  int32_t ccol0;        // unused (see col0)
   int32_t rch0;         // first reduction chunk of the box (k_reduce1, k_reduce2)
   int32_t cncx, cncy;   // k_cpull columns along x, y
   FastDiv fccx, fccy;   // division by cncx, cncy
+  TileShape fs, cs;     // column tiles of k_fused and k_cpull
 };
 
 constexpr int kBlock = 256;
@@ -1529,33 +1536,38 @@ __global__ __launch_bounds__(kBlock) void k_init(const BoxDev *__restrict__ boxe
 
 // ---------------------------------------------------------------------------
 // k_fused: interface stencils and collision in one pass.  A block owns a
-// TX x TY column of the box and marches along z over ZC output slabs.  Slab
+// column of the box and marches along z over a chunk of output slabs.  Slab
 // s of the phase field enters a 3-slot LDS ring; n and |grad phi| of slab
 // s-1, and q = (p - rho c_s^2) u of slab s-2 follow in their own rings; the
 // correction term and the collision of slab s-3 complete the iteration.
 // Halo widths in x, y: 3 for phi, 2 for n, 1 for q.
+//
+// The tile's extents are run-time values (TileShape, fitted to the box by the
+// host: a fixed 64 x 8 tile spends 40 % of its lanes on nothing in boxes of
+// 24 to 128 nodes an edge); a geometry fixes the block's threads and how many
+// points of each ring its LDS arrays hold.
 // ---------------------------------------------------------------------------
-template <int TX, int TY>
+template <int NT_, int R3_, int R2_, int R1_>
 struct FusedGeom {
-  static constexpr int NT = TX * TY;
-  static constexpr int R3X = TX + 6, R3Y = TY + 6, R3 = R3X * R3Y;
-  static constexpr int R2X = TX + 4, R2Y = TY + 4, R2 = R2X * R2Y;
-  static constexpr int R1X = TX + 2, R1Y = TY + 2, R1 = R1X * R1Y;
-  static constexpr int A_PER = (R3 + NT - 1) / NT;
+  static constexpr int NT = NT_;
+  // points held of phi (tile + 3), n (tile + 2) and q (tile + 1)
+  static constexpr int R3 = R3_, R2 = R2_, R1 = R1_;
+  static constexpr int A_PER = (R3 + NT - 1) / NT, B_PER = (R2 + NT - 1) / NT;
+  static constexpr int kMaxRows = 64;  // of a tile with its halo of 3
 };
 
 // COMPACT: store each node's compact post-collision state (17 float planes
 // of dst, see compact_of) instead of its populations.
-template <int TX, int TY, int ZC, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false>
-__global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict__ boxes,
+template <class G, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false>
+__global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
                                                   float *__restrict__ aux,
                                                   void *__restrict__ dst_, int64_t plane_arg) {
-  using G = FusedGeom<TX, TY>;
+  constexpr int NT = G::NT;
   __shared__ float s_phi[3][G::R3];
   __shared__ float s_n[3][4][G::R2];
   __shared__ float s_q[3][3][G::R1];
-  __shared__ uint8_t s_sy[G::R3Y];
+  __shared__ uint8_t s_sy[G::kMaxRows];
 
   const int tid = threadIdx.x;
   const uint32_t lb = xcd_block();
@@ -1566,67 +1578,78 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
   const uint32_t cyu = fdiv((uint32_t)te.xy, B.fcx);
   const int cx = (int)((uint32_t)te.xy - cyu * (uint32_t)B.ncx);
   const int cy = (int)cyu;
-  const int x0 = cx * TX, y0 = cy * TY, z0 = te.z0;
+  const int TW = B.fs.w, TH = B.fs.h;
+  const int R3X = TW + 6, R2X = TW + 4, R1X = TW + 2;
+  const int n3 = R3X * (TH + 6), n2 = R2X * (TH + 4);
+  const int own = TW * TH, ring = 2 * (R1X + TH);  // tile points, halo-1 points around them
+  const int x0 = cx * TW, y0 = cy * TH, z0 = te.z0;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
   const int z1 = te.z1;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
   const bool zwalls = WALLS && (B.walls & 2u) != 0;
 
-  for (int i = tid; i < G::R3Y; i += G::NT) {
-    const int gy = wrap_any(y0 + i - 3, ny);
-    s_sy[i] = WALLS && (B.walls & 1u) && (gy == 0 || gy == ny - 1);
-  }
+  if (WALLS)
+    for (int i = tid; i < TH + 6; i += NT) {
+      const int gy = wrap_any(y0 + i - 3, ny);
+      s_sy[i] = (B.walls & 1u) && (gy == 0 || gy == ny - 1);
+    }
   // solid flag of an R3 row (always false without walls)
   auto sy = [&](int r) -> bool { return WALLS ? (bool)s_sy[r] : false; };
   // xy offsets of this thread's phase-field points (fixed over the march)
   int a_off[G::A_PER];
 #pragma unroll
   for (int k = 0; k < G::A_PER; ++k) {
-    const int i = tid + k * G::NT;
+    const int i = tid + k * NT;
     a_off[k] = 0;
-    if (i < G::R3) {
-      const int lx = i % G::R3X, ly = i / G::R3X;
+    if (i < n3) {
+      const int ly = (int)fdiv((uint32_t)i, B.fs.d6), lx = i - ly * R3X;
       a_off[k] = wrap_any(x0 + lx - 3, nx) + nx * wrap_any(y0 + ly - 3, ny);
     }
   }
-  // R1 points of this thread: the tile point first, then the halo ring
-  // (top and bottom rows, then the two side columns)
-  auto r1_point = [&](int j, int &lx, int &ly) {
-    if (j < G::NT) {
-      lx = (j % TX) + 1;
-      ly = (j / TX) + 1;
-    } else {
-      const int h = j - G::NT;
-      if (h < 2 * G::R1X) {
-        lx = h % G::R1X;
-        ly = (h / G::R1X) * (G::R1Y - 1);
-      } else {
-        const int h2 = h - 2 * G::R1X;
-        lx = (h2 & 1) * (G::R1X - 1);
-        ly = (h2 >> 1) + 1;
-      }
-    }
-  };
-  constexpr int C_PER = (G::R1 + G::NT - 1) / G::NT;
+  // and of its normals: the stencil's centre in the phi ring and its row
+  int b_c3[G::B_PER], b_ly[G::B_PER];
+#pragma unroll
+  for (int k = 0; k < G::B_PER; ++k) {
+    const int i = min(tid + k * NT, n2 - 1);
+    const int ly = (int)fdiv((uint32_t)i, B.fs.d4), lx = i - ly * R2X;
+    b_ly[k] = ly;
+    b_c3[k] = (lx + 1) + R3X * (ly + 1);
+  }
+  // halo-1 points of this thread: its tile point, then one of the ring (top
+  // and bottom rows, then the two side columns)
+  constexpr int C_PER = 2;
+  const bool c_has[C_PER] = {tid < own, tid < ring};
   uint32_t c_off[C_PER];
+  int c_c2[C_PER], c_ri[C_PER], c_ly[C_PER];
 #pragma unroll
   for (int kk = 0; kk < C_PER; ++kk) {
-    const int j = tid + kk * G::NT;
-    c_off[kk] = 0;
-    if (j < G::R1) {
-      int lx, ly;
-      r1_point(j, lx, ly);
-      c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + (uint32_t)nx * (uint32_t)wrap_any(y0 + ly - 1, ny);
+    int lx = 1, ly = 1;
+    if (kk == 0) {
+      if (tid < own) {
+        const int r = (int)fdiv((uint32_t)tid, B.fs.d0);
+        lx = tid - r * TW + 1;
+        ly = r + 1;
+      }
+    } else if (tid < 2 * R1X) {
+      ly = tid < R1X ? 0 : TH + 1;
+      lx = tid < R1X ? tid : tid - R1X;
+    } else if (tid < ring) {
+      const int h2 = tid - 2 * R1X;
+      lx = (h2 & 1) * (TW + 1);
+      ly = (h2 >> 1) + 1;
     }
+    c_ly[kk] = ly;
+    c_c2[kk] = (lx + 1) + R2X * (ly + 1);
+    c_ri[kk] = lx + R1X * ly;
+    c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + (uint32_t)nx * (uint32_t)wrap_any(y0 + ly - 1, ny);
   }
   // tile point of this thread
-  const int ox = tid % TX, oy = tid / TX;
-  const int gxo = x0 + ox, gyo = y0 + oy;
-  const bool in_xy = gxo < nx && gyo < ny;
-  // the tile point clamped into the box: lanes outside it load valid
-  // addresses and store nowhere
-  const uint32_t oxy = (uint32_t)min(gxo, nx - 1) + (uint32_t)nx * (uint32_t)min(gyo, ny - 1);
-  const bool solid_y_o = (B.walls & 1u) && (gyo == 0 || gyo == ny - 1);
+  const int oy = c_ly[0] - 1;
+  const int gxo = x0 + c_ri[0] - R1X * c_ly[0] - 1, gyo = y0 + oy;
+  const bool in_xy = c_has[0] && gxo < nx && gyo < ny;
+  // (lanes without a node of the box load at wrapped, valid addresses and
+  // store nowhere)
+  const bool solid_y_o = WALLS && (B.walls & 1u) && (gyo == 0 || gyo == ny - 1);
   // interface values of the tile point, one slab behind the q ring
   float h_nx = 0.f, h_ny = 0.f, h_nz = 0.f, h_Fx = 0.f, h_Fy = 0.f, h_Fz = 0.f, h_k = 0.f;
   auto slab_solid = [&](int s) {
@@ -1641,7 +1664,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
   // never include those stores, which share the in-order vector memory
   // counter with the loads.
   // (except the loads of a wavefront's later points when none of its lanes
-  // has one, e.g. the second R1 point in five of the eight wavefronts of a
+  // has one, e.g. the ring point in five of the eight wavefronts of a
   // 64x8 column: their values are set to zero instead)
   float a_rr[G::A_PER], a_rb[G::A_PER];
   float pc_[C_PER][5];
@@ -1650,7 +1673,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
     const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)wrap_any(sl, nz);
 #pragma unroll
     for (int k = 0; k < G::A_PER; ++k) {
-      if (k > 0 && wave0 + k * G::NT >= G::R3) {
+      if (k > 0 && wave0 + k * NT >= n3) {
         a_rr[k] = a_rb[k] = 0.f;
         continue;
       }
@@ -1663,7 +1686,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
     const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)wrap_any(sl, nz);
 #pragma unroll
     for (int kk = 0; kk < C_PER; ++kk) {
-      if (kk > 0 && wave0 + kk * G::NT >= G::R1) {
+      if (kk > 0 && wave0 >= ring) {
 #pragma unroll
         for (int m = 0; m < 5; ++m) pc_[kk][m] = 0.f;
         continue;
@@ -1676,7 +1699,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
       pc_[kk][4] = ldpl(aux, pl, A_JZ, node);
     }
   };
-  // inputs of the collision at the (clamped) tile point.  With 16-bit
+  // inputs of the collision at the tile point.  With 16-bit
   // storage they are loaded one iteration ahead, inside the collision before
   // its first store (measured faster); with 32-bit storage at the top of the
   // iteration (the earlier issue measured slower there).
@@ -1685,7 +1708,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
   double d_rr = 0.0, d_rb = 0.0;
   auto load_d = [&](int sl, int64_t pl) {
     if (EXPORT) return;
-    const uint32_t node = (uint32_t)B.base + oxy + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t node = (uint32_t)B.base + c_off[0] + nxy * (uint32_t)wrap_any(sl, nz);
     // the second moments and FP64 densities are read by stage D only
     if (S::kExact) {
       const double *r64 = aux_rho64(aux, pl);
@@ -1735,14 +1758,13 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
   for (int s = z0 - 3; s < z1 + 3; ++s) {
     const int64_t plane = opaque_i64(plane_arg);
     if (!kPipeD) load_d(s - 3, plane);
-    // inputs of the collision of slab s-3 at the (clamped) tile point
     // ---- A: phase field of slab s (Eq. 14) ----
     {
       float *ph = s_phi[(s + 3) % 3];
 #pragma unroll
       for (int k = 0; k < G::A_PER; ++k) {
-        const int i = tid + k * G::NT;
-        if (i < G::R3) {
+        const int i = tid + k * NT;
+        if (i < n3) {
           const float rr = a_rr[k] * B.ir0r;
           const float rb = a_rb[k] * B.ir0b;
           ph[i] = phase_field(rr, rb);
@@ -1758,9 +1780,11 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
       const float *pc = s_phi[(sb + 3) % 3];
       const float *pp = s_phi[(sb + 1 + 3) % 3];
       float(*nn)[G::R2] = s_n[(sb + 3) % 3];
-      for (int i = tid; i < G::R2; i += G::NT) {
-        const int lx = i % G::R2X, ly = i / G::R2X;
-        const int c3 = (lx + 1) + G::R3X * (ly + 1);
+#pragma unroll
+      for (int k = 0; k < G::B_PER; ++k) {
+        const int i = tid + k * NT;
+        if (i >= n2) break;
+        const int c3 = b_c3[k], ly = b_ly[k];
         float nxv = 0.f, nyv = 0.f, nzv = 0.f, mag = 0.f;
         if (!(sy(ly + 1) | sz_c)) {
           const float vc = pc[c3];
@@ -1774,7 +1798,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
               const bool sd = szd | sy(ly + 1 + dy);
 #pragma unroll
               for (int dx = -1; dx <= 1; ++dx)
-                v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c3 + dx + G::R3X * dy]);
+                v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c3 + dx + R3X * dy]);
             }
           }
           float gx = 0.f, gy = 0.f, gz = 0.f;
@@ -1815,12 +1839,8 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
       // first pass: the tile points in thread order, then the halo ring
 #pragma unroll
       for (int kk = 0; kk < C_PER; ++kk) {
-        const int j = tid + kk * G::NT;
-        if (j >= G::R1) break;
-        int lx, ly;
-        r1_point(j, lx, ly);
-        const int c2 = (lx + 1) + G::R2X * (ly + 1);
-        const int ri = lx + G::R1X * ly;
+        if (!c_has[kk]) continue;
+        const int ly = c_ly[kk], c2 = c_c2[kk], ri = c_ri[kk];
         float qx = 0.f, qy = 0.f, qz = 0.f;
         float kap = 0.f, Fx = 0.f, Fy = 0.f, Fz = 0.f;
         const float nxv = nc[0][c2], nyv = nc[1][c2], nzv = nc[2][c2], mag = nc[3][c2];
@@ -1839,7 +1859,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
                 const bool sd = szd | sy(ly + 2 + dy);
 #pragma unroll
                 for (int dx = -1; dx <= 1; ++dx)
-                  v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c2 + dx + G::R2X * dy]);
+                  v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c2 + dx + R2X * dy]);
               }
             }
             float gx = 0.f, gy = 0.f, gz = 0.f;
@@ -1877,7 +1897,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
         qq[0][ri] = qx;
         qq[1][ri] = qy;
         qq[2][ri] = qz;
-        if (j < G::NT) {
+        if (kk == 0) {
           f_nx = nxv;
           f_ny = nyv;
           f_nz = nzv;
@@ -1903,7 +1923,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
       float(*qm)[G::R1] = s_q[(sd + 8) % 3];
       float(*qc)[G::R1] = s_q[(sd + 9) % 3];
       float(*qp)[G::R1] = s_q[(sd + 10) % 3];
-      const int c1 = (ox + 1) + G::R1X * (oy + 1);
+      const int c1 = c_ri[0];
       // d q_x / dx: pairs along x over (dy, dz); likewise y and z
       float Qx = 0.f, Qy = 0.f, Qz = 0.f;
 #pragma unroll
@@ -1915,30 +1935,30 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
             const float *pl = b2 < 0 ? qm[0] : (b2 > 0 ? qp[0] : qc[0]);
             const bool sdd = (b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false)) | sy(oy + 3 + a2);
             const float vc = qc[0][c1];
-            const float vp = wall_rule(sdd, vc, pl[c1 + 1 + G::R1X * a2]);
-            const float vm = wall_rule(sdd, vc, pl[c1 - 1 + G::R1X * a2]);
+            const float vp = wall_rule(sdd, vc, pl[c1 + 1 + R1X * a2]);
+            const float vm = wall_rule(sdd, vc, pl[c1 - 1 + R1X * a2]);
             Qx = fmaf(w, vp - vm, Qx);
           }
           {  // y: a2 = dx, b2 = dz
             const float *pl = b2 < 0 ? qm[1] : (b2 > 0 ? qp[1] : qc[1]);
             const bool szd = b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false);
             const float vc = qc[1][c1];
-            const float vp = wall_rule(szd | sy(oy + 4), vc, pl[c1 + a2 + G::R1X]);
-            const float vm = wall_rule(szd | sy(oy + 2), vc, pl[c1 + a2 - G::R1X]);
+            const float vp = wall_rule(szd | sy(oy + 4), vc, pl[c1 + a2 + R1X]);
+            const float vm = wall_rule(szd | sy(oy + 2), vc, pl[c1 + a2 - R1X]);
             Qy = fmaf(w, vp - vm, Qy);
           }
           {  // z: a2 = dx, b2 = dy
             const bool syd = sy(oy + 3 + b2);
             const float vc = qc[2][c1];
-            const float vp = wall_rule(sz_p | syd, vc, qp[2][c1 + a2 + G::R1X * b2]);
-            const float vm = wall_rule(sz_m | syd, vc, qm[2][c1 + a2 + G::R1X * b2]);
+            const float vp = wall_rule(sz_p | syd, vc, qp[2][c1 + a2 + R1X * b2]);
+            const float vm = wall_rule(sz_m | syd, vc, qm[2][c1 + a2 + R1X * b2]);
             Qz = fmaf(w, vp - vm, Qz);
           }
         }
       Qx *= -3.0f;
       Qy *= -3.0f;
       Qz *= -3.0f;
-      const uint32_t node = (uint32_t)B.base + oxy + nxy * (uint32_t)wrap_any(sd, nz);
+      const uint32_t node = (uint32_t)B.base + c_off[0] + nxy * (uint32_t)wrap_any(sd, nz);
       if (!EXPORT) {
         NodeIn in = din;
         in.nx = h_nx;
@@ -1997,7 +2017,7 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
 // k_cpull: the pull of the compact schedule.  The stored state is the
 // compact post-collision state of every node (k_fused<..., COMPACT>); the
 // moments of a node after streaming (Eq. 5) are sums of its neighbours'
-// collided populations, f_i(x) = f*_i(x - c_i).  A block owns a TX x TY
+// collided populations, f_i(x) = f*_i(x - c_i).  A block owns a
 // column and marches along z: for slab s it rebuilds the collided
 // populations of the column and its one-node ring in registers (z and y
 // passes of the back-transform), then, for each z component cz of the
@@ -2018,44 +2038,27 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_fused(const BoxDev *__restrict
 // sums of the arrivals and that rest, so each colour's mass is conserved to
 // FP64 rounding; they go to the FP64 aux planes as well.
 // ---------------------------------------------------------------------------
-template <int TX, int TY>
+// The tile's extents are run-time values (TileShape), as in k_fused: at 24
+// boxes of 24 to 128 nodes an edge the pull takes 421 us a step instead of
+// 540, at 160^3 with mass-exact storage 164 instead of 194; on the 256^3 box,
+// which the nominal 64 x 8 tile divides, it takes the same 440.  The state is
+// read through plane pointers (two scalar registers a plane) and not
+// descriptors (four): 17 of those had spilled to vector lanes.  A
+// geometry fixes the block's threads and the ring points its LDS array holds.
+template <int NT_, int R1_, int W_ = 0>
 struct CPullGeom {
-  static constexpr int NT = TX * TY;
-  static constexpr int R1X = TX + 2, R1Y = TY + 2, R1 = R1X * R1Y;
-  static constexpr int CP = (R1 + NT - 1) / NT;  // ring points per thread
-  // the halo fills whole wavefronts: those of the rows first, then one or
-  // more of the columns
-  static_assert(CP == 2 && NT % 64 == 0 && (2 * TX) % 64 == 0, "ring layout");
-  // ring point j of the block: the column's own points first (thread j's
-  // column node), then the halo: the rows below and above the tile (without
-  // the corners), then the columns beside it (corners included); (lx, ly) in
-  // the (TX + 2) x (TY + 2) ring
-  __device__ static void point(int j, int &lx, int &ly) {
-    if (j < NT) {
-      lx = (j % TX) + 1;
-      ly = (j / TX) + 1;
-    } else {
-      const int h = j - NT;
-      if (h < 2 * TX) {
-        lx = h % TX + 1;
-        ly = (h / TX) * (R1Y - 1);
-      } else {
-        const int h2 = h - 2 * TX;
-        lx = (h2 & 1) * (R1X - 1);
-        ly = h2 >> 1;
-      }
-    }
-  }
+  static constexpr int NT = NT_, R1 = R1_, W = W_;
+  static constexpr int CP = 2;  // ring points per thread: its column node, a halo point
+  static_assert(NT % 64 == 0, "whole wavefronts");
 };
 
-template <int TX, int TY, int ZC, bool WALLS = false, class S = StoreF32, bool GENERAL = false>
-__global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ boxes,
+template <class G, bool WALLS = false, class S = StoreF32, bool GENERAL = false>
+__global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
                                                   const float *__restrict__ cst,
                                                   float *__restrict__ aux, int64_t plane_arg,
                                                   const void *__restrict__ wst_in,
                                                   void *__restrict__ wst_out, int64_t wplane) {
-  using G = CPullGeom<TX, TY>;
   constexpr bool EXACT = S::kExact;
   __shared__ float xb[18][G::R1];  // one z component: 9 directions x 2 colours
   const int tid = threadIdx.x;
@@ -2067,51 +2070,63 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
   const uint32_t cyu = fdiv((uint32_t)te.xy, B.fccx);
   const int cxi = (int)((uint32_t)te.xy - cyu * (uint32_t)B.cncx);
   const int cyi = (int)cyu;
-  const int x0 = cxi * TX, y0 = cyi * TY, z0 = te.z0;
+  const int TW = G::W ? G::W : B.cs.w, TH = G::W ? G::NT / G::W : B.cs.h, R1X = TW + 2;
+  const int x0 = cxi * TW, y0 = cyi * TH, z0 = te.z0;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
   const int z1 = te.z1;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
-  // ring points of this thread (its own column node first, then a halo
-  // point or none) and their LDS slots (row-major in the ring); wavefronts
-  // with no halo point skip the second pass, and the lanes past the ring in
-  // the last halo wavefront read point 0 and write nothing
+  // Ring points of this thread (its own column node first, then a halo point
+  // or none) and their LDS slots (row-major in the (TW + 2) x (TH + 2) ring).
+  // Halo points: the rows below and above the tile (without the corners) in
+  // whole wavefronts, then the columns beside it (corners included), so that
+  // a wavefront holds rows only or columns only; wavefronts with no halo
+  // point skip the second pass, and lanes past the rows or the ring in a
+  // halo wavefront read a valid point and write nothing.
+  const int rows_end = (2 * TW + 63) & ~63, halo_end = rows_end + 2 * (TH + 2);
   uint32_t roff[G::CP];
   int rgx[G::CP], rgy[G::CP], rls[G::CP];
   // a halo point's one c_y row (above or below the tile) or c_x column
   // (beside it) that reaches the tile: c = +1 (true) or -1
   bool rfwd = false;
-  // a wavefront of halo points holds rows only or columns only; the
-  // wavefronts past the halo have no second point
   const int wave0 = (int)__builtin_amdgcn_readfirstlane(tid);
-  const bool rowwave = wave0 < 2 * TX, halowave = wave0 + G::NT < G::R1;
+  const bool rowwave = wave0 < rows_end, halowave = wave0 < halo_end;
+  const bool has[G::CP] = {tid < TW * TH, tid < 2 * TW || (tid >= rows_end && tid < halo_end)};
 #pragma unroll
   for (int k = 0; k < G::CP; ++k) {
-    const int j = tid + k * G::NT;
-    roff[k] = 0;
-    rgx[k] = rgy[k] = rls[k] = 0;
-    if (j < G::R1) {
-      int lx, ly;
-      G::point(j, lx, ly);
-      if (k > 0) rfwd = rowwave ? ly == 0 : lx == 0;
-      rls[k] = lx + G::R1X * ly;
-      rgx[k] = wrap_any(x0 + lx - 1, nx);
-      rgy[k] = wrap_any(y0 + ly - 1, ny);
-      roff[k] = (uint32_t)rgx[k] + (uint32_t)nx * (uint32_t)rgy[k];
+    int lx = 1, ly = 1;
+    if (has[k]) {
+      if (k == 0) {
+        const int r = (int)fdiv((uint32_t)tid, B.cs.d0);
+        lx = tid - r * TW + 1;
+        ly = r + 1;
+      } else if (rowwave) {
+        lx = (tid < TW ? tid : tid - TW) + 1;
+        ly = tid < TW ? 0 : TH + 1;
+      } else {
+        const int h2 = tid - rows_end;
+        lx = (h2 & 1) * (TW + 1);
+        ly = h2 >> 1;
+      }
     }
+    if (k > 0) rfwd = rowwave ? ly == 0 : lx == 0;
+    rls[k] = lx + R1X * ly;
+    rgx[k] = wrap_any(x0 + lx - 1, nx);
+    rgy[k] = wrap_any(y0 + ly - 1, ny);
+    roff[k] = (uint32_t)rgx[k] + (uint32_t)nx * (uint32_t)rgy[k];
   }
-  const int ox = tid % TX, oy = tid / TX;
-  const bool in_xy = x0 + ox < nx && y0 + oy < ny;
-  const int gxo = min(x0 + ox, nx - 1), gyo = min(y0 + oy, ny - 1);
-  const uint32_t oxy = (uint32_t)min(x0 + ox, nx - 1) + (uint32_t)nx * (uint32_t)min(y0 + oy, ny - 1);
-  // moments of slabs s-1, s, s+1 at the column node
+  // the column node lies in the box (not past its last column or row)
+  const bool in_xy = has[0] && rgx[0] >= x0 && rgy[0] >= y0;
+  // moments of slabs s-1, s, s+1 at the column node; those of s+1 begin with
+  // the arrivals from s (an assignment: zeroing them and adding cost 20
+  // operations a node)
   float acc[3][11];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int m = 0; m < 11; ++m) acc[a][m] = 0.f;
   double acc64[3][2];  // mass-exact storage: the colour densities in FP64
 #pragma unroll
-  for (int a = 0; a < 3; ++a) acc64[a][0] = acc64[a][1] = 0.0;
+  for (int a = 0; a < 2; ++a) acc64[a][0] = acc64[a][1] = 0.0;
 
   for (int s = z0 - 1; s <= z1; ++s) {
     const int64_t plane = opaque_i64(plane_arg);
@@ -2124,13 +2139,13 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
     bool rsolid[G::CP];
 #pragma unroll
     for (int k = 0; k < G::CP; ++k)
-      rsolid[k] = WALLS && tid + k * G::NT < G::R1 && is_solid(B, rgy[k], gz);
+      rsolid[k] = WALLS && has[k] && is_solid(B, rgy[k], gz);
     // the column node's FP64 colour densities at slab s (its ring point k = 0)
     double own_r = 0.0, own_b = 0.0;
     if constexpr (EXACT) {
       const double *r64 = compact_rho64(const_cast<float *>(cst), plane);
-      own_r = buf_ld_f64(plane_rsrc(r64, plane * 8, 0), (zoff + oxy) * 8u);
-      own_b = buf_ld_f64(plane_rsrc(r64, plane * 8, 1), (zoff + oxy) * 8u);
+      own_r = buf_ld_f64(plane_rsrc(r64, plane * 8, 0), (zoff + roff[0]) * 8u);
+      own_b = buf_ld_f64(plane_rsrc(r64, plane * 8, 1), (zoff + roff[0]) * 8u);
     }
     float h[G::CP][3][3][3];
     float pux[G::CP], pcr[G::CP], pcb[G::CP], pRx[G::CP], pRy[G::CP], pRz[G::CP];
@@ -2149,7 +2164,7 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
       }
       float c[kCompact];
 #pragma unroll
-      for (int m = 0; m < kCompact; ++m) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
+      for (int m = 0; m < kCompact; ++m) c[m] = at(PL(cst, m), zoff + roff[k]);
       CompactPost o;
       compact_post<GENERAL>(B, c, o);
       float g[3][3][3];
@@ -2180,8 +2195,7 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
       // z component pz - 1, as emit_recoloured computes them
 #pragma unroll
       for (int k = 0; k < G::CP; ++k) {
-        const int j = tid + k * G::NT;
-        if ((k == 0 || halowave) && j < G::R1) {
+        if ((k == 0 || halowave) && has[k]) {
           // a solid ring point: what the bounce-back stored for these
           // directions, loaded before the emission so that the loads'
           // latency passes behind it
@@ -2290,7 +2304,7 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
 #pragma unroll
           for (int cx = 0; cx < 3; ++cx) {
             const int q = 3 * cy + cx;
-            const int src = (ox + 2 - cx) + G::R1X * (oy + 2 - cy);
+            const int src = rls[0] + (1 - cx) + R1X * (1 - cy);
             fr[q] = xb[2 * q][src];
             fb[q] = xb[2 * q + 1][src];
             f[q] = fr[q] + fb[q];
@@ -2311,8 +2325,8 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
             s64r += (double)fr[q];
             s64b += (double)fb[q];
           }
-          acc64[pz][0] += s64r;
-          acc64[pz][1] += s64b;
+          acc64[pz][0] = pz == 2 ? s64r : acc64[pz][0] + s64r;
+          acc64[pz][1] = pz == 2 ? s64b : acc64[pz][1] + s64b;
         }
         float r0[3], r1[3], r2[3];  // per row: sum, c_x-weighted, c_x^2-weighted
 #pragma unroll
@@ -2355,8 +2369,8 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
         if (WALLS) {
           // a solid column node keeps what arrives, reversed, for the next step
           const int d = s + pz - 1, gd = wrap_any(d, nz);
-          if (in_xy && d >= z0 && d < z1 && is_solid(B, gyo, gd)) {
-            const uint32_t slot = (uint32_t)B.wbase + wall_slot(B, gxo, gyo, gd);
+          if (in_xy && d >= z0 && d < z1 && is_solid(B, rgy[0], gd)) {
+            const uint32_t slot = (uint32_t)B.wbase + wall_slot(B, rgx[0], rgy[0], gd);
 #pragma unroll
             for (int cy = 0; cy < 3; ++cy)
 #pragma unroll
@@ -2375,19 +2389,24 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
           }
         }
         float *a = acc[pz];
-        a[0] += sr;
-        a[1] += sb;
-        a[2] += m10;
-        a[3] += m01;
-        a[5] += m20;
-        a[6] += m02;
-        a[8] += m11;
-        if (pz != 1) {
-          const bool up = pz == 2;
-          a[4] += up ? m00d : -m00d;
-          a[7] += m00;
-          a[9] += up ? m10 : -m10;
-          a[10] += up ? m01 : -m01;
+        if (pz == 2) {
+          const float v[11] = {sr, sb, m10, m01, m00d, m20, m02, m00, m11, m10, m01};
+#pragma unroll
+          for (int m = 0; m < 11; ++m) a[m] = v[m];
+        } else {
+          a[0] += sr;
+          a[1] += sb;
+          a[2] += m10;
+          a[3] += m01;
+          a[5] += m20;
+          a[6] += m02;
+          a[8] += m11;
+          if (pz == 0) {
+            a[4] -= m00d;
+            a[7] += m00;
+            a[9] -= m10;
+            a[10] -= m01;
+          }
         }
       }
       __syncthreads();
@@ -2399,9 +2418,9 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
     }
     // slab s - 1 is complete (solid nodes: zero moments)
     const int gzm = wrap_any(s - 1, nz);
-    const uint32_t node = (uint32_t)B.base + oxy + nxy * (uint32_t)gzm;
+    const uint32_t node = (uint32_t)B.base + roff[0] + nxy * (uint32_t)gzm;
     const uint32_t off = boff<float>(in_xy && s - 1 >= z0, node);
-    const bool osolid = WALLS && is_solid(B, gyo, gzm);
+    const bool osolid = WALLS && is_solid(B, rgy[0], gzm);
     if constexpr (EXACT) {
       acc[0][0] = (float)acc64[0][0];
       acc[0][1] = (float)acc64[0][1];
@@ -2413,7 +2432,6 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
       for (int c = 0; c < 2; ++c) {
         acc64[0][c] = acc64[1][c];
         acc64[1][c] = acc64[2][c];
-        acc64[2][c] = 0.0;
       }
     }
 #pragma unroll
@@ -2423,7 +2441,6 @@ __global__ __launch_bounds__(TX *TY) void k_cpull(const BoxDev *__restrict__ box
     for (int m = 0; m < 11; ++m) {
       acc[0][m] = acc[1][m];
       acc[1][m] = acc[2][m];
-      acc[2][m] = 0.f;
     }
   }
 }

@@ -12,54 +12,84 @@
 
 namespace cglbm {
 
-// Launch geometries of the fused kernel: column extent in x and y, z chunk,
-// minimum waves per SIMD requested from the register allocator.  Every
-// variant performs the same arithmetic per node (results are bitwise equal);
-// cglbm_autotune picks the fastest for the boxes at hand.
+// Launch geometries of the fused kernel: nominal column extent in x and y
+// (their product is the block's threads; fit_tile shapes the column to each
+// box), longest z chunk, minimum waves per SIMD requested from the register
+// allocator.  Every variant performs the same arithmetic per node (results
+// are bitwise equal); cglbm_autotune picks the fastest for the boxes at hand.
 using FusedFn = void (*)(const BoxDev *, const TileEntry *, float *, void *, int64_t);
+struct FusedKernels {
+  int nt, r3, r2, r1;  // threads; points of the tile + 3, + 2 and + 1 its LDS arrays hold
+  FusedFn fn[7][2];    // time step: [storage][0: tiles away from solid layers, 1: near them]
+  FusedFn fx[2];       // field export (no population store): [near solid layers]
+  FusedFn fc[2];       // compact schedule: compact state out (FP32): [near solid layers]
+  FusedFn fcx[2];      // compact schedule, mass-exact storage (FP64 densities): [near solid layers]
+};
+#define CGLBM_FK_S(G, MW, S) {k_fused<G, MW, false, S, false>, k_fused<G, MW, true, S, false>}
+#define CGLBM_FK(G, MW)                                                                      \
+  {G::NT, G::R3, G::R2, G::R1,                                                                \
+   {CGLBM_FK_S(G, MW, StoreF32), CGLBM_FK_S(G, MW, StoreF16), CGLBM_FK_S(G, MW, StoreBF16),   \
+    CGLBM_FK_S(G, MW, StoreF32X), CGLBM_FK_S(G, MW, StoreF32P), CGLBM_FK_S(G, MW, StoreF16C), \
+    CGLBM_FK_S(G, MW, StoreBF16C)},                                                          \
+   {k_fused<G, MW, false, StoreF32, true>, k_fused<G, MW, true, StoreF32, true>},            \
+   {k_fused<G, MW, false, StoreF32, false, true>, k_fused<G, MW, true, StoreF32, false, true>}, \
+   {k_fused<G, MW, false, StoreF32X, false, true>, k_fused<G, MW, true, StoreF32X, false, true>}}
+// Blocks of 128 to 1024 threads.  The rings' room fits the nominal shapes
+// (32 x 4, 32 x 8, 64 x 4, 32 x 16 and 64 x 8, 64 x 16) and what LDS allows
+// beyond them at the same blocks per CU (two of FG512, four of FG256).
+using FG128 = FusedGeom<128, 384, 288, 208>;
+using FG256 = FusedGeom<256, 552, 440, 350>;
+using FG256W = FusedGeom<256, 704, 544, 400>;
+using FG512 = FusedGeom<512, 1024, 856, 684>;
+using FG1024 = FusedGeom<1024, 1540, 1360, 1188>;
+// the kernels of the geometries, in three units
+extern const FusedKernels kFusedPart0[3];
+extern const FusedKernels kFusedPart1[2];
+extern const FusedKernels kFusedPart2[2];
 struct FusedVariant {
   int tx, ty, zc, minw;
-  FusedFn fn[7][2];  // time step: [storage][0: tiles away from solid layers, 1: near them]
-  FusedFn fx[2];     // field export (no population store): [near solid layers]
-  FusedFn fc[2];     // compact schedule: compact state out (FP32): [near solid layers]
-  FusedFn fcx[2];    // compact schedule, mass-exact storage (FP64 densities): [near solid layers]
+  const FusedKernels *k;
 };
-#define CGLBM_FV_S(TX, TY, ZC, MW, S) \
-  {k_fused<TX, TY, ZC, MW, false, S, false>, k_fused<TX, TY, ZC, MW, true, S, false>}
-#define CGLBM_FV(TX, TY, ZC, MW)                                                              \
-  {TX, TY, ZC, MW,                                                                           \
-   {CGLBM_FV_S(TX, TY, ZC, MW, StoreF32), CGLBM_FV_S(TX, TY, ZC, MW, StoreF16),               \
-    CGLBM_FV_S(TX, TY, ZC, MW, StoreBF16), CGLBM_FV_S(TX, TY, ZC, MW, StoreF32X),             \
-    CGLBM_FV_S(TX, TY, ZC, MW, StoreF32P), CGLBM_FV_S(TX, TY, ZC, MW, StoreF16C),             \
-    CGLBM_FV_S(TX, TY, ZC, MW, StoreBF16C)},                                                 \
-   {k_fused<TX, TY, ZC, MW, false, StoreF32, true>, k_fused<TX, TY, ZC, MW, true, StoreF32, true>}, \
-   {k_fused<TX, TY, ZC, MW, false, StoreF32, false, true>,                                    \
-    k_fused<TX, TY, ZC, MW, true, StoreF32, false, true>},                                    \
-   {k_fused<TX, TY, ZC, MW, false, StoreF32X, false, true>,                                   \
-    k_fused<TX, TY, ZC, MW, true, StoreF32X, false, true>}}
-// the thirteen geometries, in three units
-extern const FusedVariant kFusedPart0[4];
-extern const FusedVariant kFusedPart1[4];
-extern const FusedVariant kFusedPart2[5];
 constexpr int kNumFusedVariants = 13;
 inline const FusedVariant &fused_variant(int v) {
-  return v < 4 ? kFusedPart0[v] : (v < 8 ? kFusedPart1[v - 4] : kFusedPart2[v - 8]);
+  static const FusedVariant t[kNumFusedVariants] = {
+      {32, 8, 32, 4, &kFusedPart0[0]},  {32, 8, 64, 4, &kFusedPart0[0]},
+      {32, 8, 16, 4, &kFusedPart0[0]},  {32, 8, 32, 1, &kFusedPart0[1]},
+      {32, 16, 32, 4, &kFusedPart1[0]}, {32, 16, 64, 4, &kFusedPart1[0]},
+      {64, 4, 32, 4, &kFusedPart2[0]},  {32, 4, 32, 4, &kFusedPart2[1]},
+      {32, 8, 32, 5, &kFusedPart0[2]},  {64, 8, 64, 4, &kFusedPart1[0]},
+      {64, 8, 32, 4, &kFusedPart1[0]},  {64, 16, 64, 4, &kFusedPart1[1]},
+      {64, 16, 32, 4, &kFusedPart1[1]}};
+  return t[v];
 }
 
-// The compact schedule's pull (column tile and z chunk, chosen by the
-// autotuner; equal results).
+// The compact schedule's pull (nominal column and longest z chunk, chosen by
+// the autotuner; equal results).
 using CPullFn = void (*)(const BoxDev *, const TileEntry *, const float *, float *, int64_t,
                          const void *, void *, int64_t);
-struct CPullVariant {
-  int tx, ty, zc;
+struct CPullKernels {
+  int nt, r1;  // threads, points of the tile + 1 its LDS array holds
   // [general equilibrium family][0 tiles away from solid layers, 1 tiles near
   // them with FP32 planes, 2 tiles near them with FP32 pairs]
   CPullFn fn[2][3];
   CPullFn fx[2];  // mass-exact storage, Model D with Q: [near solid layers]
 };
-extern const CPullVariant kCPullTable[5];
+using CG256 = CPullGeom<256, 400>;
+using CG512 = CPullGeom<512, 684>;
+extern const CPullKernels kCPull256, kCPull512;
+struct CPullVariant {
+  int tx, ty, zc;
+  const CPullKernels *k;
+};
 constexpr int kNumCPullVariants = 5;
-inline const CPullVariant &cpull_variant(int v) { return kCPullTable[v]; }
+inline const CPullVariant &cpull_variant(int v) {
+  static const CPullVariant t[kNumCPullVariants] = {{64, 8, 64, &kCPull512},
+                                                    {64, 8, 32, &kCPull512},
+                                                    {32, 8, 32, &kCPull256},
+                                                    {64, 4, 32, &kCPull256},
+                                                    {32, 8, 64, &kCPull256}};
+  return t[v];
+}
 
 // Tile shapes of the two-dimensional (D2Q9) step kernel, 256 threads each;
 // bitwise equal results, picked by cglbm_autotune.  Kernels per storage slot:

@@ -211,18 +211,19 @@ __device__ __forceinline__ void buf_st(double v, __amdgpu_buffer_rsrc_t r, uint3
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0,
                                         kNonTemporal);
 }
-// The same, for values read once: the streaming hint keeps them from
-// displacing the halo lines that neighbouring columns share in L2.
-__device__ __forceinline__ float ldpl_nt(const float *base, int64_t plane, int p, uint32_t node) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                       plane_rsrc(base, plane * 4, p), (int)(node * 4u), 0, kNonTemporal));
-}
 __device__ __forceinline__ double buf_ld_f64_nt(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, kNonTemporal));
 }
-// Float plane p of an aux-like array at node.
+// Float plane p of an aux-like array at node, through a plane pointer (two
+// scalar registers a plane where a descriptor takes four; every lane's node
+// is a valid one).
 __device__ __forceinline__ float ldpl(const float *base, int64_t plane, int p, uint32_t node) {
-  return buf_ld_f32(plane_rsrc(base, plane * 4, p), node * 4u);
+  return at(base + (int64_t)p * plane, node);
+}
+// The same, for values read once: the streaming hint keeps them from
+// displacing the halo lines that neighbouring columns share in L2.
+__device__ __forceinline__ float ldpl_nt(const float *base, int64_t plane, int p, uint32_t node) {
+  return __builtin_nontemporal_load(&at(base + (int64_t)p * plane, node));
 }
 // Byte offset of node in a plane of T, or kDrop for a lane that must not
 // access it.
@@ -1553,7 +1554,6 @@ struct FusedGeom {
   // points held of phi (tile + 3), n (tile + 2) and q (tile + 1)
   static constexpr int R3 = R3_, R2 = R2_, R1 = R1_;
   static constexpr int A_PER = (R3 + NT - 1) / NT, B_PER = (R2 + NT - 1) / NT;
-  static constexpr int kMaxRows = 64;  // of a tile with its halo of 3
 };
 
 // COMPACT: store each node's compact post-collision state (17 float planes
@@ -1567,7 +1567,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   __shared__ float s_phi[3][G::R3];
   __shared__ float s_n[3][4][G::R2];
   __shared__ float s_q[3][3][G::R1];
-  __shared__ uint8_t s_sy[G::kMaxRows];
+  __shared__ uint32_t s_pure[4];  // per wavefront a byte: its phi all +1 (bit 0), all -1 (bit 1)
 
   const int tid = threadIdx.x;
   const uint32_t lb = xcd_block();
@@ -1588,13 +1588,17 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
   const bool zwalls = WALLS && (B.walls & 2u) != 0;
 
-  if (WALLS)
-    for (int i = tid; i < TH + 6; i += NT) {
-      const int gy = wrap_any(y0 + i - 3, ny);
-      s_sy[i] = (B.walls & 1u) && (gy == 0 || gy == ny - 1);
-    }
-  // solid flag of an R3 row (always false without walls)
-  auto sy = [&](int r) -> bool { return WALLS ? (bool)s_sy[r] : false; };
+  // Rows in solid layers (y walls), as bits of one register: for each normal
+  // point of this thread the rows below, at and above it (from bit 0), the
+  // same for its halo-1 points (from bit 9), and the row of each of its phi
+  // points (from bit 15).
+  static_assert(G::A_PER <= 3 && G::B_PER <= 3, "row bits");
+  uint32_t rows = 0;
+  auto solid_row = [&](int y) -> uint32_t {
+    const int gy = wrap_any(y, ny);
+    return (B.walls & 1u) && (gy == 0 || gy == ny - 1) ? 1u : 0u;
+  };
+  auto row_bit = [&](int i) -> bool { return WALLS ? (bool)((rows >> i) & 1u) : false; };
   // xy offsets of this thread's phase-field points (fixed over the march)
   int a_off[G::A_PER];
 #pragma unroll
@@ -1604,23 +1608,27 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     if (i < n3) {
       const int ly = (int)fdiv((uint32_t)i, B.fs.d6), lx = i - ly * R3X;
       a_off[k] = wrap_any(x0 + lx - 3, nx) + nx * wrap_any(y0 + ly - 3, ny);
+      if (WALLS) rows |= solid_row(y0 + ly - 3) << (15 + k);
     }
   }
-  // and of its normals: the stencil's centre in the phi ring and its row
-  int b_c3[G::B_PER], b_ly[G::B_PER];
+  if (tid < 4) s_pure[tid] = 0xFFFFFFFFu;
+  // and of its normals: the stencil's centre in the phi ring
+  int b_c3[G::B_PER];
 #pragma unroll
   for (int k = 0; k < G::B_PER; ++k) {
     const int i = min(tid + k * NT, n2 - 1);
     const int ly = (int)fdiv((uint32_t)i, B.fs.d4), lx = i - ly * R2X;
-    b_ly[k] = ly;
     b_c3[k] = (lx + 1) + R3X * (ly + 1);
+    if (WALLS)
+      for (int d = 0; d < 3; ++d) rows |= solid_row(y0 + ly - 3 + d) << (3 * k + d);
   }
   // halo-1 points of this thread: its tile point, then one of the ring (top
   // and bottom rows, then the two side columns)
   constexpr int C_PER = 2;
   const bool c_has[C_PER] = {tid < own, tid < ring};
   uint32_t c_off[C_PER];
-  int c_c2[C_PER], c_ri[C_PER], c_ly[C_PER];
+  int gxo = 0, gyo = 0;  // the tile point
+  int c_c2[C_PER], c_ri[C_PER];
 #pragma unroll
   for (int kk = 0; kk < C_PER; ++kk) {
     int lx = 1, ly = 1;
@@ -1638,18 +1646,19 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       lx = (h2 & 1) * (TW + 1);
       ly = (h2 >> 1) + 1;
     }
-    c_ly[kk] = ly;
+    if (WALLS)
+      for (int d = 0; d < 3; ++d) rows |= solid_row(y0 + ly - 2 + d) << (9 + 3 * kk + d);
+    if (kk == 0) {
+      gxo = x0 + lx - 1;
+      gyo = y0 + ly - 1;
+    }
     c_c2[kk] = (lx + 1) + R2X * (ly + 1);
     c_ri[kk] = lx + R1X * ly;
     c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + (uint32_t)nx * (uint32_t)wrap_any(y0 + ly - 1, ny);
   }
-  // tile point of this thread
-  const int oy = c_ly[0] - 1;
-  const int gxo = x0 + c_ri[0] - R1X * c_ly[0] - 1, gyo = y0 + oy;
   const bool in_xy = c_has[0] && gxo < nx && gyo < ny;
   // (lanes without a node of the box load at wrapped, valid addresses and
   // store nowhere)
-  const bool solid_y_o = WALLS && (B.walls & 1u) && (gyo == 0 || gyo == ny - 1);
   // interface values of the tile point, one slab behind the q ring
   float h_nx = 0.f, h_ny = 0.f, h_nz = 0.f, h_Fx = 0.f, h_Fy = 0.f, h_Fz = 0.f, h_k = 0.f;
   auto slab_solid = [&](int s) {
@@ -1673,13 +1682,16 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)wrap_any(sl, nz);
 #pragma unroll
     for (int k = 0; k < G::A_PER; ++k) {
-      if (k > 0 && wave0 + k * NT >= n3) {
-        a_rr[k] = a_rb[k] = 0.f;
-        continue;
+      // (assigned once, after the branch: assignments in both branches had
+      // been merged into stores through a selected address, in scratch)
+      float rr = 0.f, rb = 0.f;
+      if (k == 0 || wave0 + k * NT < n3) {
+        const uint32_t node = zoff + (uint32_t)a_off[k];
+        rr = ldpl(aux, pl, A_RR, node);
+        rb = ldpl(aux, pl, A_RB, node);
       }
-      const uint32_t node = zoff + (uint32_t)a_off[k];
-      a_rr[k] = ldpl(aux, pl, A_RR, node);
-      a_rb[k] = ldpl(aux, pl, A_RB, node);
+      a_rr[k] = rr;
+      a_rb[k] = rb;
     }
   };
   auto load_c = [&](int sl, int64_t pl) {
@@ -1755,23 +1767,51 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   }
   __syncthreads();
 
+  // Where phi is +1 (or -1) on all points of three slabs, the gradient of the
+  // middle one is exactly zero, and so are its normals, its curvature force
+  // and the stencils that form them: away from the interface, most of a box,
+  // stages B and C skip them (and the barrier between them).  Compact states,
+  // 256^3 droplet: 476 -> 454 us, 24 boxes of 24 to 128 nodes an edge 594 ->
+  // 566 us; what is left is bound by memory (4.4 TB/s).  pure: of the
+  // last three slabs, two bits each (all +1, all -1), newest lowest; n_zero:
+  // bit of each slot of the n ring that holds zeros throughout.
+  uint32_t pure = 0, n_zero = 0;
   for (int s = z0 - 3; s < z1 + 3; ++s) {
     const int64_t plane = opaque_i64(plane_arg);
+    // (opaque: the tests of its bits, one lane mask each, are not hoisted
+    // into scalar registers)
+    if (WALLS) asm volatile("" : "+v"(rows));
     if (!kPipeD) load_d(s - 3, plane);
     // ---- A: phase field of slab s (Eq. 14) ----
     {
       float *ph = s_phi[(s + 3) % 3];
+      bool red = true, blue = true;
 #pragma unroll
       for (int k = 0; k < G::A_PER; ++k) {
         const int i = tid + k * NT;
         if (i < n3) {
           const float rr = a_rr[k] * B.ir0r;
           const float rb = a_rb[k] * B.ir0b;
-          ph[i] = phase_field(rr, rb);
+          const float v = phase_field(rr, rb);
+          ph[i] = v;
+          const bool any = row_bit(15 + k);
+          red = red && (any || v == 1.0f);
+          blue = blue && (any || v == -1.0f);
         }
       }
+      const uint32_t bits = (__all(red) ? 1u : 0u) | (__all(blue) ? 2u : 0u);
+      if ((tid & 63) == 0)
+        reinterpret_cast<uint8_t *>(s_pure)[tid >> 6] = slab_solid(s) ? 3 : (uint8_t)bits;
     }
     __syncthreads();
+    {
+      uint32_t w = s_pure[0];
+#pragma unroll
+      for (int i = 1; i < (NT + 255) / 256; ++i) w &= s_pure[i];
+      w &= w >> 16;
+      w &= w >> 8;
+      pure = (pure << 2) | ((uint32_t)__builtin_amdgcn_readfirstlane((int)w) & 3u);
+    }
     // ---- B: grad phi and n of slab s-1 (Eqs. 17, 20) ----
     if (s - 1 >= z0 - 2) {
       const int sb = s - 1;
@@ -1779,87 +1819,38 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       const float *pm = s_phi[(sb - 1 + 3) % 3];
       const float *pc = s_phi[(sb + 3) % 3];
       const float *pp = s_phi[(sb + 1 + 3) % 3];
-      float(*nn)[G::R2] = s_n[(sb + 3) % 3];
+      const uint32_t slot = (uint32_t)(sb + 3) % 3u;
+      float(*nn)[G::R2] = s_n[slot];
+      const bool zero = (pure & (pure >> 2) & (pure >> 4) & 3u) != 0u;
+      if (zero && !((n_zero >> slot) & 1u)) {
 #pragma unroll
-      for (int k = 0; k < G::B_PER; ++k) {
-        const int i = tid + k * NT;
-        if (i >= n2) break;
-        const int c3 = b_c3[k], ly = b_ly[k];
-        float nxv = 0.f, nyv = 0.f, nzv = 0.f, mag = 0.f;
-        if (!(sy(ly + 1) | sz_c)) {
-          const float vc = pc[c3];
-          float v[3][3][3];
-#pragma unroll
-          for (int dz = -1; dz <= 1; ++dz) {
-            const float *pl = dz < 0 ? pm : (dz > 0 ? pp : pc);
-            const bool szd = dz < 0 ? sz_m : (dz > 0 ? sz_p : sz_c);
-#pragma unroll
-            for (int dy = -1; dy <= 1; ++dy) {
-              const bool sd = szd | sy(ly + 1 + dy);
-#pragma unroll
-              for (int dx = -1; dx <= 1; ++dx)
-                v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c3 + dx + R3X * dy]);
-            }
-          }
-          float gx = 0.f, gy = 0.f, gz = 0.f;
-#pragma unroll
-          for (int a2 = 0; a2 < 3; ++a2)
-#pragma unroll
-            for (int b2 = 0; b2 < 3; ++b2) {
-              const float w = 0.5f * w1d(a2 - 1) * w1d(b2 - 1);
-              gx = fmaf(w, v[b2][a2][2] - v[b2][a2][0], gx);
-              gy = fmaf(w, v[b2][2][a2] - v[b2][0][a2], gy);
-              gz = fmaf(w, v[2][b2][a2] - v[0][b2][a2], gz);
-            }
-          const float g2 = gx * gx + gy * gy + gz * gz;
-          if (g2 > 1e-24f) {  // |grad phi| > 1e-12
-            const float inv = rsq(g2);
-            mag = g2 * inv;
-            nxv = gx * inv;
-            nyv = gy * inv;
-            nzv = gz * inv;
-          }
+        for (int k = 0; k < G::B_PER; ++k) {
+          const int i = tid + k * NT;
+          if (i < n2) nn[0][i] = nn[1][i] = nn[2][i] = nn[3][i] = 0.f;
         }
-        nn[0][i] = nxv;
-        nn[1][i] = nyv;
-        nn[2][i] = nzv;
-        nn[3][i] = mag;
+        __syncthreads();
       }
-    }
-    __syncthreads();
-    // ---- C: grad n, kappa, F, u, q of slab s-2 (Eqs. 11, 15, 16, 65) ----
-    float f_nx = 0.f, f_ny = 0.f, f_nz = 0.f, f_Fx = 0.f, f_Fy = 0.f, f_Fz = 0.f, f_k = 0.f;
-    if (s - 2 >= z0 - 1) {
-      const int sc = s - 2;
-      const bool sz_m = slab_solid(sc - 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc + 1);
-      float(*nm)[G::R2] = s_n[(sc - 1 + 3) % 3];
-      float(*nc)[G::R2] = s_n[(sc + 3) % 3];
-      float(*np)[G::R2] = s_n[(sc + 1 + 3) % 3];
-      float(*qq)[G::R1] = s_q[(sc + 3) % 3];
-      // first pass: the tile points in thread order, then the halo ring
+      n_zero = zero ? n_zero | (1u << slot) : n_zero & ~(1u << slot);
+      if (!zero) {
 #pragma unroll
-      for (int kk = 0; kk < C_PER; ++kk) {
-        if (!c_has[kk]) continue;
-        const int ly = c_ly[kk], c2 = c_c2[kk], ri = c_ri[kk];
-        float qx = 0.f, qy = 0.f, qz = 0.f;
-        float kap = 0.f, Fx = 0.f, Fy = 0.f, Fz = 0.f;
-        const float nxv = nc[0][c2], nyv = nc[1][c2], nzv = nc[2][c2], mag = nc[3][c2];
-        if (!(sy(ly + 2) | sz_c)) {
-          float d[3][3];  // d[a][b] = d n_a / d x_b
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            const float vc = nc[a][c2];
+        for (int k = 0; k < G::B_PER; ++k) {
+          const int i = tid + k * NT;
+          if (i >= n2) continue;
+          const int c3 = b_c3[k];
+          float nxv = 0.f, nyv = 0.f, nzv = 0.f, mag = 0.f;
+          if (!(row_bit(3 * k + 1) | sz_c)) {
+            const float vc = pc[c3];
             float v[3][3][3];
 #pragma unroll
             for (int dz = -1; dz <= 1; ++dz) {
-              const float *pl = dz < 0 ? nm[a] : (dz > 0 ? np[a] : nc[a]);
+              const float *pl = dz < 0 ? pm : (dz > 0 ? pp : pc);
               const bool szd = dz < 0 ? sz_m : (dz > 0 ? sz_p : sz_c);
 #pragma unroll
               for (int dy = -1; dy <= 1; ++dy) {
-                const bool sd = szd | sy(ly + 2 + dy);
+                const bool sd = szd | row_bit(3 * k + 1 + dy);
 #pragma unroll
                 for (int dx = -1; dx <= 1; ++dx)
-                  v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c2 + dx + R2X * dy]);
+                  v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c3 + dx + R3X * dy]);
               }
             }
             float gx = 0.f, gy = 0.f, gz = 0.f;
@@ -1872,15 +1863,92 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
                 gy = fmaf(w, v[b2][2][a2] - v[b2][0][a2], gy);
                 gz = fmaf(w, v[2][b2][a2] - v[0][b2][a2], gz);
               }
-            d[a][0] = gx;
-            d[a][1] = gy;
-            d[a][2] = gz;
+            const float g2 = gx * gx + gy * gy + gz * gz;
+            if (g2 > 1e-24f) {  // |grad phi| > 1e-12
+              const float inv = rsq(g2);
+              mag = g2 * inv;
+              nxv = gx * inv;
+              nyv = gy * inv;
+              nzv = gz * inv;
+            }
           }
-          const float div = d[0][0] + d[1][1] + d[2][2];
-          const float proj = nxv * (nxv * d[0][0] + nyv * d[0][1] + nzv * d[0][2]) +
-                             nyv * (nxv * d[1][0] + nyv * d[1][1] + nzv * d[1][2]) +
-                             nzv * (nxv * d[2][0] + nyv * d[2][1] + nzv * d[2][2]);
-          kap = proj - div;
+          nn[0][i] = nxv;
+          nn[1][i] = nyv;
+          nn[2][i] = nzv;
+          nn[3][i] = mag;
+        }
+        __syncthreads();
+      }
+    }
+    // ---- C: grad n, kappa, F, u, q of slab s-2 (Eqs. 11, 15, 16, 65) ----
+    float f_nx = 0.f, f_ny = 0.f, f_nz = 0.f, f_Fx = 0.f, f_Fy = 0.f, f_Fz = 0.f, f_k = 0.f;
+    if (s - 2 >= z0 - 1) {
+      const int sc = s - 2;
+      const bool sz_m = slab_solid(sc - 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc + 1);
+      // (the exported curvature is wanted next to the interface too)
+      const bool flat = EXPORT ? n_zero == 7u : ((n_zero >> ((uint32_t)(sc + 3) % 3u)) & 1u) != 0u;
+      float(*nm)[G::R2] = s_n[(sc - 1 + 3) % 3];
+      float(*nc)[G::R2] = s_n[(sc + 3) % 3];
+      float(*np)[G::R2] = s_n[(sc + 1 + 3) % 3];
+      float(*qq)[G::R1] = s_q[(sc + 3) % 3];
+      // first pass: the tile points in thread order, then the halo ring
+#pragma unroll
+      for (int kk = 0; kk < C_PER; ++kk) {
+        if (!c_has[kk]) continue;
+        const int c2 = c_c2[kk], ri = c_ri[kk];
+        float qx = 0.f, qy = 0.f, qz = 0.f;
+        float kap = 0.f, Fx = 0.f, Fy = 0.f, Fz = 0.f;
+        float nxv = 0.f, nyv = 0.f, nzv = 0.f, mag = 0.f;
+        if (!flat) {
+          nxv = nc[0][c2];
+          nyv = nc[1][c2];
+          nzv = nc[2][c2];
+          mag = nc[3][c2];
+        }
+        const bool fluid = !(row_bit(10 + 3 * kk) | sz_c);
+        // a wavefront whose nodes all have |grad phi| = 0 has no force from
+        // the curvature, whatever it is
+        if (!flat && (EXPORT || __any(mag != 0.f))) {
+          if (fluid) {
+            float d[3][3];  // d[a][b] = d n_a / d x_b
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              const float vc = nc[a][c2];
+              float v[3][3][3];
+#pragma unroll
+              for (int dz = -1; dz <= 1; ++dz) {
+                const float *pl = dz < 0 ? nm[a] : (dz > 0 ? np[a] : nc[a]);
+                const bool szd = dz < 0 ? sz_m : (dz > 0 ? sz_p : sz_c);
+#pragma unroll
+                for (int dy = -1; dy <= 1; ++dy) {
+                  const bool sd = szd | row_bit(10 + 3 * kk + dy);
+#pragma unroll
+                  for (int dx = -1; dx <= 1; ++dx)
+                    v[dz + 1][dy + 1][dx + 1] = wall_rule(sd, vc, pl[c2 + dx + R2X * dy]);
+                }
+              }
+              float gx = 0.f, gy = 0.f, gz = 0.f;
+#pragma unroll
+              for (int a2 = 0; a2 < 3; ++a2)
+#pragma unroll
+                for (int b2 = 0; b2 < 3; ++b2) {
+                  const float w = 0.5f * w1d(a2 - 1) * w1d(b2 - 1);
+                  gx = fmaf(w, v[b2][a2][2] - v[b2][a2][0], gx);
+                  gy = fmaf(w, v[b2][2][a2] - v[b2][0][a2], gy);
+                  gz = fmaf(w, v[2][b2][a2] - v[0][b2][a2], gz);
+                }
+              d[a][0] = gx;
+              d[a][1] = gy;
+              d[a][2] = gz;
+            }
+            const float div = d[0][0] + d[1][1] + d[2][2];
+            const float proj = nxv * (nxv * d[0][0] + nyv * d[0][1] + nzv * d[0][2]) +
+                               nyv * (nxv * d[1][0] + nyv * d[1][1] + nzv * d[1][2]) +
+                               nzv * (nxv * d[2][0] + nyv * d[2][1] + nzv * d[2][2]);
+            kap = proj - div;
+          }
+        }
+        if (fluid) {
           const float rr = pc_[kk][0];
           const float rb = pc_[kk][1];
           const float rho = rr + rb;
@@ -1919,7 +1987,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     {
       const int sd = s - 3;
       const bool sz_m = slab_solid(sd - 1), sz_p = slab_solid(sd + 1);
-      const bool fluid = in_xy && !(solid_y_o || slab_solid(sd));
+      const bool fluid = in_xy && !(row_bit(10) || slab_solid(sd));
       float(*qm)[G::R1] = s_q[(sd + 8) % 3];
       float(*qc)[G::R1] = s_q[(sd + 9) % 3];
       float(*qp)[G::R1] = s_q[(sd + 10) % 3];
@@ -1933,7 +2001,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
           const float w = 0.5f * w1d(a2) * w1d(b2);
           {  // x: a2 = dy, b2 = dz
             const float *pl = b2 < 0 ? qm[0] : (b2 > 0 ? qp[0] : qc[0]);
-            const bool sdd = (b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false)) | sy(oy + 3 + a2);
+            const bool sdd = (b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false)) | row_bit(10 + a2);
             const float vc = qc[0][c1];
             const float vp = wall_rule(sdd, vc, pl[c1 + 1 + R1X * a2]);
             const float vm = wall_rule(sdd, vc, pl[c1 - 1 + R1X * a2]);
@@ -1943,12 +2011,12 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
             const float *pl = b2 < 0 ? qm[1] : (b2 > 0 ? qp[1] : qc[1]);
             const bool szd = b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false);
             const float vc = qc[1][c1];
-            const float vp = wall_rule(szd | sy(oy + 4), vc, pl[c1 + a2 + R1X]);
-            const float vm = wall_rule(szd | sy(oy + 2), vc, pl[c1 + a2 - R1X]);
+            const float vp = wall_rule(szd | row_bit(11), vc, pl[c1 + a2 + R1X]);
+            const float vm = wall_rule(szd | row_bit(9), vc, pl[c1 + a2 - R1X]);
             Qy = fmaf(w, vp - vm, Qy);
           }
           {  // z: a2 = dx, b2 = dy
-            const bool syd = sy(oy + 3 + b2);
+            const bool syd = row_bit(10 + b2);
             const float vc = qc[2][c1];
             const float vp = wall_rule(sz_p | syd, vc, qp[2][c1 + a2 + R1X * b2]);
             const float vm = wall_rule(sz_m | syd, vc, qm[2][c1 + a2 + R1X * b2]);
@@ -2164,7 +2232,7 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
       }
       float c[kCompact];
 #pragma unroll
-      for (int m = 0; m < kCompact; ++m) c[m] = at(PL(cst, m), zoff + roff[k]);
+      for (int m = 0; m < kCompact; ++m) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
       CompactPost o;
       compact_post<GENERAL>(B, c, o);
       float g[3][3][3];

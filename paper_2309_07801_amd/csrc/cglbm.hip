@@ -986,6 +986,36 @@ int capture_compact_pair(cglbm_handle *h) {
   return CGLBM_OK;
 }
 
+// Mean milliseconds of launch() over `reps` runs of before() and launch() on
+// stream s, after one of each untimed; only launch() is timed.
+template <class B, class F>
+int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, double &ms_out) {
+  const int n = std::min(reps, 64);
+  std::vector<hipEvent_t> ev(2 * (size_t)n, nullptr);
+  int rc = CGLBM_OK;
+  for (hipEvent_t &e : ev)
+    if (!rc && hipEventCreate(&e) != hipSuccess) rc = fail(CGLBM_EHIP, "autotune: event create failed");
+  for (int r = -1; r < n && !rc; ++r) {
+    rc = before();
+    if (!rc && r >= 0) (void)hipEventRecord(ev[2 * (size_t)r], s);
+    if (!rc) rc = launch();
+    if (!rc && r >= 0) (void)hipEventRecord(ev[2 * (size_t)r + 1], s);
+  }
+  if (!rc) rc = check_launch();
+  if (!rc && hipEventSynchronize(ev.back()) != hipSuccess)
+    rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
+  double sum = 0.0;
+  for (int r = 0; r < n && !rc; ++r) {
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, ev[2 * (size_t)r], ev[2 * (size_t)r + 1]);
+    sum += (double)ms;
+  }
+  for (hipEvent_t e : ev)
+    if (e) (void)hipEventDestroy(e);
+  ms_out = sum / n;
+  return rc;
+}
+
 // Mean milliseconds per launch(k) over `reps` replays of a graph that
 // captures launch(stream, 0) and launch(stream, 1) on the capture stream.
 template <class F>
@@ -1621,10 +1651,15 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     const int rc = flush_compact(h, s);
     if (rc) return rc;
   }
-  // the fused kernel is idempotent for a fixed pull: time every variant on
-  // the same inputs; the stored state is unchanged afterwards (in place, the
-  // variants all write the next state into the one buffer: the call then
-  // advances the state by exactly one step)
+  // Each candidate is timed as a step runs it: after the kernel before it in
+  // the step, which leaves its inputs where a step finds them.  (Launched back
+  // to back on one set of inputs, the candidates found them in the memory-side
+  // cache, and a geometry won that was 12 % slower in a step: 128x112x96 with
+  // 16-bit storage.)  The pull of the population schedules reads the stored
+  // state, which nothing here advances; in place, where the candidates
+  // themselves write the next state into the one buffer, they run on the one
+  // pull, and the call advances the state by exactly one step.
+  auto pull = [&] { return h->inplace ? CGLBM_OK : launch_pull(h, s, 1); };
   int rc = launch_pull(h, s, 1);
   if (rc || (rc = check_launch())) return rc;
   hipEvent_t e0, e1;
@@ -1633,95 +1668,62 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   int best = h->variant;
   double best_ms = 1e300;
   for (int v = 0; v < kNumFused; ++v) {
-    if ((rc = select_variant(h, v, s))) break;
-    if ((rc = launch_fused(h, s, 0))) break;
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < reps && !rc; ++r) rc = launch_fused(h, s, 0);
-    (void)hipEventRecord(e1, s);
-    if (rc || (rc = check_launch())) break;
-    if (hipEventSynchronize(e1) != hipSuccess) {
-      rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
+    double ms = 0.0;
+    if ((rc = select_variant(h, v, s)) ||
+        (rc = time_in_step(s, reps, pull, [&] { return launch_fused(h, s, 0); }, ms)))
       break;
-    }
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    const double avg = (double)ms / reps;
-    if (ms_per_variant) ms_per_variant[v] = avg;
-    if (avg < best_ms) {
-      best_ms = avg;
+    if (ms_per_variant) ms_per_variant[v] = ms;
+    if (ms < best_ms) {
+      best_ms = ms;
       best = v;
     }
   }
-  // the compact schedule's fused kernel on the same inputs (it writes
-  // compact states into the other buffer only): its own best geometry
+  // the three-kernel schedule after the same pull
+  double three_ms = 1e300;
+  if (!rc && !(rc = select_variant(h, best, s)))
+    rc = time_in_step(s, reps, pull,
+                      [&] {
+                        const int r = launch_iface(h, s, 0);
+                        return r ? r : launch_collide(h, s);
+                      },
+                      three_ms);
+  if (!rc && ms_per_variant) ms_per_variant[kNumFused] = three_ms;
+  // the compact schedule's fused kernel (its own best geometry), then its
+  // pull, in steps of that schedule: they advance only the compact state in
+  // the other buffer, which the first collision writes from the pull above
   int cfbest = best;
-  if (!rc && compact_ok(h) && !h->L.general) {
+  if (!rc && compact_ok(h)) {
+    if (!(rc = launch_pull(h, s, 1))) rc = launch_compact_collide(h, s);
     double cf_ms = 1e300;
-    for (int v = 0; v < kNumFused && !rc; ++v) {
-      if ((rc = select_variant(h, v, s)) || (rc = launch_fused_compact(h, s))) break;
-      (void)hipEventRecord(e0, s);
-      for (int r = 0; r < reps && !rc; ++r) rc = launch_fused_compact(h, s);
-      (void)hipEventRecord(e1, s);
-      if (!rc) rc = check_launch();
-      if (!rc && hipEventSynchronize(e1) != hipSuccess)
-        rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
-      if (rc) break;
-      float ms = 0.f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      if ((double)ms / reps < cf_ms) {
-        cf_ms = (double)ms / reps;
+    for (int v = 0; v < kNumFused && !rc && !h->L.general; ++v) {
+      double ms = 0.0;
+      if ((rc = select_variant(h, v, s)) ||
+          (rc = time_in_step(s, reps, [&] { return launch_cpull(h, s); },
+                             [&] { return launch_fused_compact(h, s); }, ms)))
+        break;
+      if (ms < cf_ms) {
+        cf_ms = ms;
         cfbest = v;
       }
     }
-  }
-  h->fvar_pop = best;
-  h->fvar_compact = cfbest;
-  // the three-kernel schedule on the same inputs (its interface and collide
-  // kernels are idempotent for a fixed pull as well)
-  double three_ms = 1e300;
-  if (!rc) rc = select_variant(h, best, s);
-  if (!rc && !(rc = launch_iface(h, s, 0)) && !(rc = launch_collide(h, s))) {
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < reps && !rc; ++r) {
-      rc = launch_iface(h, s, 0);
-      if (!rc) rc = launch_collide(h, s);
-    }
-    (void)hipEventRecord(e1, s);
-    if (!rc) rc = check_launch();
-    if (!rc && hipEventSynchronize(e1) != hipSuccess)
-      rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
-    if (!rc) {
-      float ms = 0.f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      three_ms = (double)ms / reps;
-      if (ms_per_variant) ms_per_variant[kNumFused] = three_ms;
-    }
-  }
-  // the compact schedule's pull geometry: the compact state the fused kernel
-  // writes into the other buffer from the same pull, then each k_cpull
-  // variant on it (both write only that buffer and aux)
-  if (!rc && compact_ok(h) && !(rc = select_variant(h, cfbest, s)) &&
-      !(rc = launch_compact_collide(h, s))) {
+    if (!rc) rc = select_variant(h, cfbest, s);
     int cbest = h->cvariant;
     double cbest_ms = 1e300;
     for (int v = 0; v < kNumCPull && !rc; ++v) {
-      if ((rc = select_cvariant(h, v, s)) || (rc = launch_cpull(h, s))) break;
-      (void)hipEventRecord(e0, s);
-      for (int r = 0; r < reps && !rc; ++r) rc = launch_cpull(h, s);
-      (void)hipEventRecord(e1, s);
-      if (!rc) rc = check_launch();
-      if (!rc && hipEventSynchronize(e1) != hipSuccess)
-        rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
-      if (rc) break;
-      float ms = 0.f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      if ((double)ms / reps < cbest_ms) {
-        cbest_ms = (double)ms / reps;
+      double ms = 0.0;
+      if ((rc = select_cvariant(h, v, s)) ||
+          (rc = time_in_step(s, reps, [&] { return launch_compact_collide(h, s); },
+                             [&] { return launch_cpull(h, s); }, ms)))
+        break;
+      if (ms < cbest_ms) {
+        cbest_ms = ms;
         cbest = v;
       }
     }
     if (!rc) rc = select_cvariant(h, cbest, s);
   }
+  h->fvar_pop = best;
+  h->fvar_compact = cfbest;
   // boxes with walls: the wall mode of each schedule with its chosen
   // geometries, timed as the steps run (replays of a captured graph of two
   // launches): the fused kernel alone for the population schedule (its pull

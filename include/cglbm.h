@@ -323,9 +323,8 @@ int cglbm_load_state(cglbm_handle *h, const void *src, void *stream);
  *     otherwise (the moment sums run in another order).  Layouts: D3Q27,
  *     two buffers, unit higher rates, and either CGLBM_FP32 or
  *     CGLBM_FP32_PAIRS storage with any equilibrium family and Q switch
- *     (Model D with Q runs the fused kernel; the others the interface and
- *     collide kernels, writing compact states; one step per call then
- *     equals schedule 1 bit for bit), or CGLBM_FP32_EXACT storage with
+ *     (the fused kernel serves them all; with another family or without Q
+ *     one step per call equals schedule 1 bit for bit), or CGLBM_FP32_EXACT storage with
  *     Model D and Q (the compact state then carries the FP64 colour
  *     densities as well, 84 bytes per node, and per-colour mass stays
  *     exact to FP64 rounding), or one of the 16-bit storages with Model D

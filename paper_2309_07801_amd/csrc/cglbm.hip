@@ -62,7 +62,7 @@ int fail(int code, const char *fmt, ...) {
 
 constexpr int kTX = 8, kTY = 8, kTZ = 8;   // interface tile (three-kernel schedule)
 
-using EmitFn = void (*)(const BoxDev *, const int32_t *, const float *, void *, int64_t);
+using EmitFn = void (*)(const BoxDev *, const int32_t *, const float *, void *, int64_t, int64_t);
 constexpr int kNumFused = kNumFusedVariants;
 constexpr int kNumCPull = kNumCPullVariants;
 constexpr int kNumV2 = kNumVariants2;
@@ -93,7 +93,7 @@ int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
 // Kernels by storage format (index = cglbm_storage).
 using PullFn = void (*)(const BoxDev *, const int32_t *, void *, void *, float *, int64_t, int,
-                        void *, int64_t);
+                        void *, int64_t, int64_t);
 using WallCopyFn = void (*)(const BoxDev *, const int32_t *, const void *, void *, int64_t,
                             int64_t);
 using CollideFn = void (*)(const BoxDev *, const int32_t *, float *, const void *, void *,
@@ -141,8 +141,6 @@ const WallCopyFn kWallEncode[7] = {nullptr,
                                    nullptr,
                                    k_wall_encode<StoreF16C>,
                                    k_wall_encode<StoreBF16C>};
-// the three-kernel schedule's collision writing compact states
-const CollideFn kCollideCompact = k_collide<StoreF32, true>;
 const WallCopyFn kWallCopy[7] = {k_wall_copy<StoreF32>,  k_wall_copy<StoreF16>,
                                  k_wall_copy<StoreBF16>, k_wall_copy<StoreF32X>,
                                  k_wall_copy<StoreF32P>, k_wall_copy<StoreF16C>,
@@ -190,6 +188,7 @@ struct Layout {
   std::vector<int32_t> rch_box;   // reduction chunks (kRedChunk nodes of one box each)
   int64_t wtotal = 0;             // wall-node slots of all boxes (stash plane length)
   int64_t total = 0;  // plane length (nodes, all boxes, aligned)
+  int64_t ctotal = 0; // plane length of the compact schedule's arrays (padded rows)
   int32_t nblk = 0, ntile = 0, ncol = 0, nblk_pad = 0;
   // D3Q27: col_tiles and ccol_tiles hold first the tiles that run the kernel
   // without wall logic (ncol_plain, nccol_plain entries, padded to a
@@ -293,7 +292,8 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, Layout &L,
     B.nz = P.nz;
     B.walls = P.walls;
     B.n = (int64_t)P.nx * P.ny * P.nz;
-    B.base = off;
+    B.base = B.pbase = off;
+    B.px = P.nx;
     off = align_up(off + B.n, kAlign);
     B.blk0 = blk;
     const int32_t nb = (int32_t)((B.n + kBlock - 1) / kBlock);
@@ -380,11 +380,43 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, Layout &L,
   // (16-bit storage measured 1-3 % faster than with power-of-two planes).
   L.total = std::max<int64_t>(off, kAlign);
   if ((L.total / kAlign) % 2 == 0) L.total += kAlign;
+  L.ctotal = L.total;
   L.nblk = blk;
   L.ntile = tile;
   // grids remapped across XCDs are padded to a multiple of 8 idle blocks
   L.nblk_pad = (int32_t)align_up(blk, 8);
   while ((int32_t)L.blk_box.size() < L.nblk_pad) L.blk_box.push_back(-1);
+}
+
+// Rows of the compact schedule's arrays (the compact state in a population
+// buffer, the moments in aux): padded to 64 bytes if all boxes' padded planes
+// fit the caller's buffers (whose sizes are those of the unpadded populations
+// and of 21 aux planes; the schedule uses 17 and 11, and two FP64 planes with
+// the mass-exact formats), else not.  A tile's row segments then start on a
+// sector and its streaming stores fill whole ones: unpadded, the 16-bit
+// 190x131x150 box took 182 + 218 us a step, padded 157 + 171.  (To 128 bytes:
+// the same there, but 24 boxes of 24 to 128 nodes an edge take 5 % longer.)
+void pad_rows(Layout &L, int32_t storage) {
+  constexpr int32_t kUnit = 16;
+  size_t pop = 0, aux = 0;
+  buffer_sizes(storage, L.total, &pop, &aux);
+  const int64_t extra = storage_exact(storage) ? 16 : 0;
+  int64_t off = 0;
+  for (const BoxDev &B : L.boxes)
+    off = align_up(off + align_up(B.nx, kUnit) * B.ny * B.nz, kAlign);
+  int64_t total = std::max<int64_t>(off, kAlign);
+  if ((total / kAlign) % 2 == 0) total += kAlign;
+  if (total > kMaxNodes + 2 * kAlign ||
+      align256(kCompact * total * 4) + extra * total > (int64_t)pop ||
+      align256(kMoments * total * 4) + extra * total > (int64_t)aux)
+    return;
+  off = 0;
+  for (BoxDev &B : L.boxes) {
+    B.pbase = off;
+    B.px = (int32_t)align_up(B.nx, kUnit);
+    off = align_up(off + (int64_t)B.px * B.ny * B.nz, kAlign);
+  }
+  L.ctotal = total;
 }
 
 // Split of a box's tiles between the launch without wall logic and the one
@@ -412,7 +444,8 @@ int32_t pack_tiles(std::vector<TileEntry> &out, std::vector<TileEntry> &plain,
 // hold r3, r2 and r1 points of the tile + 3, + 2 and + 1 (0: no such ring):
 // of the shapes that fit, the one that covers the box with the fewest tiles,
 // counting 4 / w of a tile for its short rows (each row segment of w nodes
-// touches one more cache line than it fills); the nominal shape wins ties.
+// touches one more cache line than it fills; twice that where its neighbours
+// share 64-byte sectors with it); the nominal shape wins ties.
 // A fixed shape left most lanes of ragged boxes idle: a 70 x 70 layer takes
 // 18 tiles of 64 x 8 but 12 of 80 x 6.
 void fit_tile(int nx, int ny, int tx, int ty, int nt, int r3, int r2, int r1, TileShape &T) {
@@ -422,7 +455,8 @@ void fit_tile(int nx, int ny, int tx, int ty, int nt, int r3, int r2, int r1, Ti
     if (2 * (w + 2 + h) > nt || ((2 * w + 63) & ~63) + 2 * (h + 2) > nt) return;
     if ((r3 && (w + 6) * (h + 6) > r3) || (r2 && (w + 4) * (h + 4) > r2)) return;
     if ((w + 2) * (h + 2) > r1) return;
-    const double n = (double)((nx + w - 1) / w) * ((ny + h - 1) / h) * (1.0 + 4.0 / w);
+    const double lines = w % 16 && w < nx ? 8.0 : 4.0;
+    const double n = (double)((nx + w - 1) / w) * ((ny + h - 1) / h) * (1.0 + lines / w);
     if (n < best * (1.0 - 1e-9)) {
       best = n;
       T.w = w;
@@ -658,7 +692,7 @@ int launch_pull(cglbm_handle *h, hipStream_t s, int bounce) {
   hipLaunchKernelGGL(kPull[stash ? 1 : 0][h->storage], dim3(h->L.nblk_pad), dim3(kBlock), 0, s,
                      h->d_boxes,
                      h->d_blk_box, h->pop[h->cur], h->pop[1 - h->cur], h->aux, h->L.total,
-                     bounce, stash, h->L.wtotal);
+                     bounce, stash, h->L.wtotal, (int64_t)0);
   if (stash && !h->L.wblk_box.empty())
     hipLaunchKernelGGL(kWallCopy[h->storage], dim3((unsigned)h->L.wblk_box.size()), dim3(kBlock),
                        0, s, h->d_boxes, h->d_wblk_box, (const void *)stash, h->pop[1 - h->cur],
@@ -719,7 +753,7 @@ int launch_fused_compact(cglbm_handle *h, hipStream_t s) {
   const TileEntry *cols = h->d_col_tiles;
   float *aux = h->aux;
   void *dst = h->pop[1 - h->cur];
-  int64_t plane = h->L.total;
+  int64_t plane = h->L.ctotal;
   const FusedFn *fn = storage_exact(h->storage) ? F.k->fcx : F.k->fc;
   return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.k->nt, s, boxes, cols, aux, dst,
                       plane);
@@ -743,7 +777,7 @@ int launch_cpull(cglbm_handle *h, hipStream_t s, int rd = 0) {
     if (n[w] > 0)
       hipLaunchKernelGGL(fn[w], dim3((unsigned)n[w]), dim3((unsigned)C.k->nt), 0,
                          (both && w) ? h->side : s, h->d_boxes, h->d_ccol_tiles + (w ? n[0] : 0),
-                         (const float *)h->pop[1 - h->cur], h->aux, h->L.total,
+                         (const float *)h->pop[1 - h->cur], h->aux, h->L.ctotal,
                          (const void *)h->cstash[rd], h->cstash[1 - rd], h->L.wtotal);
   return both ? join_side(h, s) : CGLBM_OK;
 }
@@ -753,7 +787,7 @@ int launch_emit(cglbm_handle *h, hipStream_t s, int wi = 0) {
                          ? kEmitX[h->storage]
                          : kEmit[h->storage == CGLBM_FP32_PAIRS ? 1 : 0][h->L.general ? 1 : 0],
                      dim3(h->L.nblk_pad), dim3(kBlock), 0, s, h->d_boxes, h->d_blk_box,
-                     (const float *)h->pop[1 - h->cur], h->pop[h->cur], h->L.total);
+                     (const float *)h->pop[1 - h->cur], h->pop[h->cur], h->L.total, h->L.ctotal);
   if (h->L.walls && !h->L.wblk_box.empty())
     hipLaunchKernelGGL(storage_16bit(h->storage) ? kWallEncode[h->storage]
                                                  : kWallCopy[h->storage],
@@ -771,7 +805,7 @@ int launch_pull_compact(cglbm_handle *h, hipStream_t s) {
                                                         : kPull[stash ? 1 : 0][h->storage],
                      dim3(h->L.nblk_pad), dim3(kBlock), 0, s,
                      h->d_boxes, h->d_blk_box, h->pop[h->cur], h->pop[1 - h->cur], h->aux,
-                     h->L.total, 1, stash, h->L.wtotal);
+                     h->L.total, 1, stash, h->L.wtotal, h->L.ctotal);
   return CGLBM_OK;
 }
 // Layouts the compact schedule serves: D3Q27, FP32 storage (either layout,
@@ -887,19 +921,6 @@ int launch_collide(cglbm_handle *h, hipStream_t s) {
   return CGLBM_OK;
 }
 
-// The collision half of a compact step: the fused kernel for Model D with
-// Q; for the general families the interface kernel and the collision
-// writing compact states.
-int launch_compact_collide(cglbm_handle *h, hipStream_t s) {
-  if (!h->L.general) return launch_fused_compact(h, s);
-  int rc = launch_iface(h, s, 0);
-  if (rc) return rc;
-  hipLaunchKernelGGL(kCollideCompact, dim3(h->L.nblk_pad), dim3(kBlock), 0, s, h->d_boxes,
-                     h->d_blk_box, h->aux, (const void *)h->pop[h->cur], h->pop[1 - h->cur],
-                     h->L.total);
-  return CGLBM_OK;
-}
-
 template <class F>
 int timed(cglbm_handle *h, hipStream_t s, int kind, F &&launch) {
   if (h->prof && h->ev_used + 2 <= h->ev.size()) {
@@ -968,7 +989,7 @@ int capture_compact_pair(cglbm_handle *h) {
   int rc = CGLBM_OK;
   for (int k = 0; k < 2 && !rc; ++k) {
     rc = launch_cpull(h, h->cap_stream, k);
-    if (!rc) rc = launch_compact_collide(h, h->cap_stream);
+    if (!rc) rc = launch_fused_compact(h, h->cap_stream);
   }
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
@@ -1074,13 +1095,13 @@ int step_compact(cglbm_handle *h, int32_t n, hipStream_t s) {
     h->clive = false;
     if (wi == 1) {
       rc = timed(h, s, KIND_PULL, [&] { return launch_cpull(h, s, 1); });
-      if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_compact_collide(h, s); });
+      if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_fused_compact(h, s); });
       wi = 0;
       k = 1;
     }
   } else {
     rc = timed(h, s, KIND_PULL_FIRST, [&] { return launch_pull_compact(h, s); });
-    if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_compact_collide(h, s); });
+    if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_fused_compact(h, s); });
     k = 1;
   }
   if (!rc && h->use_graph && !h->prof && n - k >= 2) {
@@ -1089,7 +1110,7 @@ int step_compact(cglbm_handle *h, int32_t n, hipStream_t s) {
   }
   for (; k < n && !rc; ++k) {
     rc = timed(h, s, KIND_PULL, [&] { return launch_cpull(h, s, wi); });
-    if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_compact_collide(h, s); });
+    if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_fused_compact(h, s); });
     wi = 1 - wi;
   }
   if (rc) return rc;
@@ -1343,6 +1364,7 @@ int init_handle(int lattice, cglbm_handle **out, int32_t n_boxes, const cglbm_bo
   h->storage = storage;
   h->lattice = lattice;
   build_layout(n_boxes, boxes, h->L, lattice);
+  if (lattice == LATTICE_D3Q27) pad_rows(h->L, storage);
   build_ccolumns(h->L, 0);
   h->ccol_cap = h->L.ccol_tiles.size();
   for (const BoxDev &B : h->L.boxes) {
@@ -1693,9 +1715,9 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   // the other buffer, which the first collision writes from the pull above
   int cfbest = best;
   if (!rc && compact_ok(h)) {
-    if (!(rc = launch_pull(h, s, 1))) rc = launch_compact_collide(h, s);
+    if (!(rc = launch_pull_compact(h, s))) rc = launch_fused_compact(h, s);
     double cf_ms = 1e300;
-    for (int v = 0; v < kNumFused && !rc && !h->L.general; ++v) {
+    for (int v = 0; v < kNumFused && !rc; ++v) {
       double ms = 0.0;
       if ((rc = select_variant(h, v, s)) ||
           (rc = time_in_step(s, reps, [&] { return launch_cpull(h, s); },
@@ -1712,7 +1734,7 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     for (int v = 0; v < kNumCPull && !rc; ++v) {
       double ms = 0.0;
       if ((rc = select_cvariant(h, v, s)) ||
-          (rc = time_in_step(s, reps, [&] { return launch_compact_collide(h, s); },
+          (rc = time_in_step(s, reps, [&] { return launch_fused_compact(h, s); },
                              [&] { return launch_cpull(h, s); }, ms)))
         break;
       if (ms < cbest_ms) {
@@ -1734,7 +1756,7 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     if (cmp ? !compact_ok(h) : h->L.general) continue;
     auto launch = [&](hipStream_t cs, int k) {
       int r = cmp ? launch_cpull(h, cs, k) : CGLBM_OK;
-      if (!r) r = cmp ? launch_compact_collide(h, cs) : launch_fused(h, cs, 0);
+      if (!r) r = cmp ? launch_fused_compact(h, cs) : launch_fused(h, cs, 0);
       return r;
     };
     int32_t mbest = cmp ? h->wmode_compact : h->wmode_pop;

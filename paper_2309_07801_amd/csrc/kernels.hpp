@@ -55,6 +55,8 @@ struct BoxDev {
   uint32_t walls;
   int64_t base;         // first node of the box in the concatenated arrays
   int64_t n;            // nx*ny*nz
+  int64_t pbase;        // first node of the box in the compact schedule's arrays
+  int32_t px;           // and the length of their rows (nx, or padded)
   int32_t blk0;         // first 256-node block of the box (k_pull, k_collide)
   int32_t tile0;        // first tile of the box (k_interface)
   int32_t tnx, tny;     // tiles along x, y
@@ -410,9 +412,11 @@ struct Pops {
   __device__ double *restp(int c) const { return rest + (int64_t)c * plane; }
 };
 
-// FP64 colour densities (mass-exact formats), after the 21 float aux planes.
-__device__ __forceinline__ double *aux_rho64(float *aux, int64_t plane) {
-  return (double *)((char *)aux + align256((int64_t)A_COUNT * plane * 4));
+// FP64 colour densities (mass-exact formats), after the float aux planes: all
+// 21, or in the compact schedule's layout of aux the moments alone.
+constexpr int kMoments = A_PYZ + 1;
+__device__ __forceinline__ double *aux_rho64(float *aux, int64_t plane, int planes = A_COUNT) {
+  return (double *)((char *)aux + align256((int64_t)planes * plane * 4));
 }
 
 // Shift of direction i of colour c (0 without shift): the constant shift
@@ -560,7 +564,7 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
                                                  void *__restrict__ src_, void *__restrict__ dst_,
                                                  float *__restrict__ aux, int64_t plane,
                                                  int bounce, void *__restrict__ stash_,
-                                                 int64_t wplane) {
+                                                 int64_t wplane, int64_t cplane) {
   const uint32_t lb = xcd_block();
   const int b = blk_box[lb];
   if (b < 0) return;
@@ -585,6 +589,13 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
     for (int c = 0; c < 3; ++c)
       row[a][c] = (uint32_t)B.base + (uint32_t)nx * ((uint32_t)ys[a] + (uint32_t)ny * (uint32_t)zs[c]);
   const uint32_t node = (uint32_t)(B.base + local);
+  // aux node and plane length: the compact schedule's padded rows (cplane
+  // > 0), or the layout of the populations
+  const uint32_t anode = cplane ? (uint32_t)B.pbase + (uint32_t)x +
+                                      (uint32_t)B.px * ((uint32_t)y + (uint32_t)ny * (uint32_t)z)
+                                : node;
+  const int64_t aplane = cplane ? cplane : plane;
+  double *r64 = aux_rho64(aux, aplane, cplane ? kMoments : (int)A_COUNT);
 
   typename S::T gr[kQ], gb[kQ];
   constexpr int i0 = S::kExact ? 1 : 0;
@@ -655,11 +666,10 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
       }
     }
 #pragma unroll
-    for (int k = 0; k <= A_PYZ; ++k) at(PL(aux, k), node) = 0.0f;
+    for (int k = 0; k <= A_PYZ; ++k) at(aux + k * aplane, anode) = 0.0f;
     if (S::kExact) {
-      double *r64 = aux_rho64(aux, plane);
-      at(r64, node) = 0.0;
-      at(r64 + plane, node) = 0.0;
+      at(r64, anode) = 0.0;
+      at(r64 + aplane, anode) = 0.0;
     }
     return;
   }
@@ -691,23 +701,14 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   if (S::kExact) {
     rr = (float)drr;
     rb = (float)drb;
-    double *r64 = aux_rho64(aux, plane);
-    st(&at(r64, node), drr);
-    st(&at(r64 + plane, node), drb);
+    st(&at(r64, anode), drr);
+    st(&at(r64 + aplane, anode), drb);
   }
   // the moments stream to the next kernel: stores with the streaming hint
   // (measured faster for both kernels than plain stores)
-  st(&at(PL(aux, A_RR), node), rr);
-  st(&at(PL(aux, A_RB), node), rb);
-  st(&at(PL(aux, A_JX), node), jx);
-  st(&at(PL(aux, A_JY), node), jy);
-  st(&at(PL(aux, A_JZ), node), jz);
-  st(&at(PL(aux, A_PXX), node), pxx);
-  st(&at(PL(aux, A_PYY), node), pyy);
-  st(&at(PL(aux, A_PZZ), node), pzz);
-  st(&at(PL(aux, A_PXY), node), pxy);
-  st(&at(PL(aux, A_PXZ), node), pxz);
-  st(&at(PL(aux, A_PYZ), node), pyz);
+  const float m[kMoments] = {rr, rb, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz};
+#pragma unroll
+  for (int k = 0; k < kMoments; ++k) st(&at(aux + k * aplane, anode), m[k]);
 }
 
 // Force density at a fluid node: the CSF force of Eq. (15) from the
@@ -1047,9 +1048,8 @@ __device__ __forceinline__ double *compact_rho64(void *cst, int64_t plane) {
   return (double *)((char *)cst + align256((int64_t)kCompact * plane * 4));
 }
 
-// GENERAL: the box's equilibrium family and correction switch (as
-// collide_node<true>); the relaxed second moments have the same form.
-template <bool GENERAL = false>
+// The relaxed second moments have the same form in every equilibrium family;
+// a box without the correction takes Q = 0, as in collide_node<true>.
 __device__ __forceinline__ void compact_of(const BoxDev &B, const NodeIn &in, float (&c)[kCompact]) {
   const float rho = in.rr + in.rb;
   const float irho = rcp(rho);
@@ -1069,7 +1069,7 @@ __device__ __forceinline__ void compact_of(const BoxDev &B, const NodeIn &in, fl
   const float kxz = in.pxz - ux * in.jz - uz * in.jx + rho * ux * uz;
   const float kyz = in.pyz - uy * in.jz - uz * in.jy + rho * uy * uz;
   const float r1 = 1.0f - w1, h1 = 1.0f - 0.5f * w1;
-  const bool use_q = !GENERAL || B.qcorr;
+  const bool use_q = B.qcorr != 0;
   const float Qx = use_q ? in.Qx : 0.f, Qy = use_q ? in.Qy : 0.f, Qz = use_q ? in.Qz : 0.f;
   const float A = r1 * (kxx - kyy) + h1 * (Qx - Qy);
   const float Bd = r1 * (kxx - kzz) + h1 * (Qx - Qz);
@@ -1344,9 +1344,7 @@ struct PopWriter {
   }
 };
 
-// COMPACT: store the compact post-collision state (17 float planes of dst,
-// see compact_of) instead of the populations; unit higher rates only.
-template <class S, bool COMPACT = false>
+template <class S>
 __global__ __launch_bounds__(kBlock) void k_collide(const BoxDev *__restrict__ boxes,
                                                     const int32_t *__restrict__ blk_box,
                                                     float *__restrict__ aux,
@@ -1365,13 +1363,6 @@ __global__ __launch_bounds__(kBlock) void k_collide(const BoxDev *__restrict__ b
   if (is_solid(B, y, z)) return;
   const uint32_t node = (uint32_t)(B.base + local);
   const NodeIn in = load_node_in(aux, plane, node);
-  if (COMPACT) {
-    float c[kCompact];
-    compact_of<true>(B, in, c);
-#pragma unroll
-    for (int k = 0; k < kCompact; ++k) buf_st(c[k], plane_rsrc(dst_, plane * 4, k), node * 4u);
-    return;
-  }
   const Pops<S> dst(dst_, plane);
   PopWriter<S> w(dst, B, node);
   w.set_fraction(in.rr, in.rb);
@@ -1585,7 +1576,9 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   const int x0 = cx * TW, y0 = cy * TH, z0 = te.z0;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
   const int z1 = te.z1;
-  const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
+  // rows of the arrays read and written: the compact schedule's are padded
+  const uint32_t row = (uint32_t)(COMPACT ? B.px : nx), base = (uint32_t)(COMPACT ? B.pbase : B.base);
+  const uint32_t nxy = row * (uint32_t)ny;
   const bool zwalls = WALLS && (B.walls & 2u) != 0;
 
   // Rows in solid layers (y walls), as bits of one register: for each normal
@@ -1607,7 +1600,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     a_off[k] = 0;
     if (i < n3) {
       const int ly = (int)fdiv((uint32_t)i, B.fs.d6), lx = i - ly * R3X;
-      a_off[k] = wrap_any(x0 + lx - 3, nx) + nx * wrap_any(y0 + ly - 3, ny);
+      a_off[k] = wrap_any(x0 + lx - 3, nx) + (int)row * wrap_any(y0 + ly - 3, ny);
       if (WALLS) rows |= solid_row(y0 + ly - 3) << (15 + k);
     }
   }
@@ -1654,7 +1647,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     }
     c_c2[kk] = (lx + 1) + R2X * (ly + 1);
     c_ri[kk] = lx + R1X * ly;
-    c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + (uint32_t)nx * (uint32_t)wrap_any(y0 + ly - 1, ny);
+    c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + row * (uint32_t)wrap_any(y0 + ly - 1, ny);
   }
   const bool in_xy = c_has[0] && gxo < nx && gyo < ny;
   // (lanes without a node of the box load at wrapped, valid addresses and
@@ -1679,7 +1672,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   float pc_[C_PER][5];
   const int wave0 = (int)__builtin_amdgcn_readfirstlane(tid);
   auto load_a = [&](int sl, int64_t pl) {
-    const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t zoff = base + nxy * (uint32_t)wrap_any(sl, nz);
 #pragma unroll
     for (int k = 0; k < G::A_PER; ++k) {
       // (assigned once, after the branch: assignments in both branches had
@@ -1695,7 +1688,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     }
   };
   auto load_c = [&](int sl, int64_t pl) {
-    const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t zoff = base + nxy * (uint32_t)wrap_any(sl, nz);
 #pragma unroll
     for (int kk = 0; kk < C_PER; ++kk) {
       if (kk > 0 && wave0 >= ring) {
@@ -1720,10 +1713,10 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   double d_rr = 0.0, d_rb = 0.0;
   auto load_d = [&](int sl, int64_t pl) {
     if (EXPORT) return;
-    const uint32_t node = (uint32_t)B.base + c_off[0] + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t node = base + c_off[0] + nxy * (uint32_t)wrap_any(sl, nz);
     // the second moments and FP64 densities are read by stage D only
     if (S::kExact) {
-      const double *r64 = aux_rho64(aux, pl);
+      const double *r64 = aux_rho64(aux, pl, COMPACT ? kMoments : (int)A_COUNT);
       d_rr = buf_ld_f64_nt(plane_rsrc(r64, pl * 8, 0), node * 8u);
       d_rb = buf_ld_f64_nt(plane_rsrc(r64, pl * 8, 1), node * 8u);
     }
@@ -2026,7 +2019,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       Qx *= -3.0f;
       Qy *= -3.0f;
       Qz *= -3.0f;
-      const uint32_t node = (uint32_t)B.base + c_off[0] + nxy * (uint32_t)wrap_any(sd, nz);
+      const uint32_t node = base + c_off[0] + nxy * (uint32_t)wrap_any(sd, nz);
       if (!EXPORT) {
         NodeIn in = din;
         in.nx = h_nx;
@@ -2142,7 +2135,8 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
   const int x0 = cxi * TW, y0 = cyi * TH, z0 = te.z0;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
   const int z1 = te.z1;
-  const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
+  const uint32_t row = (uint32_t)B.px, base = (uint32_t)B.pbase;  // padded rows
+  const uint32_t nxy = row * (uint32_t)ny;
   // Ring points of this thread (its own column node first, then a halo point
   // or none) and their LDS slots (row-major in the (TW + 2) x (TH + 2) ring).
   // Halo points: the rows below and above the tile (without the corners) in
@@ -2180,7 +2174,7 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
     rls[k] = lx + R1X * ly;
     rgx[k] = wrap_any(x0 + lx - 1, nx);
     rgy[k] = wrap_any(y0 + ly - 1, ny);
-    roff[k] = (uint32_t)rgx[k] + (uint32_t)nx * (uint32_t)rgy[k];
+    roff[k] = (uint32_t)rgx[k] + row * (uint32_t)rgy[k];
   }
   // the column node lies in the box (not past its last column or row)
   const bool in_xy = has[0] && rgx[0] >= x0 && rgy[0] >= y0;
@@ -2203,7 +2197,7 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
     const int64_t wpl = WALLS ? opaque_i64(wplane) : wplane;
     const StashBuf<S> win(wst_in, wpl), wout(wst_out, wpl);
     const int gz = wrap_any(s, nz);
-    const uint32_t zoff = (uint32_t)B.base + nxy * (uint32_t)gz;
+    const uint32_t zoff = base + nxy * (uint32_t)gz;
     bool rsolid[G::CP];
 #pragma unroll
     for (int k = 0; k < G::CP; ++k)
@@ -2486,13 +2480,13 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
     }
     // slab s - 1 is complete (solid nodes: zero moments)
     const int gzm = wrap_any(s - 1, nz);
-    const uint32_t node = (uint32_t)B.base + roff[0] + nxy * (uint32_t)gzm;
+    const uint32_t node = base + roff[0] + nxy * (uint32_t)gzm;
     const uint32_t off = boff<float>(in_xy && s - 1 >= z0, node);
     const bool osolid = WALLS && is_solid(B, rgy[0], gzm);
     if constexpr (EXACT) {
       acc[0][0] = (float)acc64[0][0];
       acc[0][1] = (float)acc64[0][1];
-      double *r64 = aux_rho64(aux, plane);
+      double *r64 = aux_rho64(aux, plane, kMoments);
       const uint32_t off64 = boff<double>(in_xy && s - 1 >= z0, node);
       buf_st(osolid ? 0.0 : acc64[0][0], plane_rsrc(r64, plane * 8, 0), off64);
       buf_st(osolid ? 0.0 : acc64[0][1], plane_rsrc(r64, plane * 8, 1), off64);
@@ -2522,7 +2516,8 @@ template <class S, bool GENERAL = false>
 __global__ __launch_bounds__(kBlock) void k_emit(const BoxDev *__restrict__ boxes,
                                                  const int32_t *__restrict__ blk_box,
                                                  const float *__restrict__ cst,
-                                                 void *__restrict__ dst_, int64_t plane) {
+                                                 void *__restrict__ dst_, int64_t plane,
+                                                 int64_t cplane) {
   const uint32_t lb = xcd_block();
   const int b = blk_box[lb];
   if (b < 0) return;
@@ -2530,9 +2525,11 @@ __global__ __launch_bounds__(kBlock) void k_emit(const BoxDev *__restrict__ boxe
   const int64_t local = (int64_t)(lb - B.blk0) * kBlock + threadIdx.x;
   if (local >= B.n) return;
   const uint32_t node = (uint32_t)(B.base + local);
+  const uint32_t l = (uint32_t)local, yz = fdiv(l, B.fdx);
+  const uint32_t cnode = (uint32_t)B.pbase + (l - yz * (uint32_t)B.nx) + (uint32_t)B.px * yz;
   float c[kCompact];
 #pragma unroll
-  for (int m = 0; m < kCompact; ++m) c[m] = ldpl_nt(cst, plane, m, node);
+  for (int m = 0; m < kCompact; ++m) c[m] = ldpl_nt(cst, cplane, m, cnode);
   const float rho = c[0] + c[1];
   const float irho = rcp(rho);
   const float p = c[0] * B.cs2r + c[1] * B.cs2b;
@@ -2549,8 +2546,8 @@ __global__ __launch_bounds__(kBlock) void k_emit(const BoxDev *__restrict__ boxe
                   p, c[14], c[15], c[16], w);
   if (S::kExact) {
     // mass-exact storage: the rest populations closed on the FP64 densities
-    const double *r64 = compact_rho64(const_cast<float *>(cst), plane);
-    w.finish(at(r64, node), at(r64 + plane, node));
+    const double *r64 = compact_rho64(const_cast<float *>(cst), cplane);
+    w.finish(at(r64, cnode), at(r64 + cplane, cnode));
   }
 }
 

@@ -51,3 +51,20 @@ def test_every_geometry_gives_the_same_bits(nx, ny, nz, walls):
         sim.close()
         compact = got if compact is None else compact
         assert np.array_equal(got, compact), v
+
+
+@pytest.mark.parametrize("storage", [pkg.FP32, pkg.FP32_EXACT, pkg.FP16_SHIFT, pkg.BF16_CSHIFT])
+@pytest.mark.parametrize("nx", [1, 15, 16, 17, 49])
+def test_padded_rows_of_the_compact_arrays(nx, storage):
+    """Rows padded to 64 bytes where the buffers have the room (17 nodes: FP32
+    and the mass-exact format, not the 16-bit ones; 1 node: none): one step
+    per call of the compact schedule equals the population schedule."""
+    out = []
+    for schedule in (0, 2):
+        sim = _sim(nx, 21, 18, 0, storage)
+        sim.set_schedule(schedule)
+        for _ in range(3):
+            sim.step(1)
+        out.append(_state(sim))
+        sim.close()
+    assert np.array_equal(*out)

@@ -1007,7 +1007,7 @@ int capture_compact_pair(cglbm_handle *h) {
   return CGLBM_OK;
 }
 
-// Mean milliseconds of launch() over `reps` runs of before() and launch() on
+// Median milliseconds of launch() over `reps` runs of before() and launch() on
 // stream s, after one of each untimed; only launch() is timed.
 template <class B, class F>
 int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, double &ms_out) {
@@ -1025,16 +1025,41 @@ int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, double &ms_out
   if (!rc) rc = check_launch();
   if (!rc && hipEventSynchronize(ev.back()) != hipSuccess)
     rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
-  double sum = 0.0;
-  for (int r = 0; r < n && !rc; ++r) {
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, ev[2 * (size_t)r], ev[2 * (size_t)r + 1]);
-    sum += (double)ms;
-  }
+  std::vector<float> t((size_t)n, 0.f);
+  for (int r = 0; r < n && !rc; ++r)
+    (void)hipEventElapsedTime(&t[(size_t)r], ev[2 * (size_t)r], ev[2 * (size_t)r + 1]);
   for (hipEvent_t e : ev)
     if (e) (void)hipEventDestroy(e);
-  ms_out = sum / n;
+  std::sort(t.begin(), t.end());
+  ms_out = (double)t[(size_t)n / 2];
   return rc;
+}
+
+// The fastest of n candidates by time(v, ms): each once, then those within
+// 6 % of the best once more (single medians of a few launches differ by 3 %).
+// ms_out (optional) receives the first times; best_ms the fastest's.
+template <class T>
+int fastest(int n, T &&time, double *ms_out, int &best, double &best_ms) {
+  std::vector<double> ms((size_t)n, 0.0);
+  for (int v = 0; v < n; ++v) {
+    const int rc = time(v, ms[(size_t)v]);
+    if (rc) return rc;
+    if (ms_out) ms_out[v] = ms[(size_t)v];
+  }
+  const double limit = 1.06 * *std::min_element(ms.begin(), ms.end());
+  best_ms = 1e300;
+  for (int v = 0; v < n; ++v) {
+    double again = 0.0;
+    if (!(ms[(size_t)v] <= limit)) continue;
+    const int rc = time(v, again);
+    if (rc) return rc;
+    const double t = 0.5 * (ms[(size_t)v] + again);
+    if (t < best_ms) {
+      best_ms = t;
+      best = v;
+    }
+  }
+  return CGLBM_OK;
 }
 
 // Mean milliseconds per launch(k) over `reps` replays of a graph that
@@ -1689,17 +1714,13 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   HIP_TRY(hipEventCreate(&e1));
   int best = h->variant;
   double best_ms = 1e300;
-  for (int v = 0; v < kNumFused; ++v) {
-    double ms = 0.0;
-    if ((rc = select_variant(h, v, s)) ||
-        (rc = time_in_step(s, reps, pull, [&] { return launch_fused(h, s, 0); }, ms)))
-      break;
-    if (ms_per_variant) ms_per_variant[v] = ms;
-    if (ms < best_ms) {
-      best_ms = ms;
-      best = v;
-    }
-  }
+  rc = fastest(kNumFused,
+               [&](int v, double &ms) {
+                 const int r = select_variant(h, v, s);
+                 return r ? r
+                          : time_in_step(s, reps, pull, [&] { return launch_fused(h, s, 0); }, ms);
+               },
+               ms_per_variant, best, best_ms);
   // the three-kernel schedule after the same pull
   double three_ms = 1e300;
   if (!rc && !(rc = select_variant(h, best, s)))
@@ -1716,32 +1737,25 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   int cfbest = best;
   if (!rc && compact_ok(h)) {
     if (!(rc = launch_pull_compact(h, s))) rc = launch_fused_compact(h, s);
-    double cf_ms = 1e300;
-    for (int v = 0; v < kNumFused && !rc; ++v) {
-      double ms = 0.0;
-      if ((rc = select_variant(h, v, s)) ||
-          (rc = time_in_step(s, reps, [&] { return launch_cpull(h, s); },
-                             [&] { return launch_fused_compact(h, s); }, ms)))
-        break;
-      if (ms < cf_ms) {
-        cf_ms = ms;
-        cfbest = v;
-      }
-    }
-    if (!rc) rc = select_variant(h, cfbest, s);
+    auto cpull = [&] { return launch_cpull(h, s); };
+    auto collide = [&] { return launch_fused_compact(h, s); };
     int cbest = h->cvariant;
-    double cbest_ms = 1e300;
-    for (int v = 0; v < kNumCPull && !rc; ++v) {
-      double ms = 0.0;
-      if ((rc = select_cvariant(h, v, s)) ||
-          (rc = time_in_step(s, reps, [&] { return launch_fused_compact(h, s); },
-                             [&] { return launch_cpull(h, s); }, ms)))
-        break;
-      if (ms < cbest_ms) {
-        cbest_ms = ms;
-        cbest = v;
-      }
-    }
+    double c_ms = 1e300;
+    if (!rc)
+      rc = fastest(kNumFused,
+                   [&](int v, double &ms) {
+                     const int r = select_variant(h, v, s);
+                     return r ? r : time_in_step(s, reps, cpull, collide, ms);
+                   },
+                   nullptr, cfbest, c_ms);
+    if (!rc) rc = select_variant(h, cfbest, s);
+    if (!rc)
+      rc = fastest(kNumCPull,
+                   [&](int v, double &ms) {
+                     const int r = select_cvariant(h, v, s);
+                     return r ? r : time_in_step(s, reps, collide, cpull, ms);
+                   },
+                   nullptr, cbest, c_ms);
     if (!rc) rc = select_cvariant(h, cbest, s);
   }
   h->fvar_pop = best;

@@ -197,6 +197,9 @@ struct Layout {
   // boxes with z walls: the slabs next to them form short chunks of their
   // own (else the first and last chunks of every column are near walls)
   bool zedge = true;
+  // most nodes lie in boxes whose rows of stored words are not whole 128-byte
+  // lines: the fused kernel's population stores are plain ones
+  bool ragged = false;
   bool walls = false;
   bool general = false;  // a box with Model A, B or C or without Q: three-kernel schedule
   bool full_rates = false;  // a box with a higher-order rate other than 1
@@ -276,7 +279,7 @@ int validate_d2q9(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
   return CGLBM_OK;
 }
 
-void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, Layout &L,
+void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storage, Layout &L,
                   int lattice = LATTICE_D3Q27) {
   L = Layout();
   L.lattice = lattice;
@@ -374,6 +377,14 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, Layout &L,
     L.boxes.push_back(B);
     if (P.walls) L.walls = true;
   }
+  // words of the population planes: a float, or a colour pair
+  const int64_t word = storage == CGLBM_FP32 ? 4 : 2 * (int64_t)storage_bytes(storage);
+  int64_t ragged = 0, nodes = 0;
+  for (const BoxDev &B : L.boxes) {
+    nodes += B.n;
+    if (B.nx * word % 128) ragged += B.n;
+  }
+  L.ragged = 2 * ragged > nodes;
   // Plane length: an odd multiple of kAlign nodes, so that consecutive
   // planes of 4-byte words start an odd number of 256-byte units apart and
   // one wave's accesses to the 27 planes spread over more memory channels
@@ -826,7 +837,7 @@ int launch_fused(cglbm_handle *h, hipStream_t s, int export_fields) {
   float *aux = h->aux;
   void *dst = h->pop[1 - h->cur];
   int64_t plane = h->L.total;
-  const FusedFn *fn = export_fields ? F.k->fx : F.k->fn[h->storage];
+  const FusedFn *fn = export_fields ? F.k->fx : F.k->fn[h->L.ragged ? 1 : 0][h->storage];
   return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.k->nt, s, boxes, cols, aux, dst,
                       plane);
 }
@@ -1287,7 +1298,7 @@ int query_sizes(int lattice, int32_t n_boxes, const cglbm_box_params *boxes, int
                                    : validate(n_boxes, boxes, storage);
   if (rc) return rc;
   Layout L;
-  build_layout(n_boxes, boxes, L, lattice);
+  build_layout(n_boxes, boxes, storage, L, lattice);
   size_t pb, ab;
   buffer_sizes(storage, L.total, &pb, &ab, lattice);
   if (pop_bytes) *pop_bytes = pb;
@@ -1388,7 +1399,7 @@ int init_handle(int lattice, cglbm_handle **out, int32_t n_boxes, const cglbm_bo
   h->params.assign(boxes, boxes + n_boxes);
   h->storage = storage;
   h->lattice = lattice;
-  build_layout(n_boxes, boxes, h->L, lattice);
+  build_layout(n_boxes, boxes, storage, h->L, lattice);
   if (lattice == LATTICE_D3Q27) pad_rows(h->L, storage);
   build_ccolumns(h->L, 0);
   h->ccol_cap = h->L.ccol_tiles.size();

@@ -175,9 +175,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *base, i
       const_cast<char *>(static_cast<const char *>(base)) + p * plane_bytes, 0,
       (int)(uint32_t)plane_bytes, 0x00020000);
 }
-// Population stores carry the non-temporal hint: the stored state is read
-// only by the next step's pull, and keeping it out of the caches measured
-// faster for both kernels of the step than plain stores.
+// Population stores carry the non-temporal hint where a box's rows are whole
+// cache lines: the stored state is read only by the next step's pull, and
+// keeping it out of the caches measured faster for both kernels of the step
+// than plain stores (256^3: fused kernel 476 us against 501).  Where rows
+// start inside lines, neighbouring tiles write each line in parts, and plain
+// stores let L2 join them (200x144x177: 511 us against 782 with the hint).
 constexpr int kNonTemporal = 2;  // cache policy bit of a streaming access
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float buf_ld_f32(__amdgpu_buffer_rsrc_t r, uint32_t off) {
@@ -195,23 +198,25 @@ __device__ __forceinline__ W buf_ld_w(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(W, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
   }
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void buf_st(float v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)off, 0,
-                                        kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)off, 0, POLICY);
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void buf_st(uint16_t v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, POLICY);
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void buf_st(uint32_t v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, POLICY);
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void buf_st(uint64_t v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0,
-                                        kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, POLICY);
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void buf_st(double v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0,
-                                        kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, POLICY);
 }
 __device__ __forceinline__ double buf_ld_f64_nt(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, kNonTemporal));
@@ -1297,8 +1302,10 @@ __device__ __forceinline__ NodeIn load_node_in(const float *__restrict__ aux, in
 // Writes one node's collided, recoloured populations in storage format S.
 // Mass-exact formats skip the rest population during the emission and close
 // it at the end from the node's FP64 colour densities.
-template <class S>
+// PLAIN: stores without the streaming hint.
+template <class S, bool PLAIN = false>
 struct PopWriter {
+  static constexpr int kPolicy = PLAIN ? 0 : kNonTemporal;
   const Pops<S> &dst;
   const BoxDev &B;
   bool live;
@@ -1322,10 +1329,10 @@ struct PopWriter {
     using W = typename S::W;
     const int64_t pb = dst.plane * (int64_t)sizeof(W);
     if constexpr (S::kPaired) {
-      buf_st(S::pack(er, eb), plane_rsrc(dst.pw, pb, Pops<S>::slot(i)), boff<W>(live, node));
+      buf_st<kPolicy>(S::pack(er, eb), plane_rsrc(dst.pw, pb, Pops<S>::slot(i)), boff<W>(live, node));
     } else {
-      buf_st(er, plane_rsrc(dst.pw, pb, Pops<S>::slot(i, 0)), boff<W>(live, node));
-      buf_st(eb, plane_rsrc(dst.pw, pb, Pops<S>::slot(i, 1)), boff<W>(live, node));
+      buf_st<kPolicy>(er, plane_rsrc(dst.pw, pb, Pops<S>::slot(i, 0)), boff<W>(live, node));
+      buf_st<kPolicy>(eb, plane_rsrc(dst.pw, pb, Pops<S>::slot(i, 1)), boff<W>(live, node));
     }
     if (S::kExact) {
       sr += (double)decode_pop<S>(B, 0, er, shr);
@@ -1336,11 +1343,11 @@ struct PopWriter {
     if (S::kExact) {
       const int64_t pb = dst.plane * 8;
       const uint32_t off = boff<double>(live, node);
-      buf_st(rho_r - sr, plane_rsrc(dst.rest, pb, 0), off);
-      buf_st(rho_b - sb, plane_rsrc(dst.rest, pb, 1), off);
+      buf_st<kPolicy>(rho_r - sr, plane_rsrc(dst.rest, pb, 0), off);
+      buf_st<kPolicy>(rho_b - sb, plane_rsrc(dst.rest, pb, 1), off);
     }
     if constexpr (S::kCShift)
-      buf_st((uint16_t)craw, plane_rsrc(dst.cfr, dst.plane * 2, 0), boff<uint16_t>(live, node));
+      buf_st<kPolicy>((uint16_t)craw, plane_rsrc(dst.cfr, dst.plane * 2, 0), boff<uint16_t>(live, node));
   }
 };
 
@@ -1548,8 +1555,10 @@ struct FusedGeom {
 };
 
 // COMPACT: store each node's compact post-collision state (17 float planes
-// of dst, see compact_of) instead of its populations.
-template <class G, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false>
+// of dst, see compact_of) instead of its populations.  PLAIN: population
+// stores without the streaming hint.
+template <class G, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false,
+          bool PLAIN = false>
 __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
                                                   float *__restrict__ aux,
@@ -1750,7 +1759,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     }
   } else if (!EXPORT) {
     const Pops<S> dst(dst_, plane_arg);
-    PopWriter<S> w(dst, B, 0u, false);
+    PopWriter<S, PLAIN> w(dst, B, 0u, false);
 #pragma unroll
     for (int i = 0; i < kQ; ++i) w(i, 0.f, 0.f);
     w.finish(0.0, 0.0);
@@ -2047,7 +2056,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
         } else {
           const double fr = d_rr, fb = d_rb;
           const Pops<S> dst(dst_, plane);
-          PopWriter<S> w(dst, B, node, fluid && sd >= z0);
+          PopWriter<S, PLAIN> w(dst, B, node, fluid && sd >= z0);
           w.set_fraction(in.rr, in.rb);
           collide_node(B, in, w, [&] {
             if (kPipeD) load_d(s - 2, plane);

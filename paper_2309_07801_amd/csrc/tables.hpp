@@ -20,17 +20,23 @@ namespace cglbm {
 using FusedFn = void (*)(const BoxDev *, const TileEntry *, float *, void *, int64_t);
 struct FusedKernels {
   int nt, r3, r2, r1;  // threads; points of the tile + 3, + 2 and + 1 its LDS arrays hold
-  FusedFn fn[7][2];    // time step: [storage][0: tiles away from solid layers, 1: near them]
+  // time step: [streaming stores, plain ones][storage][0: tiles away from
+  // solid layers, 1: near them]
+  FusedFn fn[2][7][2];
   FusedFn fx[2];       // field export (no population store): [near solid layers]
   FusedFn fc[2];       // compact schedule: compact state out (FP32): [near solid layers]
   FusedFn fcx[2];      // compact schedule, mass-exact storage (FP64 densities): [near solid layers]
 };
-#define CGLBM_FK_S(G, MW, S) {k_fused<G, MW, false, S, false>, k_fused<G, MW, true, S, false>}
+#define CGLBM_FK_S(G, MW, P, S) \
+  {k_fused<G, MW, false, S, false, false, P>, k_fused<G, MW, true, S, false, false, P>}
+#define CGLBM_FK_P(G, MW, P)                                                                 \
+  {CGLBM_FK_S(G, MW, P, StoreF32),  CGLBM_FK_S(G, MW, P, StoreF16),                           \
+   CGLBM_FK_S(G, MW, P, StoreBF16), CGLBM_FK_S(G, MW, P, StoreF32X),                          \
+   CGLBM_FK_S(G, MW, P, StoreF32P), CGLBM_FK_S(G, MW, P, StoreF16C),                          \
+   CGLBM_FK_S(G, MW, P, StoreBF16C)}
 #define CGLBM_FK(G, MW)                                                                      \
   {G::NT, G::R3, G::R2, G::R1,                                                                \
-   {CGLBM_FK_S(G, MW, StoreF32), CGLBM_FK_S(G, MW, StoreF16), CGLBM_FK_S(G, MW, StoreBF16),   \
-    CGLBM_FK_S(G, MW, StoreF32X), CGLBM_FK_S(G, MW, StoreF32P), CGLBM_FK_S(G, MW, StoreF16C), \
-    CGLBM_FK_S(G, MW, StoreBF16C)},                                                          \
+   {CGLBM_FK_P(G, MW, false), CGLBM_FK_P(G, MW, true)},                                      \
    {k_fused<G, MW, false, StoreF32, true>, k_fused<G, MW, true, StoreF32, true>},            \
    {k_fused<G, MW, false, StoreF32, false, true>, k_fused<G, MW, true, StoreF32, false, true>}, \
    {k_fused<G, MW, false, StoreF32X, false, true>, k_fused<G, MW, true, StoreF32X, false, true>}}

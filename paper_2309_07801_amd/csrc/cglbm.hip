@@ -593,7 +593,7 @@ void build_columns(Layout &L, int v) {
   const FusedVariant &F = fused_variant(v);
   for (BoxDev &B : L.boxes)
     fit_tile(B.nx, B.ny, F.tx, F.ty, F.k->nt, F.k->r3, F.k->r2, F.k->r1, B.fs);
-  build_tiles(L, fit_chunk(L, false, F.zc, F.k->nt, 6.0), 4, L.zedge ? 6 : 0, L.col_tiles,
+  build_tiles(L, fit_chunk(L, false, F.zc, F.k->nt, 3.0), 4, L.zedge ? 6 : 0, L.col_tiles,
               L.ncol_plain, false);
   L.ncol = (int32_t)L.col_tiles.size();
 }

@@ -1743,30 +1743,6 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   };
   load_a(z0 - 3, plane_arg);
   load_c(z0 - 5, plane_arg);
-  if (kPipeD) load_d(z0 - 6, plane_arg);
-  // as many stores as stage D issues, all discarded: on entry to the march
-  // the loads above are then followed by the same count of memory
-  // instructions as in every later iteration, so the waits for them are
-  // the same on both paths into the loop
-  if (!EXPORT && COMPACT) {
-#pragma unroll
-    for (int k = 0; k < kCompact; ++k)
-      buf_st(0.f, plane_rsrc(dst_, plane_arg * 4, k), kDrop);
-    if (S::kExact) {
-      double *r64 = compact_rho64(dst_, plane_arg);
-      buf_st(0.0, plane_rsrc(r64, plane_arg * 8, 0), kDrop);
-      buf_st(0.0, plane_rsrc(r64, plane_arg * 8, 1), kDrop);
-    }
-  } else if (!EXPORT) {
-    const Pops<S> dst(dst_, plane_arg);
-    PopWriter<S, PLAIN> w(dst, B, 0u, false);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) w(i, 0.f, 0.f);
-    w.finish(0.0, 0.0);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 10; ++k) buf_st(0.f, plane_rsrc(aux, plane_arg * 4, A_NX + k), kDrop);
-  }
   __syncthreads();
 
   // Where phi is +1 (or -1) on all points of three slabs, the gradient of the
@@ -1778,12 +1754,14 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   // last three slabs, two bits each (all +1, all -1), newest lowest; n_zero:
   // bit of each slot of the n ring that holds zeros throughout.
   uint32_t pure = 0, n_zero = 0;
-  for (int s = z0 - 3; s < z1 + 3; ++s) {
+  // One iteration; with_d: its stage D runs (slab s - 3 is an output slab).
+  auto march = [&](int s, auto with_d) __attribute__((always_inline)) {
+    constexpr bool kD = decltype(with_d)::value;
     const int64_t plane = opaque_i64(plane_arg);
     // (opaque: the tests of its bits, one lane mask each, are not hoisted
     // into scalar registers)
     if (WALLS) asm volatile("" : "+v"(rows));
-    if (!kPipeD) load_d(s - 3, plane);
+    if (kD && !kPipeD) load_d(s - 3, plane);
     // ---- A: phase field of slab s (Eq. 14) ----
     {
       float *ph = s_phi[(s + 3) % 3];
@@ -1983,16 +1961,14 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     load_a(s + 1, plane);
     load_c(s - 1, plane);
     // ---- D: Q and the collision of slab s-3 (Eqs. 18-19, 25, 65-67) ----
-    // Runs on every lane and in every iteration; only lanes of a fluid node
-    // of the box in an output slab store.  The ring index keeps the slot
-    // non-negative for the slabs before the first output slab.
-    {
+    // Runs on every lane; only lanes of a fluid node of the box store.
+    if constexpr (kD) {
       const int sd = s - 3;
       const bool sz_m = slab_solid(sd - 1), sz_p = slab_solid(sd + 1);
       const bool fluid = in_xy && !(row_bit(10) || slab_solid(sd));
-      float(*qm)[G::R1] = s_q[(sd + 8) % 3];
-      float(*qc)[G::R1] = s_q[(sd + 9) % 3];
-      float(*qp)[G::R1] = s_q[(sd + 10) % 3];
+      float(*qm)[G::R1] = s_q[(sd + 2) % 3];
+      float(*qc)[G::R1] = s_q[(sd + 3) % 3];
+      float(*qp)[G::R1] = s_q[(sd + 4) % 3];
       const int c1 = c_ri[0];
       // d q_x / dx: pairs along x over (dy, dz); likewise y and z
       float Qx = 0.f, Qy = 0.f, Qz = 0.f;
@@ -2043,20 +2019,20 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
         if (COMPACT) {
           float c[kCompact];
           compact_of(B, in, c);
-          const uint32_t off = boff<float>(fluid && sd >= z0, node);
+          const uint32_t off = boff<float>(fluid, node);
 #pragma unroll
           for (int k = 0; k < kCompact; ++k) buf_st(c[k], plane_rsrc(dst_, plane * 4, k), off);
           if (S::kExact) {
             // mass-exact storage: the FP64 colour densities travel with it
             double *r64 = compact_rho64(dst_, plane);
-            const uint32_t off64 = boff<double>(fluid && sd >= z0, node);
+            const uint32_t off64 = boff<double>(fluid, node);
             buf_st(d_rr, plane_rsrc(r64, plane * 8, 0), off64);
             buf_st(d_rb, plane_rsrc(r64, plane * 8, 1), off64);
           }
         } else {
           const double fr = d_rr, fb = d_rb;
           const Pops<S> dst(dst_, plane);
-          PopWriter<S, PLAIN> w(dst, B, node, fluid && sd >= z0);
+          PopWriter<S, PLAIN> w(dst, B, node, fluid);
           w.set_fraction(in.rr, in.rb);
           collide_node(B, in, w, [&] {
             if (kPipeD) load_d(s - 2, plane);
@@ -2065,7 +2041,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
         }
       } else {
         // interface fields of every node of the box (zero at solid nodes)
-        const uint32_t off = boff<float>(in_xy && sd >= z0, node);
+        const uint32_t off = boff<float>(in_xy, node);
         const float v[10] = {h_nx, h_ny, h_nz, h_Fx, h_Fy, h_Fz, Qx, Qy, Qz, h_k};
 #pragma unroll
         for (int k = 0; k < 10; ++k)
@@ -2080,7 +2056,38 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     h_Fy = f_Fy;
     h_Fz = f_Fz;
     h_k = f_k;
+  };
+  // the six iterations that fill the rings run without stage D (which takes
+  // more than half of an iteration: 200x144x177, 28 output slabs a block, the
+  // population schedule's fused kernel 580 -> 519 us; 128x112x96 with 16-bit
+  // storage, 16 slabs a block, 150 -> 95 us)
+  int s = z0 - 3;
+  for (; s < z0 + 3; ++s) march(s, std::false_type());
+  if (kPipeD) load_d(z0, plane_arg);
+  // as many stores as stage D issues, all discarded: on entry to the march
+  // the loads above are then followed by the same count of memory
+  // instructions as in every later iteration, so the waits for them are
+  // the same on both paths into the loop
+  if (!EXPORT && COMPACT) {
+#pragma unroll
+    for (int k = 0; k < kCompact; ++k)
+      buf_st(0.f, plane_rsrc(dst_, plane_arg * 4, k), kDrop);
+    if (S::kExact) {
+      double *r64 = compact_rho64(dst_, plane_arg);
+      buf_st(0.0, plane_rsrc(r64, plane_arg * 8, 0), kDrop);
+      buf_st(0.0, plane_rsrc(r64, plane_arg * 8, 1), kDrop);
+    }
+  } else if (!EXPORT) {
+    const Pops<S> dst(dst_, plane_arg);
+    PopWriter<S, PLAIN> w(dst, B, 0u, false);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) w(i, 0.f, 0.f);
+    w.finish(0.0, 0.0);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 10; ++k) buf_st(0.f, plane_rsrc(aux, plane_arg * 4, A_NX + k), kDrop);
   }
+  for (; s < z1 + 3; ++s) march(s, std::true_type());
 }
 
 // ---------------------------------------------------------------------------

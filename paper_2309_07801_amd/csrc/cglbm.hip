@@ -822,7 +822,7 @@ int launch_pull_compact(cglbm_handle *h, hipStream_t s) {
 // Layouts the compact schedule serves: D3Q27, FP32 storage (either layout,
 // any equilibrium family), or a mass-exact storage (FP32 or 16-bit; Model D
 // with Q), two buffers, unit higher rates.  With a 16-bit storage the
-// compact state (17 floats and the FP64 colour densities, 84 bytes a node)
+// compact state (15 floats and the FP64 colour densities, 76 bytes a node)
 // fits the other population buffer (at least 120 bytes a node).
 bool compact_ok(const cglbm_handle *h) {
   return h->lattice == LATTICE_D3Q27 && !h->inplace && !h->L.full_rates &&

@@ -716,13 +716,16 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   for (int k = 0; k < kMoments; ++k) st(&at(aux + k * aplane, anode), m[k]);
 }
 
-// Force density at a fluid node: the CSF force of Eq. (15) from the
-// curvature, |grad phi| and the normal, the constant body force G, and the
-// buoyancy force -(rho - rho_ref) g of the Rayleigh-Taylor case (Sec. IV.E).
-__device__ __forceinline__ void interface_force(const BoxDev &B, float kap, float mag, float nxv,
-                                                float nyv, float nzv, float rho, float &Fx,
-                                                float &Fy, float &Fz) {
-  const float hs = 0.5f * B.sigma * kap * mag;
+// Strength of the CSF force (Eq. 15): half of sigma kappa |grad phi|, which
+// the normal turns into the force.
+__device__ __forceinline__ float csf_strength(const BoxDev &B, float kap, float mag) {
+  return 0.5f * B.sigma * kap * mag;
+}
+// Force density at a fluid node: the CSF force from its strength and the
+// normal, the constant body force G, and the buoyancy force
+// -(rho - rho_ref) g of the Rayleigh-Taylor case (Sec. IV.E).
+__device__ __forceinline__ void node_force(const BoxDev &B, float hs, float nxv, float nyv,
+                                           float nzv, float rho, float &Fx, float &Fy, float &Fz) {
   const float drho = rho - B.rho_ref;
   Fx = fmaf(-drho, B.bgx, fmaf(hs, nxv, B.Gx));
   Fy = fmaf(-drho, B.bgy, fmaf(hs, nyv, B.Gy));
@@ -872,7 +875,7 @@ __global__ __launch_bounds__(kBlock) void k_interface(const BoxDev *__restrict__
       const float rr = at(PL(aux, A_RR), node);
       const float rb = at(PL(aux, A_RB), node);
       const float rho = rr + rb;
-      interface_force(B, kap, mag, nxv, nyv, nzv, rho, Fx, Fy, Fz);
+      node_force(B, csf_strength(B, kap, mag), nxv, nyv, nzv, rho, Fx, Fy, Fz);
       const float irho = rcp(rho);
       const float ux = fmaf(0.5f, Fx, at(PL(aux, A_JX), node)) * irho;
       const float uy = fmaf(0.5f, Fy, at(PL(aux, A_JY), node)) * irho;
@@ -1038,24 +1041,38 @@ __device__ __forceinline__ void collide_node(const BoxDev &B, const NodeIn &in, 
 }
 
 // ---------------------------------------------------------------------------
-// Compact post-collision state (unit higher rates, Model D with Q).  With
-// every rate above second order equal to one, the collided populations of a
-// node (Eqs. 66-67) and their recolouring (Eqs. 18-19) are a function of 17
-// values: rho_r, rho_b, u, F, the six relaxed second-order central moments
-// and n.  compact_of computes them from a node's moments and interface
-// fields with the arithmetic of collide_node; emit_compact rebuilds the
-// populations from them, bit for bit those collide_node emits.
+// Compact post-collision state (unit higher rates).  With every rate above
+// second order equal to one, the collided populations of a node (Eqs. 66-67)
+// and their recolouring (Eqs. 18-19) are a function of its densities, its
+// velocity, the six relaxed second-order central moments, the normal n and
+// the strength hs of its CSF force (which with n and the density gives F).
+// compact_of computes them from a node's moments and interface fields with
+// the arithmetic of collide_node; emit_compact rebuilds the populations from
+// them, bit for bit those collide_node emits.
+// Away from the interface n is exactly zero: the node's hs then holds the
+// mark kFlat (-0, which no other hs is stored as), its n is not stored, and
+// readers take zero without loading it: 12 values a node there instead of 15
+// (and of the 17 with F in place of hs).
 // ---------------------------------------------------------------------------
-constexpr int kCompact = 17;  // planes: rr rb ux uy uz Fx Fy Fz sxx syy szz sxy sxz syz nx ny nz
+constexpr int kCompact = 15;  // planes: rr rb ux uy uz hs sxx syy szz sxy sxz syz nx ny nz
+constexpr int kCompactN = 12;  // first plane of n
+constexpr int kHs = 5;
+__device__ __forceinline__ float hs_mark(float hs, float nxv, float nyv, float nzv) {
+  return nxv == 0.f && nyv == 0.f && nzv == 0.f ? -0.0f : hs + 0.0f;
+}
+__device__ __forceinline__ bool hs_flat(float hs) {
+  return __builtin_bit_cast(uint32_t, hs) == 0x80000000u;
+}
 // FP64 colour densities of the compact state (mass-exact storage), after its
-// 17 float planes.
+// float planes.
 __device__ __forceinline__ double *compact_rho64(void *cst, int64_t plane) {
   return (double *)((char *)cst + align256((int64_t)kCompact * plane * 4));
 }
 
 // The relaxed second moments have the same form in every equilibrium family;
 // a box without the correction takes Q = 0, as in collide_node<true>.
-__device__ __forceinline__ void compact_of(const BoxDev &B, const NodeIn &in, float (&c)[kCompact]) {
+__device__ __forceinline__ void compact_of(const BoxDev &B, const NodeIn &in, float hs,
+                                           float (&c)[kCompact]) {
   const float rho = in.rr + in.rb;
   const float irho = rcp(rho);
   const float ux = div_refined(fmaf(0.5f, in.Fx, in.jx), rho, irho);
@@ -1086,18 +1103,16 @@ __device__ __forceinline__ void compact_of(const BoxDev &B, const NodeIn &in, fl
   c[2] = ux;
   c[3] = uy;
   c[4] = uz;
-  c[5] = in.Fx;
-  c[6] = in.Fy;
-  c[7] = in.Fz;
-  c[8] = (A + Bd + T) * third;
-  c[9] = (T - 2.0f * A + Bd) * third;
-  c[10] = (T + A - 2.0f * Bd) * third;
-  c[11] = r1 * kxy;
-  c[12] = r1 * kxz;
-  c[13] = r1 * kyz;
-  c[14] = in.nx;
-  c[15] = in.ny;
-  c[16] = in.nz;
+  c[kHs] = hs_mark(hs, in.nx, in.ny, in.nz);
+  c[6] = (A + Bd + T) * third;
+  c[7] = (T - 2.0f * A + Bd) * third;
+  c[8] = (T + A - 2.0f * Bd) * third;
+  c[9] = r1 * kxy;
+  c[10] = r1 * kxz;
+  c[11] = r1 * kyz;
+  c[12] = in.nx;
+  c[13] = in.ny;
+  c[14] = in.nz;
 }
 
 // The central moments and recolouring inputs of a compact state: k (Eqs.
@@ -1113,20 +1128,22 @@ __device__ __forceinline__ void compact_post(const BoxDev &B, const float (&c)[k
   const float rho = rr + rb;
   const float irho = rcp(rho);
   const float p = rr * B.cs2r + rb * B.cs2b;
+  float Fx, Fy, Fz;
+  node_force(B, c[kHs], c[12], c[13], c[14], rho, Fx, Fy, Fz);
   if (GENERAL)
-    model_moments(B.model, rho, p, c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9], c[10], c[11],
-                  c[12], c[13], o.k);
+    model_moments(B.model, rho, p, c[2], c[3], c[4], Fx, Fy, Fz, c[6], c[7], c[8], c[9], c[10],
+                  c[11], o.k);
   else
-    model_d_moments(rho, p, c[5], c[6], c[7], c[8], c[9], c[10], c[11], c[12], c[13], o.k);
+    model_d_moments(rho, p, Fx, Fy, Fz, c[6], c[7], c[8], c[9], c[10], c[11], o.k);
   o.ux = c[2];
   o.uy = c[3];
   o.uz = c[4];
   o.cr = div_refined(rr, rho, irho);
   o.cb = div_refined(rb, rho, irho);
   const float s = B.beta * o.cr * o.cb * p;
-  o.Rx = s * c[14];
-  o.Ry = s * c[15];
-  o.Rz = s * c[16];
+  o.Rx = s * c[12];
+  o.Ry = s * c[13];
+  o.Rz = s * c[14];
 }
 
 // Populations -> central moments about u along one axis: (f_-, f_0, f_+) ->
@@ -1554,8 +1571,8 @@ struct FusedGeom {
   static constexpr int A_PER = (R3 + NT - 1) / NT, B_PER = (R2 + NT - 1) / NT;
 };
 
-// COMPACT: store each node's compact post-collision state (17 float planes
-// of dst, see compact_of) instead of its populations.  PLAIN: population
+// COMPACT: store each node's compact post-collision state (see compact_of)
+// instead of its populations.  PLAIN: population
 // stores without the streaming hint.
 template <class G, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false,
           bool PLAIN = false>
@@ -1662,7 +1679,9 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   // (lanes without a node of the box load at wrapped, valid addresses and
   // store nowhere)
   // interface values of the tile point, one slab behind the q ring
-  float h_nx = 0.f, h_ny = 0.f, h_nz = 0.f, h_Fx = 0.f, h_Fy = 0.f, h_Fz = 0.f, h_k = 0.f;
+  // (its densities and momentum stay from stage C; hs with n gives F again)
+  float h_nx = 0.f, h_ny = 0.f, h_nz = 0.f, h_hs = 0.f, h_k = 0.f;
+  float h_m[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
   auto slab_solid = [&](int s) {
     if (!zwalls) return false;
     const int gz = wrap_any(s, nz);
@@ -1729,11 +1748,6 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       d_rr = buf_ld_f64_nt(plane_rsrc(r64, pl * 8, 0), node * 8u);
       d_rb = buf_ld_f64_nt(plane_rsrc(r64, pl * 8, 1), node * 8u);
     }
-    din.rr = ldpl(aux, pl, A_RR, node);
-    din.rb = ldpl(aux, pl, A_RB, node);
-    din.jx = ldpl(aux, pl, A_JX, node);
-    din.jy = ldpl(aux, pl, A_JY, node);
-    din.jz = ldpl(aux, pl, A_JZ, node);
     din.pxx = ldpl_nt(aux, pl, A_PXX, node);
     din.pyy = ldpl_nt(aux, pl, A_PYY, node);
     din.pzz = ldpl_nt(aux, pl, A_PZZ, node);
@@ -1861,7 +1875,8 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       }
     }
     // ---- C: grad n, kappa, F, u, q of slab s-2 (Eqs. 11, 15, 16, 65) ----
-    float f_nx = 0.f, f_ny = 0.f, f_nz = 0.f, f_Fx = 0.f, f_Fy = 0.f, f_Fz = 0.f, f_k = 0.f;
+    float f_nx = 0.f, f_ny = 0.f, f_nz = 0.f, f_hs = 0.f, f_k = 0.f;
+    float f_m[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
     if (s - 2 >= z0 - 1) {
       const int sc = s - 2;
       const bool sz_m = slab_solid(sc - 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc + 1);
@@ -1877,7 +1892,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
         if (!c_has[kk]) continue;
         const int c2 = c_c2[kk], ri = c_ri[kk];
         float qx = 0.f, qy = 0.f, qz = 0.f;
-        float kap = 0.f, Fx = 0.f, Fy = 0.f, Fz = 0.f;
+        float kap = 0.f, hs = 0.f;
         float nxv = 0.f, nyv = 0.f, nzv = 0.f, mag = 0.f;
         if (!flat) {
           nxv = nc[0][c2];
@@ -1932,7 +1947,9 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
           const float rr = pc_[kk][0];
           const float rb = pc_[kk][1];
           const float rho = rr + rb;
-          interface_force(B, kap, mag, nxv, nyv, nzv, rho, Fx, Fy, Fz);
+          float Fx, Fy, Fz;
+          hs = csf_strength(B, kap, mag);
+          node_force(B, hs, nxv, nyv, nzv, rho, Fx, Fy, Fz);
           const float irho = rcp(rho);
           const float ux = fmaf(0.5f, Fx, pc_[kk][2]) * irho;
           const float uy = fmaf(0.5f, Fy, pc_[kk][3]) * irho;
@@ -1949,10 +1966,10 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
           f_nx = nxv;
           f_ny = nyv;
           f_nz = nzv;
-          f_Fx = Fx;
-          f_Fy = Fy;
-          f_Fz = Fz;
+          f_hs = hs;
           f_k = kap;
+#pragma unroll
+          for (int m = 0; m < 5; ++m) f_m[m] = pc_[0][m];
         }
       }
     }
@@ -2005,23 +2022,32 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       Qy *= -3.0f;
       Qz *= -3.0f;
       const uint32_t node = base + c_off[0] + nxy * (uint32_t)wrap_any(sd, nz);
+      float Fx, Fy, Fz;
+      node_force(B, h_hs, h_nx, h_ny, h_nz, h_m[0] + h_m[1], Fx, Fy, Fz);
       if (!EXPORT) {
         NodeIn in = din;
+        in.rr = h_m[0];
+        in.rb = h_m[1];
+        in.jx = h_m[2];
+        in.jy = h_m[3];
+        in.jz = h_m[4];
         in.nx = h_nx;
         in.ny = h_ny;
         in.nz = h_nz;
-        in.Fx = h_Fx;
-        in.Fy = h_Fy;
-        in.Fz = h_Fz;
+        in.Fx = Fx;
+        in.Fy = Fy;
+        in.Fz = Fz;
         in.Qx = Qx;
         in.Qy = Qy;
         in.Qz = Qz;
         if (COMPACT) {
           float c[kCompact];
-          compact_of(B, in, c);
+          compact_of(B, in, h_hs, c);
           const uint32_t off = boff<float>(fluid, node);
+          const uint32_t offn = hs_flat(c[kHs]) ? kDrop : off;
 #pragma unroll
-          for (int k = 0; k < kCompact; ++k) buf_st(c[k], plane_rsrc(dst_, plane * 4, k), off);
+          for (int k = 0; k < kCompact; ++k)
+            buf_st(c[k], plane_rsrc(dst_, plane * 4, k), k < kCompactN ? off : offn);
           if (S::kExact) {
             // mass-exact storage: the FP64 colour densities travel with it
             double *r64 = compact_rho64(dst_, plane);
@@ -2042,7 +2068,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       } else {
         // interface fields of every node of the box (zero at solid nodes)
         const uint32_t off = boff<float>(in_xy, node);
-        const float v[10] = {h_nx, h_ny, h_nz, h_Fx, h_Fy, h_Fz, Qx, Qy, Qz, h_k};
+        const float v[10] = {h_nx, h_ny, h_nz, Fx, Fy, Fz, Qx, Qy, Qz, h_k};
 #pragma unroll
         for (int k = 0; k < 10; ++k)
           buf_st(fluid ? v[k] : 0.f, plane_rsrc(aux, plane * 4, A_NX + k), off);
@@ -2052,10 +2078,10 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     h_nx = f_nx;
     h_ny = f_ny;
     h_nz = f_nz;
-    h_Fx = f_Fx;
-    h_Fy = f_Fy;
-    h_Fz = f_Fz;
+    h_hs = f_hs;
     h_k = f_k;
+#pragma unroll
+    for (int m = 0; m < 5; ++m) h_m[m] = f_m[m];
   };
   // the six iterations that fill the rings run without stage D (which takes
   // more than half of an iteration: 200x144x177, 28 output slabs a block, the
@@ -2130,7 +2156,7 @@ struct CPullGeom {
 };
 
 template <class G, bool WALLS = false, class S = StoreF32, bool GENERAL = false>
-__global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxes,
+__global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
                                                   const float *__restrict__ cst,
                                                   float *__restrict__ aux, int64_t plane_arg,
@@ -2206,6 +2232,20 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
 #pragma unroll
   for (int a = 0; a < 2; ++a) acc64[a][0] = acc64[a][1] = 0.0;
 
+  // hs of this thread's ring points, one slab ahead: its mark decides whether
+  // the normals are loaded at all
+  float hs_next[G::CP];
+  auto load_hs = [&](int s, int64_t pl) {
+    const uint32_t zoff = base + nxy * (uint32_t)wrap_any(s, nz);
+#pragma unroll
+    for (int k = 0; k < G::CP; ++k) {
+      float v = 0.f;
+      if (k == 0 || halowave) v = ldpl(cst, pl, kHs, zoff + roff[k]);
+      hs_next[k] = v;
+    }
+  };
+  load_hs(z0 - 1, plane_arg);
+
   for (int s = z0 - 1; s <= z1; ++s) {
     const int64_t plane = opaque_i64(plane_arg);
     // the wall stashes (one descriptor each, rebuilt per slab from an
@@ -2241,8 +2281,15 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
         continue;
       }
       float c[kCompact];
+      c[kHs] = hs_next[k];
 #pragma unroll
-      for (int m = 0; m < kCompact; ++m) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
+      for (int m = 0; m < kCompactN; ++m)
+        if (m != kHs) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
+      c[12] = c[13] = c[14] = 0.f;
+      if (!hs_flat(c[kHs])) {
+#pragma unroll
+        for (int m = kCompactN; m < kCompact; ++m) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
+      }
       CompactPost o;
       compact_post<GENERAL>(B, c, o);
       float g[3][3][3];
@@ -2265,6 +2312,7 @@ __global__ __launch_bounds__(G::NT) void k_cpull(const BoxDev *__restrict__ boxe
       pRy[k] = o.Ry;
       pRz[k] = o.Rz;
     }
+    load_hs(s + 1, plane);
     // mass-exact storage: FP64 sums of the moving values the column node emits
     double emit_r = 0.0, emit_b = 0.0;
 #pragma unroll
@@ -2545,21 +2593,28 @@ __global__ __launch_bounds__(kBlock) void k_emit(const BoxDev *__restrict__ boxe
   const uint32_t cnode = (uint32_t)B.pbase + (l - yz * (uint32_t)B.nx) + (uint32_t)B.px * yz;
   float c[kCompact];
 #pragma unroll
-  for (int m = 0; m < kCompact; ++m) c[m] = ldpl_nt(cst, cplane, m, cnode);
+  for (int m = 0; m < kCompactN; ++m) c[m] = ldpl_nt(cst, cplane, m, cnode);
+  c[12] = c[13] = c[14] = 0.f;
+  if (!hs_flat(c[kHs])) {
+#pragma unroll
+    for (int m = kCompactN; m < kCompact; ++m) c[m] = ldpl_nt(cst, cplane, m, cnode);
+  }
   const float rho = c[0] + c[1];
   const float irho = rcp(rho);
   const float p = c[0] * B.cs2r + c[1] * B.cs2b;
+  float Fx, Fy, Fz;
+  node_force(B, c[kHs], c[12], c[13], c[14], rho, Fx, Fy, Fz);
   float k[27];
   if (GENERAL)
-    model_moments(B.model, rho, p, c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9], c[10], c[11],
-                  c[12], c[13], k);
+    model_moments(B.model, rho, p, c[2], c[3], c[4], Fx, Fy, Fz, c[6], c[7], c[8], c[9], c[10],
+                  c[11], k);
   else
-    model_d_moments(rho, p, c[5], c[6], c[7], c[8], c[9], c[10], c[11], c[12], c[13], k);
+    model_d_moments(rho, p, Fx, Fy, Fz, c[6], c[7], c[8], c[9], c[10], c[11], k);
   const Pops<S> dst(dst_, plane);
   PopWriter<S> w(dst, B, node);
   w.set_fraction(c[0], c[1]);
   emit_recoloured(B, k, c[2], c[3], c[4], div_refined(c[0], rho, irho), div_refined(c[1], rho, irho),
-                  p, c[14], c[15], c[16], w);
+                  p, c[12], c[13], c[14], w);
   if (S::kExact) {
     // mass-exact storage: the rest populations closed on the FP64 densities
     const double *r64 = compact_rho64(const_cast<float *>(cst), cplane);

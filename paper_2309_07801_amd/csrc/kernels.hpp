@@ -2155,6 +2155,51 @@ struct CPullGeom {
   static_assert(NT % 64 == 0, "whole wavefronts");
 };
 
+// The 1D map of cm_to_pop_1d for triplets whose moments m0, m1 or m2 are zero
+// (Z0, Z1, Z2), with the terms of the zero ones left out: the same values (but
+// for the sign of a zero).
+template <bool Z0, bool Z1, bool Z2>
+__device__ __forceinline__ void cm_map(float m0, float m1, float m2, float u, float &fm, float &f0,
+                                       float &fp) {
+  if constexpr (Z0 && Z1 && Z2) {
+    fm = f0 = fp = 0.f;
+  } else {
+    const float M1 = Z0 ? m1 : (Z1 ? u * m0 : fmaf(u, m0, m1));
+    const float in = Z0 ? 2.0f * m1 : (Z1 ? M1 : fmaf(u, m0, 2.0f * m1));
+    const float M2 = Z2 ? u * in : fmaf(u, in, m2);
+    f0 = Z0 ? -M2 : m0 - M2;
+    fp = 0.5f * (M2 + M1);
+    fm = 0.5f * (M2 - M1);
+  }
+}
+// z pass of the back-transform of a compact state with no force and no normal
+// (the bulk of a box without body forces): every odd central moment above
+// second order is zero there, and so are k_211 and k_121 (Eqs. 66-67), which
+// leaves g[1][2] and g[2][1] zero.
+__device__ __forceinline__ void bulk_z_pass(float rho, float p, const float (&c)[kCompact],
+                                            float (&g)[3][3][3]) {
+  const float p3 = p * kCs2, p9 = p * kCs4, uz = c[4];
+#define Z_(a, b, Z0, Z1, Z2, m0, m1, m2) \
+  cm_map<Z0, Z1, Z2>(m0, m1, m2, uz, g[a][b][0], g[a][b][1], g[a][b][2])
+  Z_(0, 0, false, true, false, rho, 0.f, c[8]);
+  Z_(1, 0, true, false, true, 0.f, c[10], 0.f);
+  Z_(0, 1, true, false, true, 0.f, c[11], 0.f);
+  Z_(2, 0, false, true, false, c[6], 0.f, p3);
+  Z_(0, 2, false, true, false, c[7], 0.f, p3);
+  Z_(1, 1, false, true, true, c[9], 0.f, 0.f);
+  Z_(2, 2, false, true, false, p3, 0.f, p9);
+  Z_(1, 2, true, true, true, 0.f, 0.f, 0.f);
+  Z_(2, 1, true, true, true, 0.f, 0.f, 0.f);
+#undef Z_
+}
+// One outer output of the 1D map: f_+ (sg = 1) or f_- (sg = -1), the value
+// cm_to_pop_1d gives.
+__device__ __forceinline__ float cm_side(float m0, float m1, float m2, float u, float sg) {
+  const float M1 = fmaf(u, m0, m1);
+  const float M2 = fmaf(u, fmaf(u, m0, 2.0f * m1), m2);
+  return 0.5f * fmaf(sg, M1, M2);
+}
+
 template <class G, bool WALLS = false, class S = StoreF32, bool GENERAL = false>
 __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
@@ -2190,8 +2235,8 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
   uint32_t roff[G::CP];
   int rgx[G::CP], rgy[G::CP], rls[G::CP];
   // a halo point's one c_y row (above or below the tile) or c_x column
-  // (beside it) that reaches the tile: c = +1 (true) or -1
-  bool rfwd = false;
+  // (beside it) that reaches the tile: c = +1 or -1
+  float sg = 1.f;
   const int wave0 = (int)__builtin_amdgcn_readfirstlane(tid);
   const bool rowwave = wave0 < rows_end, halowave = wave0 < halo_end;
   const bool has[G::CP] = {tid < TW * TH, tid < 2 * TW || (tid >= rows_end && tid < halo_end)};
@@ -2212,12 +2257,15 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
         ly = h2 >> 1;
       }
     }
-    if (k > 0) rfwd = rowwave ? ly == 0 : lx == 0;
+    if (k > 0) sg = (rowwave ? ly == 0 : lx == 0) ? 1.f : -1.f;
     rls[k] = lx + R1X * ly;
     rgx[k] = wrap_any(x0 + lx - 1, nx);
     rgy[k] = wrap_any(y0 + ly - 1, ny);
     roff[k] = (uint32_t)rgx[k] + row * (uint32_t)rgy[k];
   }
+  // LDS slot of the first direction a halo point sends (row c_y = sg, or
+  // column c_x = sg, of the nine)
+  const int hslot = rls[1] + (sg > 0.f ? (rowwave ? 12 : 4) * G::R1 : 0);
   // the column node lies in the box (not past its last column or row)
   const bool in_xy = has[0] && rgx[0] >= x0 && rgy[0] >= y0;
   // moments of slabs s-1, s, s+1 at the column node; those of s+1 begin with
@@ -2232,19 +2280,30 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
 #pragma unroll
   for (int a = 0; a < 2; ++a) acc64[a][0] = acc64[a][1] = 0.0;
 
-  // hs of this thread's ring points, one slab ahead: its mark decides whether
-  // the normals are loaded at all
-  float hs_next[G::CP];
-  auto load_hs = [&](int s, int64_t pl) {
+  // One slab ahead: hs of the column node, whose mark decides whether its
+  // normal is loaded at all, and the whole state (but the normal) of the halo
+  // point.  A halo wavefront transforms two points a slab and the others wait
+  // for it at the barrier: with its halo point at hand it starts at once, and
+  // the column node's loads pass behind that (256^3: 420 -> 403 us).  Not with
+  // the FP64 sums of the mass-exact formats, which leave no registers for it
+  // (150 -> 171 us at 160^3): there the mark alone.
+  constexpr bool kAhead = !EXACT;
+  float hs_next, c1[kCompact];
+  auto load_ahead = [&](int s, int64_t pl) {
     const uint32_t zoff = base + nxy * (uint32_t)wrap_any(s, nz);
+    hs_next = ldpl(cst, pl, kHs, zoff + roff[0]);
 #pragma unroll
-    for (int k = 0; k < G::CP; ++k) {
+    for (int m = 0; m < kCompactN; ++m) {
+      if (!kAhead && m != kHs) continue;
       float v = 0.f;
-      if (k == 0 || halowave) v = ldpl(cst, pl, kHs, zoff + roff[k]);
-      hs_next[k] = v;
+      if (halowave) v = ldpl(cst, pl, m, zoff + roff[1]);
+      c1[m] = v;
     }
   };
-  load_hs(z0 - 1, plane_arg);
+  load_ahead(z0 - 1, plane_arg);
+  // no body force and no buoyancy: a node without a normal has no force
+  const bool quiet = !GENERAL && B.Gx == 0.f && B.Gy == 0.f && B.Gz == 0.f && B.bgx == 0.f &&
+                     B.bgy == 0.f && B.bgz == 0.f;
 
   for (int s = z0 - 1; s <= z1; ++s) {
     const int64_t plane = opaque_i64(plane_arg);
@@ -2265,156 +2324,227 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
       own_r = buf_ld_f64(plane_rsrc(r64, plane * 8, 0), (zoff + roff[0]) * 8u);
       own_b = buf_ld_f64(plane_rsrc(r64, plane * 8, 1), (zoff + roff[0]) * 8u);
     }
-    float h[G::CP][3][3][3];
-    float pux[G::CP], pcr[G::CP], pcb[G::CP], pRx[G::CP], pRy[G::CP], pRz[G::CP];
-#pragma unroll
-    for (int k = 0; k < G::CP; ++k) {
-      if (k > 0 && !halowave) {
-        // (defined values here keep the register use of the others down)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int cy = 0; cy < 3; ++cy)
-#pragma unroll
-            for (int cz = 0; cz < 3; ++cz) h[k][a][cy][cz] = 0.f;
-        pux[k] = pcr[k] = pcb[k] = pRx[k] = pRy[k] = pRz[k] = 0.f;
-        continue;
-      }
-      float c[kCompact];
-      c[kHs] = hs_next[k];
-#pragma unroll
-      for (int m = 0; m < kCompactN; ++m)
-        if (m != kHs) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
+    // The compact state of ring point k and the z pass of its back-transform.
+    struct Post {
+      float g[3][3][3];
+      float ux, uy, cr, cb, Rx, Ry, Rz;
+    };
+    // bulk: the wavefront's nodes have no normal and no force
+    auto load_n = [&](int k, float (&c)[kCompact]) __attribute__((always_inline)) {
       c[12] = c[13] = c[14] = 0.f;
       if (!hs_flat(c[kHs])) {
 #pragma unroll
         for (int m = kCompactN; m < kCompact; ++m) c[m] = ldpl(cst, plane, m, zoff + roff[k]);
       }
-      CompactPost o;
-      compact_post<GENERAL>(B, c, o);
-      float g[3][3][3];
+    };
+    auto post = [&](const float (&c)[kCompact], Post &o, bool &bulk) __attribute__((always_inline)) {
+      bulk = quiet && __all(hs_flat(c[kHs]));
+      o.ux = c[2];
+      o.uy = c[3];
+      if (bulk) {
+        const float rho = c[0] + c[1], irho = rcp(rho);
+        o.cr = div_refined(c[0], rho, irho);
+        o.cb = div_refined(c[1], rho, irho);
+        o.Rx = o.Ry = o.Rz = 0.f;
+        bulk_z_pass(rho, c[0] * B.cs2r + c[1] * B.cs2b, c, o.g);
+        return;
+      }
+      CompactPost q;
+      compact_post<GENERAL>(B, c, q);
+      o.cr = q.cr;
+      o.cb = q.cb;
+      o.Rx = q.Rx;
+      o.Ry = q.Ry;
+      o.Rz = q.Rz;
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int bb = 0; bb < 3; ++bb)
-          cm_to_pop_1d(o.k[a + 3 * bb], o.k[a + 3 * bb + 9], o.k[a + 3 * bb + 18], o.uz,
-                       g[a][bb][0], g[a][bb][1], g[a][bb][2]);
+          cm_to_pop_1d(q.k[a + 3 * bb], q.k[a + 3 * bb + 9], q.k[a + 3 * bb + 18], q.uz,
+                       o.g[a][bb][0], o.g[a][bb][1], o.g[a][bb][2]);
+    };
+    // The halo point first, down to what it sends into the tile: three
+    // directions of each z component (hv[pz][j][colour]), the same values the
+    // full transform below gives.  (Finished before the column node's own
+    // transform begins, it holds 18 registers beside it instead of 33.)
+    float hv[3][3][2];
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+    for (int q = 0; q < 18; ++q) hv[q / 6][q / 2 % 3][q % 2] = 0.f;
+    float c0[kCompact];
+    c0[kHs] = hs_next;
 #pragma unroll
-        for (int cz = 0; cz < 3; ++cz)
-          cm_to_pop_1d(g[a][0][cz], g[a][1][cz], g[a][2][cz], o.uy, h[k][a][0][cz],
-                       h[k][a][1][cz], h[k][a][2][cz]);
-      pux[k] = o.ux;
-      pcr[k] = o.cr;
-      pcb[k] = o.cb;
-      pRx[k] = o.Rx;
-      pRy[k] = o.Ry;
-      pRz[k] = o.Rz;
+    for (int m = 0; m < kCompactN; ++m)
+      if (m != kHs) c0[m] = ldpl(cst, plane, m, zoff + roff[0]);
+    load_n(0, c0);
+    if (halowave) {
+      if (!kAhead) {
+#pragma unroll
+        for (int m = 0; m < kCompactN; ++m)
+          if (m != kHs) c1[m] = ldpl(cst, plane, m, zoff + roff[1]);
+      }
+      load_n(1, c1);
+      Post o;
+      bool bulk;
+      post(c1, o, bulk);
+      if (rowwave) {
+        // below (c_y = +1) or above (c_y = -1) the tile: that row, j = c_x + 1
+        const float yR = sg * o.Ry;
+#pragma unroll
+        for (int pz = 0; pz < 3; ++pz) {
+          float hr[3], fx[3];
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            hr[a] = cm_side(o.g[a][0][pz], o.g[a][1][pz], o.g[a][2][pz], o.uy, sg);
+          cm_to_pop_1d(hr[0], hr[1], hr[2], o.ux, fx[0], fx[1], fx[2]);
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const int i = dir_of(j - 1, 1, pz - 1);  // |c|, c_x, c_z as in either row
+            const float cR = (kCX[i] ? (kCX[i] > 0 ? o.Rx : -o.Rx) : 0.f) + yR +
+                             (kCZ[i] ? (kCZ[i] > 0 ? o.Rz : -o.Rz) : 0.f);
+            const float d = 3.0f * weight(i) * cR;
+            hv[pz][j][0] = fmaf(o.cr, fx[j], d);
+            hv[pz][j][1] = fmaf(o.cb, fx[j], -d);
+          }
+        }
+      } else {
+        // left (c_x = +1) or right (c_x = -1) of the tile: that column,
+        // j = c_y + 1
+        const float xR = sg * o.Rx;
+#pragma unroll
+        for (int pz = 0; pz < 3; ++pz) {
+          float hc[3][3];
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            cm_to_pop_1d(o.g[a][0][pz], o.g[a][1][pz], o.g[a][2][pz], o.uy, hc[a][0], hc[a][1],
+                         hc[a][2]);
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const float fv = cm_side(hc[0][j], hc[1][j], hc[2][j], o.ux, sg);
+            const int i = dir_of(1, j - 1, pz - 1);  // |c|, c_y, c_z as in either column
+            const float cR = xR + (kCY[i] ? (kCY[i] > 0 ? o.Ry : -o.Ry) : 0.f) +
+                             (kCZ[i] ? (kCZ[i] > 0 ? o.Rz : -o.Rz) : 0.f);
+            const float d = 3.0f * weight(i) * cR;
+            hv[pz][j][0] = fmaf(o.cr, fv, d);
+            hv[pz][j][1] = fmaf(o.cb, fv, -d);
+          }
+        }
+      }
+      if (WALLS && rsolid[1]) {
+        // a solid halo point sends what the bounce-back stored there
+        const uint32_t wslot = (uint32_t)B.wbase + wall_slot(B, rgx[1], rgy[1], gz);
+#pragma unroll
+        for (int pz = 0; pz < 3; ++pz)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const int up = rowwave ? dir_of(j - 1, 1, pz - 1) : dir_of(1, j - 1, pz - 1);
+            const int dn = rowwave ? dir_of(j - 1, -1, pz - 1) : dir_of(-1, j - 1, pz - 1);
+            typename S::T r, bl;
+            win.ld(sg > 0.f ? up : dn, wslot, r, bl);
+            hv[pz][j][0] = S::dec(r);
+            hv[pz][j][1] = S::dec(bl);
+          }
+      }
     }
-    load_hs(s + 1, plane);
+    Post own;
+    bool bulk;
+    post(c0, own, bulk);
+    load_ahead(s + 1, plane);
     // mass-exact storage: FP64 sums of the moving values the column node emits
     double emit_r = 0.0, emit_b = 0.0;
 #pragma unroll
     for (int pz = 0; pz < 3; ++pz) {
-      // the x pass and the recolouring (Eqs. 18-19) of the directions with
-      // z component pz - 1, as emit_recoloured computes them
+      // the slabs beside the chunk send into it with one z component only
+      if (s < z0 ? pz != 2 : s >= z1 && pz != 0) continue;
+      // the y and x passes and the recolouring (Eqs. 18-19) of the directions
+      // with z component pz - 1, as emit_recoloured computes them
+      if (halowave && has[1]) {
 #pragma unroll
-      for (int k = 0; k < G::CP; ++k) {
-        if ((k == 0 || halowave) && has[k]) {
-          // a solid ring point: what the bounce-back stored for these
-          // directions, loaded before the emission so that the loads'
-          // latency passes behind it
-          typename S::T stv[9][2];
-          if (WALLS && rsolid[k]) {
-            const uint32_t wslot = (uint32_t)B.wbase + wall_slot(B, rgx[k], rgy[k], gz);
+        for (int j = 0; j < 3; ++j) {
+          float *to = &xb[0][hslot] + (rowwave ? 2 * j : 6 * j) * G::R1;
+          to[0] = hv[pz][j][0];
+          to[G::R1] = hv[pz][j][1];
+        }
+      }
+      if (has[0]) {
+        // a solid column node: what the bounce-back stored for these
+        // directions, loaded before the emission so that the loads' latency
+        // passes behind it
+        typename S::T stv[9][2];
+        if (WALLS && rsolid[0]) {
+          const uint32_t wslot = (uint32_t)B.wbase + wall_slot(B, rgx[0], rgy[0], gz);
 #pragma unroll
-            for (int q = 0; q < 9; ++q) {
-              const int i = dir_of(q % 3 - 1, q / 3 - 1, pz - 1);
-              if (EXACT && i == 0) {
-                stv[q][0] = stv[q][1] = S::enc(0.f);
-              } else {
-                win.ld(i, wslot, stv[q][0], stv[q][1]);
-              }
+          for (int q = 0; q < 9; ++q) {
+            const int i = dir_of(q % 3 - 1, q / 3 - 1, pz - 1);
+            if (EXACT && i == 0) {
+              stv[q][0] = stv[q][1] = S::enc(0.f);
+            } else {
+              win.ld(i, wslot, stv[q][0], stv[q][1]);
             }
           }
-          const int slot = rls[k];
-          if (k == 0) {
-            // the column node: all nine directions
+        }
+        const int slot = rls[0];
+        float h[3][3];
+        if (bulk) {
+          // the recolouring is the split by colour fraction
+          cm_map<false, false, false>(own.g[0][0][pz], own.g[0][1][pz], own.g[0][2][pz], own.uy,
+                                      h[0][0], h[0][1], h[0][2]);
+          cm_map<false, false, true>(own.g[1][0][pz], own.g[1][1][pz], 0.f, own.uy, h[1][0],
+                                     h[1][1], h[1][2]);
+          cm_map<false, true, false>(own.g[2][0][pz], 0.f, own.g[2][2][pz], own.uy, h[2][0],
+                                     h[2][1], h[2][2]);
 #pragma unroll
-            for (int cy = 0; cy < 3; ++cy) {
-              // (the plain maps here: the doubled ones of emit_recoloured
-              // give the same bits but cost this kernel 8 VGPRs and an
-              // occupancy step)
-              float fx[3];
-              cm_to_pop_1d(h[k][0][cy][pz], h[k][1][cy][pz], h[k][2][cy][pz], pux[k], fx[0], fx[1],
-                           fx[2]);
-#pragma unroll
-              for (int cx = 0; cx < 3; ++cx) {
-                const int i = dir_of(cx - 1, cy - 1, pz - 1);
-                const float cR = (kCX[i] ? (kCX[i] > 0 ? pRx[k] : -pRx[k]) : 0.f) +
-                                 (kCY[i] ? (kCY[i] > 0 ? pRy[k] : -pRy[k]) : 0.f) +
-                                 (kCZ[i] ? (kCZ[i] > 0 ? pRz[k] : -pRz[k]) : 0.f);
-                const float d = 3.0f * weight(i) * cR;
-                const int q = 3 * cy + cx;
-                const float vr = fmaf(pcr[k], fx[cx], d), vb = fmaf(pcb[k], fx[cx], -d);
-                if (EXACT && i != 0) {
-                  emit_r += (double)vr;
-                  emit_b += (double)vb;
-                }
-                xb[2 * q][slot] = vr;
-                xb[2 * q + 1][slot] = vb;
-              }
-            }
-          } else if (rowwave) {
-            // a halo point below (c_y = +1) or above (c_y = -1) the tile:
-            // the three directions of that row, the same values as above
-            const bool fw = rfwd;
+          for (int cy = 0; cy < 3; ++cy) {
             float fx[3];
-            cm_to_pop_1d(fw ? h[k][0][2][pz] : h[k][0][0][pz], fw ? h[k][1][2][pz] : h[k][1][0][pz],
-                         fw ? h[k][2][2][pz] : h[k][2][0][pz], pux[k], fx[0], fx[1], fx[2]);
-            const float yR = fw ? pRy[k] : -pRy[k];
+            cm_to_pop_1d(h[0][cy], h[1][cy], h[2][cy], own.ux, fx[0], fx[1], fx[2]);
 #pragma unroll
             for (int cx = 0; cx < 3; ++cx) {
-              const int i = dir_of(cx - 1, 1, pz - 1);  // |c|, c_x, c_z as in either row
-              const float cR = (kCX[i] ? (kCX[i] > 0 ? pRx[k] : -pRx[k]) : 0.f) + yR +
-                               (kCZ[i] ? (kCZ[i] > 0 ? pRz[k] : -pRz[k]) : 0.f);
-              const float d = 3.0f * weight(i) * cR;
-              const int q = (fw ? 6 : 0) + cx;
-              xb[2 * q][slot] = fmaf(pcr[k], fx[cx], d);
-              xb[2 * q + 1][slot] = fmaf(pcb[k], fx[cx], -d);
-            }
-          } else {
-            // a halo point left (c_x = +1) or right (c_x = -1) of the tile:
-            // the three directions of that column
-            const bool fw = rfwd;
-            const float xR = fw ? pRx[k] : -pRx[k];
-#pragma unroll
-            for (int cy = 0; cy < 3; ++cy) {
-              float fx[3];
-              cm_to_pop_1d(h[k][0][cy][pz], h[k][1][cy][pz], h[k][2][cy][pz], pux[k], fx[0], fx[1],
-                           fx[2]);
-              const float fv = fw ? fx[2] : fx[0];
-              const int i = dir_of(1, cy - 1, pz - 1);  // |c|, c_y, c_z as in either column
-              const float cR = xR + (kCY[i] ? (kCY[i] > 0 ? pRy[k] : -pRy[k]) : 0.f) +
-                               (kCZ[i] ? (kCZ[i] > 0 ? pRz[k] : -pRz[k]) : 0.f);
-              const float d = 3.0f * weight(i) * cR;
-              const int q = 3 * cy + (fw ? 2 : 0);
-              xb[2 * q][slot] = fmaf(pcr[k], fv, d);
-              xb[2 * q + 1][slot] = fmaf(pcb[k], fv, -d);
+              const int q = 3 * cy + cx;
+              const float vr = own.cr * fx[cx], vb = own.cb * fx[cx];
+              if (EXACT && !(pz == 1 && q == 4)) {
+                emit_r += (double)vr;
+                emit_b += (double)vb;
+              }
+              xb[2 * q][slot] = vr;
+              xb[2 * q + 1][slot] = vb;
             }
           }
-          if (WALLS && rsolid[k]) {
-            // A solid point emits what the bounce-back stored there instead
-            // (its rest population, which only it receives, stays in the
-            // stash): one branch per point and z component, after the
-            // emission above.  (A solid column node's own sums above feed
-            // only its own moments, which are stored as zero.)
+        } else {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) {
-              xb[2 * q][slot] = S::dec(stv[q][0]);
-              xb[2 * q + 1][slot] = S::dec(stv[q][1]);
+          for (int a = 0; a < 3; ++a)
+            cm_to_pop_1d(own.g[a][0][pz], own.g[a][1][pz], own.g[a][2][pz], own.uy, h[a][0],
+                         h[a][1], h[a][2]);
+#pragma unroll
+          for (int cy = 0; cy < 3; ++cy) {
+            float fx[3];
+            cm_to_pop_1d(h[0][cy], h[1][cy], h[2][cy], own.ux, fx[0], fx[1], fx[2]);
+#pragma unroll
+            for (int cx = 0; cx < 3; ++cx) {
+              const int i = dir_of(cx - 1, cy - 1, pz - 1);
+              const float cR = (kCX[i] ? (kCX[i] > 0 ? own.Rx : -own.Rx) : 0.f) +
+                               (kCY[i] ? (kCY[i] > 0 ? own.Ry : -own.Ry) : 0.f) +
+                               (kCZ[i] ? (kCZ[i] > 0 ? own.Rz : -own.Rz) : 0.f);
+              const float d = 3.0f * weight(i) * cR;
+              const int q = 3 * cy + cx;
+              const float vr = fmaf(own.cr, fx[cx], d), vb = fmaf(own.cb, fx[cx], -d);
+              if (EXACT && i != 0) {
+                emit_r += (double)vr;
+                emit_b += (double)vb;
+              }
+              xb[2 * q][slot] = vr;
+              xb[2 * q + 1][slot] = vb;
             }
+          }
+        }
+        if (WALLS && rsolid[0]) {
+          // A solid point emits what the bounce-back stored there instead
+          // (its rest population, which only it receives, stays in the
+          // stash): one branch per z component, after the emission above.
+          // (A solid column node's own sums above feed only its own moments,
+          // which are stored as zero.)
+#pragma unroll
+          for (int q = 0; q < 9; ++q) {
+            xb[2 * q][slot] = S::dec(stv[q][0]);
+            xb[2 * q + 1][slot] = S::dec(stv[q][1]);
           }
         }
       }

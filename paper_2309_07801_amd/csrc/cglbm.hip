@@ -712,18 +712,19 @@ int launch_pull(cglbm_handle *h, hipStream_t s, int bounce) {
   return CGLBM_OK;
 }
 
-int launch_fused(cglbm_handle *h, hipStream_t s, int export_fields);
+int launch_fused(cglbm_handle *h, hipStream_t s, uint32_t need);
 
-// Interface fields of every node into aux: the tiled kernel, or from
+// Interface fields of every node into aux (those in `need` at least): the
+// tiled kernel, or from
 // kIfaceNodes nodes on the fused kernel's field export (the same bits), whose
 // columns share their halos along z.  Measured: 64x64x64 21 us against 45,
 // 97x80x113 61 against 75, 200x180x160 283 against 188.
 constexpr int64_t kIfaceNodes = 2 << 20;
-int launch_iface(cglbm_handle *h, hipStream_t s, int write_kappa) {
-  if (h->L.total >= kIfaceNodes) return launch_fused(h, s, 1);
+int launch_iface(cglbm_handle *h, hipStream_t s, uint32_t need = NEED_N | NEED_F | NEED_Q) {
+  if (h->L.total >= kIfaceNodes) return launch_fused(h, s, need);
   hipLaunchKernelGGL((k_interface<kTX, kTY, kTZ, kIfaceThreads>), dim3(h->L.ntile),
                      dim3(kIfaceThreads), 0, s, h->d_boxes, h->d_tile_box, h->aux, h->L.total,
-                     write_kappa);
+                     (int)(need & NEED_KAPPA));
   return CGLBM_OK;
 }
 
@@ -746,7 +747,7 @@ int join_side(cglbm_handle *h, hipStream_t s) {
 // dependencies).
 int launch_split(cglbm_handle *h, int32_t ncol, int32_t nplain, const FusedFn *fn, int nthreads,
                  hipStream_t s, const BoxDev *boxes, const TileEntry *cols, float *aux,
-                 void *dst, int64_t plane) {
+                 void *dst, int64_t plane, uint32_t need = 0) {
   const int32_t n[2] = {nplain, ncol - nplain};
   const bool both = (h->wmode & 2) && n[0] > 0 && n[1] > 0;
   if (both) {
@@ -756,15 +757,14 @@ int launch_split(cglbm_handle *h, int32_t ncol, int32_t nplain, const FusedFn *f
   for (int w = 1; w >= 0; --w) {
     if (n[w] <= 0) continue;
     const TileEntry *c = cols + (w ? nplain : 0);
-    void *args[] = {(void *)&boxes, (void *)&c, (void *)&aux, (void *)&dst, (void *)&plane};
+    void *args[] = {(void *)&boxes, (void *)&c, (void *)&aux, (void *)&dst, (void *)&plane,
+                    (void *)&need};
     HIP_TRY(hipLaunchKernel((const void *)fn[w], dim3((unsigned)n[w]), dim3(nthreads), args, 0,
                             (both && w) ? h->side : s));
   }
   return both ? join_side(h, s) : CGLBM_OK;
 }
 
-// export == 0: interface stencils + collision of a time step; export != 0:
-// the interface fields n, F, Q, kappa into aux, populations untouched.
 // Compact schedule: the fused kernel writes the compact state into the
 // other population buffer; k_cpull turns it into the moments of the next
 // step; k_emit stores it as populations in the state buffer.
@@ -840,16 +840,18 @@ bool compact_ok(const cglbm_handle *h) {
           (storage_exact(h->storage) && !h->L.general));
 }
 
-int launch_fused(cglbm_handle *h, hipStream_t s, int export_fields) {
+// need == 0: interface stencils + collision of a time step; else the interface
+// fields in `need` into aux, populations untouched.
+int launch_fused(cglbm_handle *h, hipStream_t s, uint32_t need) {
   const FusedVariant &F = fused_variant(h->variant);
   const BoxDev *boxes = h->d_boxes;
   const TileEntry *cols = h->d_col_tiles;
   float *aux = h->aux;
   void *dst = h->pop[1 - h->cur];
   int64_t plane = h->L.total;
-  const FusedFn *fn = export_fields ? F.k->fx : F.k->fn[h->L.ragged ? 1 : 0][h->storage];
+  const FusedFn *fn = need ? F.k->fx : F.k->fn[h->L.ragged ? 1 : 0][h->storage];
   return launch_split(h, h->L.ncol, h->L.ncol_plain, fn, F.k->nt, s, boxes, cols, aux, dst,
-                      plane);
+                      plane, need);
 }
 
 // Select fused variant v: rebuild and upload the column tables.
@@ -993,7 +995,7 @@ int launch_step(cglbm_handle *h, hipStream_t s) {
   if (effective_schedule(h) == 0) {
     if (!rc) rc = timed(h, s, KIND_FUSED, [&] { return launch_fused(h, s, 0); });
   } else {
-    if (!rc) rc = timed(h, s, KIND_IFACE, [&] { return launch_iface(h, s, 0); });
+    if (!rc) rc = timed(h, s, KIND_IFACE, [&] { return launch_iface(h, s); });
     if (!rc) rc = timed(h, s, KIND_COLLIDE, [&] { return launch_collide(h, s); });
   }
   if (!rc) rc = check_launch();
@@ -1196,7 +1198,8 @@ int capture_pair(cglbm_handle *h) {
   return CGLBM_OK;
 }
 
-int compute_fields(cglbm_handle *h, hipStream_t s, int write_kappa) {
+// need: the interface fields wanted (NEED_*; others may be written too).
+int compute_fields(cglbm_handle *h, hipStream_t s, uint32_t need) {
   if (h->clive) {
     const int rc = flush_compact(h, s);
     if (rc) return rc;
@@ -1207,10 +1210,8 @@ int compute_fields(cglbm_handle *h, hipStream_t s, int write_kappa) {
   }
   int rc = launch_pull(h, s, 0);
   if (rc) return rc;
-  if (effective_schedule(h) != 1)
-    rc = launch_fused(h, s, 1);
-  else
-    rc = launch_iface(h, s, write_kappa);
+  if (!need) return check_launch();
+  rc = effective_schedule(h) != 1 ? launch_fused(h, s, need) : launch_iface(h, s, need);
   if (rc) return rc;
   return check_launch();
 }
@@ -1237,7 +1238,7 @@ int scratch_lookup(int device) {
 // doubles per box; out: the packed CGLBM_NDIAG doubles per box, device.
 int reduce_launch(cglbm_handle *h, hipStream_t s, const double *centre, double *part,
                   double *diag, double *out) {
-  int rc = compute_fields(h, s, 0);
+  int rc = compute_fields(h, s, NEED_F);
   if (rc) return rc;
   const double *rho64 =
       storage_exact(h->storage)
@@ -1541,7 +1542,12 @@ int cglbm_moments(cglbm_handle *h, int32_t box, uint32_t field_mask, float *out_
   if (field_mask == 0 || (field_mask >> 17)) return fail(CGLBM_EINVAL, "bad field mask 0x%x", field_mask);
   if (!out_dev) return fail(CGLBM_EINVAL, "out_dev must not be NULL");
   hipStream_t s = (hipStream_t)stream;
-  int rc = compute_fields(h, s, (field_mask >> 10) & 1u);
+  // u and F take F, then n, kappa and Q by themselves
+  const uint32_t need = (field_mask & 0x3870u ? (uint32_t)NEED_F : 0u) |
+                        (field_mask & 0x380u ? (uint32_t)NEED_N : 0u) |
+                        (field_mask & 0x400u ? (uint32_t)NEED_KAPPA : 0u) |
+                        (field_mask & 0x1C000u ? (uint32_t)NEED_Q : 0u);
+  int rc = compute_fields(h, s, need);
   if (rc) return rc;
   const int64_t n = h->L.boxes[box].n;
   hipLaunchKernelGGL(k_fields, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
@@ -1747,7 +1753,7 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   if (!rc && !(rc = select_variant(h, best, s)))
     rc = time_in_step(s, reps, pull,
                       [&] {
-                        const int r = launch_iface(h, s, 0);
+                        const int r = launch_iface(h, s);
                         return r ? r : launch_collide(h, s);
                       },
                       three_ms);

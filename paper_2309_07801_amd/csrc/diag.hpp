@@ -22,34 +22,31 @@ __global__ __launch_bounds__(kBlock) void k_fields(const BoxDev *__restrict__ bo
   const int y = (int)(yz - (uint32_t)z * (uint32_t)B.ny);
   const uint32_t node = (uint32_t)(B.base + local);
   const bool solid = is_solid(B, y, z);
-  const NodeIn in = load_node_in(aux, plane, node);
-  const float rho = in.rr + in.rb;
-  const float sr = in.rr * B.ir0r, sb = in.rb * B.ir0b;
-  float v[17];
-  v[0] = in.rr;
-  v[1] = in.rb;
-  v[2] = (sr + sb) > 0.f ? (sr - sb) / (sr + sb) : 0.f;
-  v[3] = in.rr * B.cs2r + in.rb * B.cs2b;
-  v[4] = solid ? 0.f : fmaf(0.5f, in.Fx, in.jx) / rho;
-  v[5] = solid ? 0.f : fmaf(0.5f, in.Fy, in.jy) / rho;
-  v[6] = solid ? 0.f : fmaf(0.5f, in.Fz, in.jz) / rho;
-  v[7] = in.nx;
-  v[8] = in.ny;
-  v[9] = in.nz;
-  v[10] = at(PL(aux, A_KAPPA), node);
-  v[11] = in.Fx;
-  v[12] = in.Fy;
-  v[13] = in.Fz;
-  v[14] = in.Qx;
-  v[15] = in.Qy;
-  v[16] = in.Qz;
-  int slot = 0;
-  for (int k = 0; k < 17; ++k) {
-    if (mask & (1u << k)) {
-      out[(int64_t)slot * B.n + local] = v[k];
-      ++slot;
-    }
+  // only the planes the wanted fields are made of (mask is uniform): seven
+  // fields of a 192^3 box 89 -> 74 us
+  float *o = out + local;
+  auto put = [&](float v) {
+    *o = v;
+    o += B.n;
+  };
+  const float rr = ld(&at(PL(aux, A_RR), node)), rb = ld(&at(PL(aux, A_RB), node));
+  if (mask & 1u) put(rr);
+  if (mask & 2u) put(rb);
+  if (mask & 4u) {
+    const float sr = rr * B.ir0r, sb = rb * B.ir0b;
+    put((sr + sb) > 0.f ? (sr - sb) / (sr + sb) : 0.f);
   }
+  if (mask & 8u) put(rr * B.cs2r + rb * B.cs2b);
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if (mask & (0x10u << a)) {
+      const float F = ld(&at(PL(aux, A_FX + a), node)), j = ld(&at(PL(aux, A_JX + a), node));
+      put(solid ? 0.f : fmaf(0.5f, F, j) / (rr + rb));
+    }
+  constexpr int kPlane[10] = {A_NX, A_NY, A_NZ, A_KAPPA, A_FX, A_FY, A_FZ, A_QX, A_QY, A_QZ};
+#pragma unroll
+  for (int k = 0; k < 10; ++k)
+    if (mask & (0x80u << k)) put(ld(&at(PL(aux, kPlane[k]), node)));
 }
 
 // ---------------------------------------------------------------------------
@@ -111,46 +108,64 @@ __global__ __launch_bounds__(kBlock) void k_reduce1(const BoxDev *__restrict__ b
               cz = centre_of(B, centre, b, 2);
   double v[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const int64_t first = (int64_t)(blockIdx.x - (uint32_t)B.rch0) * kRedChunk + threadIdx.x;
-  for (int g = 0; g < kRedG; ++g) {
-    const int64_t local = first + (int64_t)g * kBlock;
-    if (local >= B.n) break;
-    const uint32_t l = (uint32_t)local;
-    const uint32_t yz = fdiv(l, B.fdx);
-    const int x = (int)(l - yz * (uint32_t)B.nx);
-    const int z = (int)fdiv(yz, B.fdy);
-    const int y = (int)(yz - (uint32_t)z * (uint32_t)B.ny);
-    if (is_solid(B, y, z)) continue;
-    const uint32_t node = (uint32_t)(B.base + local);
-    const NodeIn in = load_node_in(aux, plane, node);
-    const bool finite = isfinite(in.rr) && isfinite(in.rb) && isfinite(in.jx) &&
-                        isfinite(in.jy) && isfinite(in.jz) && isfinite(in.pxx) &&
-                        isfinite(in.pyy) && isfinite(in.pzz) && isfinite(in.pxy) &&
-                        isfinite(in.pxz) && isfinite(in.pyz);
-    if (!finite) {
-      v[10] += 1.0;
-      continue;
+  // kRedIn nodes' values are loaded before the first is added (in the same
+  // order): a 192^3 box has 432 blocks, too few to hide the loads one by one
+  // (102 -> 63 us)
+  constexpr int kRedIn = 4;
+  for (int g = 0; g < kRedG && first + (int64_t)g * kBlock < B.n; g += kRedIn) {
+    float in[kRedIn][14];  // rho_r, rho_b, j, Pi, F
+    double d64[kRedIn][2];
+#pragma unroll
+    for (int c = 0; c < kRedIn; ++c) {
+      const int64_t local = first + (int64_t)(g + c) * kBlock;
+      const uint32_t node = (uint32_t)(B.base + (local < B.n ? local : first));
+#pragma unroll
+      for (int k = 0; k < kMoments; ++k) in[c][k] = ld(&at(PL(aux, k), node));
+#pragma unroll
+      for (int k = 0; k < 3; ++k) in[c][kMoments + k] = ld(&at(PL(aux, A_FX + k), node));
+      d64[c][0] = rho64 ? at(rho64, node) : 0.0;
+      d64[c][1] = rho64 ? at(rho64 + plane, node) : 0.0;
     }
-    // colour densities in FP64 where the storage carries them
-    const double rr = rho64 ? at(rho64, node) : (double)in.rr;
-    const double rb = rho64 ? at(rho64 + plane, node) : (double)in.rb;
-    const double rho = rr + rb;
-    const double jx = (double)in.jx + 0.5 * in.Fx, jy = (double)in.jy + 0.5 * in.Fy,
-                 jz = (double)in.jz + 0.5 * in.Fz;
-    const float sr = in.rr * B.ir0r, sb = in.rb * B.ir0b;
-    const double phi = (sr + sb) > 0.f ? (double)((sr - sb) / (sr + sb)) : 0.0;
-    const double dx = periodic_offset(x - cx, B.nx, true);
-    const double dy = periodic_offset(y - cy, B.ny, !(B.walls & 1u));
-    const double dz = periodic_offset(z - cz, B.nz, !(B.walls & 2u));
-    v[0] += rr;
-    v[1] += rb;
-    v[2] += jx;
-    v[3] += jy;
-    v[4] += jz;
-    v[5] += 0.5 * (1.0 + phi);
-    v[6] += rr * dx;
-    v[7] += rr * dy;
-    v[8] += rr * dz;
-    v[9] += 0.5 * (jx * jx + jy * jy + jz * jz) / rho;
+#pragma unroll
+    for (int c = 0; c < kRedIn; ++c) {
+      const int64_t local = first + (int64_t)(g + c) * kBlock;
+      if (local >= B.n) break;
+      const uint32_t l = (uint32_t)local;
+      const uint32_t yz = fdiv(l, B.fdx);
+      const int x = (int)(l - yz * (uint32_t)B.nx);
+      const int z = (int)fdiv(yz, B.fdy);
+      const int y = (int)(yz - (uint32_t)z * (uint32_t)B.ny);
+      if (is_solid(B, y, z)) continue;
+      const float(&m)[14] = in[c];
+      bool finite = true;
+#pragma unroll
+      for (int k = 0; k < kMoments; ++k) finite = finite && isfinite(m[k]);
+      if (!finite) {
+        v[10] += 1.0;
+        continue;
+      }
+      // colour densities in FP64 where the storage carries them
+      const double rr = rho64 ? d64[c][0] : (double)m[0];
+      const double rb = rho64 ? d64[c][1] : (double)m[1];
+      const double rho = rr + rb;
+      const double jx = (double)m[2] + 0.5 * m[11], jy = (double)m[3] + 0.5 * m[12],
+                   jz = (double)m[4] + 0.5 * m[13];
+      const float sr = m[0] * B.ir0r, sb = m[1] * B.ir0b;
+      const double phi = (sr + sb) > 0.f ? (double)((sr - sb) / (sr + sb)) : 0.0;
+      const double dx = periodic_offset(x - cx, B.nx, true);
+      const double dy = periodic_offset(y - cy, B.ny, !(B.walls & 1u));
+      const double dz = periodic_offset(z - cz, B.nz, !(B.walls & 2u));
+      v[0] += rr;
+      v[1] += rb;
+      v[2] += jx;
+      v[3] += jy;
+      v[4] += jz;
+      v[5] += 0.5 * (1.0 + phi);
+      v[6] += rr * dx;
+      v[7] += rr * dy;
+      v[8] += rr * dz;
+      v[9] += 0.5 * (jx * jx + jy * jy + jz * jz) / rho;
+    }
   }
   block_sum_f64<11>(v, part + (int64_t)blockIdx.x * kNPart);
 }
@@ -168,29 +183,40 @@ __global__ __launch_bounds__(kBlock) void k_reduce2(const BoxDev *__restrict__ b
   double v[4] = {0, 0, 0, 0};
   const double reff = diag[(int64_t)b * kNPart + 7];
   const int64_t first = (int64_t)(blockIdx.x - (uint32_t)B.rch0) * kRedChunk + threadIdx.x;
-  for (int g = 0; g < kRedG; ++g) {
-    const int64_t local = first + (int64_t)g * kBlock;
-    if (local >= B.n) break;
-    const uint32_t l = (uint32_t)local;
-    const uint32_t yz = fdiv(l, B.fdx);
-    const int x = (int)(l - yz * (uint32_t)B.nx);
-    const int z = (int)fdiv(yz, B.fdy);
-    const int y = (int)(yz - (uint32_t)z * (uint32_t)B.ny);
-    if (is_solid(B, y, z)) continue;
-    const uint32_t node = (uint32_t)(B.base + local);
-    const double p = (double)(at(PL(aux, A_RR), node) * B.cs2r + at(PL(aux, A_RB), node) * B.cs2b);
-    const double dx = periodic_offset(x - cx, B.nx, true);
-    const double dy = periodic_offset(y - cy, B.ny, !(B.walls & 1u));
-    const double dz = periodic_offset(z - cz, B.nz, !(B.walls & 2u));
-    const double d = sqrt(dx * dx + dy * dy + dz * dz);
-    if (isfinite(p)) {
-      if (d < reff - 3.0) {
-        v[0] += p;
-        v[1] += 1.0;
-      }
-      if (d > reff + 5.0) {
-        v[2] += p;
-        v[3] += 1.0;
+  constexpr int kRedIn = 8;  // (as in k_reduce1: 53 -> 31 us)
+  for (int g = 0; g < kRedG && first + (int64_t)g * kBlock < B.n; g += kRedIn) {
+    float rr[kRedIn], rb[kRedIn];
+#pragma unroll
+    for (int c = 0; c < kRedIn; ++c) {
+      const int64_t local = first + (int64_t)(g + c) * kBlock;
+      const uint32_t node = (uint32_t)(B.base + (local < B.n ? local : first));
+      rr[c] = at(PL(aux, A_RR), node);
+      rb[c] = at(PL(aux, A_RB), node);
+    }
+#pragma unroll
+    for (int c = 0; c < kRedIn; ++c) {
+      const int64_t local = first + (int64_t)(g + c) * kBlock;
+      if (local >= B.n) break;
+      const uint32_t l = (uint32_t)local;
+      const uint32_t yz = fdiv(l, B.fdx);
+      const int x = (int)(l - yz * (uint32_t)B.nx);
+      const int z = (int)fdiv(yz, B.fdy);
+      const int y = (int)(yz - (uint32_t)z * (uint32_t)B.ny);
+      if (is_solid(B, y, z)) continue;
+      const double p = (double)(rr[c] * B.cs2r + rb[c] * B.cs2b);
+      const double dx = periodic_offset(x - cx, B.nx, true);
+      const double dy = periodic_offset(y - cy, B.ny, !(B.walls & 1u));
+      const double dz = periodic_offset(z - cz, B.nz, !(B.walls & 2u));
+      const double d = sqrt(dx * dx + dy * dy + dz * dz);
+      if (isfinite(p)) {
+        if (d < reff - 3.0) {
+          v[0] += p;
+          v[1] += 1.0;
+        }
+        if (d > reff + 5.0) {
+          v[2] += p;
+          v[3] += 1.0;
+        }
       }
     }
   }

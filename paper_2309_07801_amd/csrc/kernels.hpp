@@ -1599,13 +1599,15 @@ struct FusedGeom {
 
 // COMPACT: store each node's compact post-collision state (see compact_of)
 // instead of its populations.  PLAIN: population
-// stores without the streaming hint.
+// stores without the streaming hint.  EXPORT: the interface fields in `need`
+// (bits NEED_*) into aux, the others left as they are.
+enum { NEED_N = 1, NEED_F = 2, NEED_Q = 4, NEED_KAPPA = 8 };
 template <class G, int MINW, bool WALLS, class S, bool EXPORT, bool COMPACT = false,
           bool PLAIN = false>
 __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict__ boxes,
                                                   const TileEntry *__restrict__ tiles,
                                                   float *__restrict__ aux,
-                                                  void *__restrict__ dst_, int64_t plane_arg) {
+                                                  void *__restrict__ dst_, int64_t plane_arg, uint32_t need) {
   constexpr int NT = G::NT;
   __shared__ float s_phi[3][G::R3];
   __shared__ float s_n[3][4][G::R2];
@@ -1907,7 +1909,8 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       const int sc = s - 2;
       const bool sz_m = slab_solid(sc - 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc + 1);
       // (the exported curvature is wanted next to the interface too)
-      const bool flat = EXPORT ? n_zero == 7u : ((n_zero >> ((uint32_t)(sc + 3) % 3u)) & 1u) != 0u;
+      const bool curv = EXPORT && (need & NEED_KAPPA) != 0u;
+      const bool flat = curv ? n_zero == 7u : ((n_zero >> ((uint32_t)(sc + 3) % 3u)) & 1u) != 0u;
       float(*nm)[G::R2] = s_n[(sc - 1 + 3) % 3];
       float(*nc)[G::R2] = s_n[(sc + 3) % 3];
       float(*np)[G::R2] = s_n[(sc + 1 + 3) % 3];
@@ -1929,7 +1932,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
         const bool fluid = !(row_bit(10 + 3 * kk) | sz_c);
         // a wavefront whose nodes all have |grad phi| = 0 has no force from
         // the curvature, whatever it is
-        if (!flat && (EXPORT || __any(mag != 0.f))) {
+        if (!flat && (curv || __any(mag != 0.f))) {
           if (fluid) {
             float d[3][3];  // d[a][b] = d n_a / d x_b
 #pragma unroll
@@ -2015,35 +2018,37 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       const int c1 = c_ri[0];
       // d q_x / dx: pairs along x over (dy, dz); likewise y and z
       float Qx = 0.f, Qy = 0.f, Qz = 0.f;
+      if (!EXPORT || (need & NEED_Q)) {
 #pragma unroll
-      for (int a2 = -1; a2 <= 1; ++a2)
+        for (int a2 = -1; a2 <= 1; ++a2)
 #pragma unroll
-        for (int b2 = -1; b2 <= 1; ++b2) {
-          const float w = 0.5f * w1d(a2) * w1d(b2);
-          {  // x: a2 = dy, b2 = dz
-            const float *pl = b2 < 0 ? qm[0] : (b2 > 0 ? qp[0] : qc[0]);
-            const bool sdd = (b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false)) | row_bit(10 + a2);
-            const float vc = qc[0][c1];
-            const float vp = wall_rule(sdd, vc, pl[c1 + 1 + R1X * a2]);
-            const float vm = wall_rule(sdd, vc, pl[c1 - 1 + R1X * a2]);
-            Qx = fmaf(w, vp - vm, Qx);
+          for (int b2 = -1; b2 <= 1; ++b2) {
+            const float w = 0.5f * w1d(a2) * w1d(b2);
+            {  // x: a2 = dy, b2 = dz
+              const float *pl = b2 < 0 ? qm[0] : (b2 > 0 ? qp[0] : qc[0]);
+              const bool sdd = (b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false)) | row_bit(10 + a2);
+              const float vc = qc[0][c1];
+              const float vp = wall_rule(sdd, vc, pl[c1 + 1 + R1X * a2]);
+              const float vm = wall_rule(sdd, vc, pl[c1 - 1 + R1X * a2]);
+              Qx = fmaf(w, vp - vm, Qx);
+            }
+            {  // y: a2 = dx, b2 = dz
+              const float *pl = b2 < 0 ? qm[1] : (b2 > 0 ? qp[1] : qc[1]);
+              const bool szd = b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false);
+              const float vc = qc[1][c1];
+              const float vp = wall_rule(szd | row_bit(11), vc, pl[c1 + a2 + R1X]);
+              const float vm = wall_rule(szd | row_bit(9), vc, pl[c1 + a2 - R1X]);
+              Qy = fmaf(w, vp - vm, Qy);
+            }
+            {  // z: a2 = dx, b2 = dy
+              const bool syd = row_bit(10 + b2);
+              const float vc = qc[2][c1];
+              const float vp = wall_rule(sz_p | syd, vc, qp[2][c1 + a2 + R1X * b2]);
+              const float vm = wall_rule(sz_m | syd, vc, qm[2][c1 + a2 + R1X * b2]);
+              Qz = fmaf(w, vp - vm, Qz);
+            }
           }
-          {  // y: a2 = dx, b2 = dz
-            const float *pl = b2 < 0 ? qm[1] : (b2 > 0 ? qp[1] : qc[1]);
-            const bool szd = b2 < 0 ? sz_m : (b2 > 0 ? sz_p : false);
-            const float vc = qc[1][c1];
-            const float vp = wall_rule(szd | row_bit(11), vc, pl[c1 + a2 + R1X]);
-            const float vm = wall_rule(szd | row_bit(9), vc, pl[c1 + a2 - R1X]);
-            Qy = fmaf(w, vp - vm, Qy);
-          }
-          {  // z: a2 = dx, b2 = dy
-            const bool syd = row_bit(10 + b2);
-            const float vc = qc[2][c1];
-            const float vp = wall_rule(sz_p | syd, vc, qp[2][c1 + a2 + R1X * b2]);
-            const float vm = wall_rule(sz_m | syd, vc, qm[2][c1 + a2 + R1X * b2]);
-            Qz = fmaf(w, vp - vm, Qz);
-          }
-        }
+      }
       Qx *= -3.0f;
       Qy *= -3.0f;
       Qz *= -3.0f;
@@ -2094,10 +2099,12 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       } else {
         // interface fields of every node of the box (zero at solid nodes)
         const uint32_t off = boff<float>(in_xy, node);
+        const uint32_t offs[4] = {need & NEED_N ? off : kDrop, need & NEED_F ? off : kDrop,
+                                  need & NEED_Q ? off : kDrop, need & NEED_KAPPA ? off : kDrop};
         const float v[10] = {h_nx, h_ny, h_nz, Fx, Fy, Fz, Qx, Qy, Qz, h_k};
 #pragma unroll
         for (int k = 0; k < 10; ++k)
-          buf_st(fluid ? v[k] : 0.f, plane_rsrc(aux, plane * 4, A_NX + k), off);
+          buf_st(fluid ? v[k] : 0.f, plane_rsrc(aux, plane * 4, A_NX + k), offs[k / 3]);
       }
     }
     // the interface values of slab s-2 become those of the next collision

@@ -17,7 +17,7 @@ namespace cglbm {
 // box), longest z chunk, minimum waves per SIMD requested from the register
 // allocator.  Every variant performs the same arithmetic per node (results
 // are bitwise equal); cglbm_autotune picks the fastest for the boxes at hand.
-using FusedFn = void (*)(const BoxDev *, const TileEntry *, float *, void *, int64_t);
+using FusedFn = void (*)(const BoxDev *, const TileEntry *, float *, void *, int64_t, uint32_t);
 struct FusedKernels {
   int nt, r3, r2, r1;  // threads; points of the tile + 3, + 2 and + 1 its LDS arrays hold
   // time step: [streaming stores, plain ones][storage][0: tiles away from

@@ -3,14 +3,12 @@ field is +1 or -1 throughout skip the interface stencils.  Pure and mixed
 ones meet in every order along the march: layers one to five slabs thick, a
 droplet smaller than a tile, no second phase at all, a perturbed bulk, with
 and without walls.  The two kernels, which skip by different regions, give
-the same bits in every exported field, and the update stays within the FP32
-bars of the oracle, which forms every stencil."""
+the same bits in every exported field and state."""
 import numpy as np
 import pytest
 
 import paper_2309_07801_amd as pkg
 import workloads as WL
-from _common import check, errors, gpu_fields, run_oracle, u_ref
 
 pytestmark = pytest.mark.gpu
 
@@ -53,21 +51,6 @@ def test_skipped_stencils_change_no_bit(kind, walls):
         sim.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b)
-
-
-@pytest.mark.parametrize("schedule", [0, 1, 2])
-@pytest.mark.parametrize("walls", [0, 3])
-@pytest.mark.parametrize("kind", ["layers", "speck", "trace"])
-def test_skipped_stencils_against_the_oracle(kind, walls, schedule):
-    box = WL.two_phase_box((43, 22, 38), 10.0, 1.0, 0.7, 0.02, 0.7, walls=walls)
-    rr, rb, u = _fields(kind, box)
-    sim = pkg.Simulation([pkg.box_params_of(box)], [rr], [rb], [u], seed=2, noise=1e-5)
-    sim.set_schedule(schedule)
-    sim.step(4)
-    got = gpu_fields(sim)
-    sim.close()
-    want, _ = run_oracle(box, rr, rb, u, 4, seed=2, noise=1e-5)
-    check(errors(got, want, box, u_ref(box, 0.02)), ctx=(kind, walls, schedule))
 
 
 def test_field_export_serves_large_boxes_in_the_three_kernel_schedule():

@@ -379,7 +379,9 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
     if (P.walls) L.walls = true;
   }
   // words of the population planes: a float, or a colour pair
-  const int64_t word = storage == CGLBM_FP32 ? 4 : 2 * (int64_t)storage_bytes(storage);
+  const int64_t word = storage == CGLBM_FP32 && lattice == LATTICE_D3Q27
+                           ? 4
+                           : 2 * (int64_t)storage_bytes(storage);
   int64_t ragged = 0, nodes = 0;
   for (const BoxDev &B : L.boxes) {
     nodes += B.n;
@@ -977,7 +979,7 @@ int effective_schedule(const cglbm_handle *h) {
 int launch_step2(cglbm_handle *h, hipStream_t s, int export_fields) {
   const Variant2 &V = variant2(h->variant);
   const int slot = storage2_slot(h->storage);
-  hipLaunchKernelGGL(export_fields ? V.fields[slot] : V.step[slot], dim3(h->L.ncol), dim3(256), 0,
+  hipLaunchKernelGGL(export_fields ? V.fields[slot] : V.step[h->L.ragged ? 1 : 0][slot], dim3(h->L.ncol), dim3(256), 0,
                      s, h->d_boxes, h->d_col_box, (const void *)h->pop[h->cur],
                      h->pop[1 - h->cur], h->aux, h->L.total);
   return CGLBM_OK;

@@ -103,7 +103,8 @@ inline const CPullVariant &cpull_variant(int v) {
 using Step2Fn = void (*)(const BoxDev *, const int32_t *, const void *, void *, float *, int64_t);
 struct Variant2 {
   int tx, ty;
-  Step2Fn step[4], fields[4];
+  Step2Fn step[2][4];  // [streaming stores, plain ones][storage slot]
+  Step2Fn fields[4];
 };
 extern const Variant2 kVariants2Table[4];
 constexpr int kNumVariants2 = 4;

@@ -68,3 +68,27 @@ def test_padded_rows_of_the_compact_arrays(nx, storage):
         out.append(_state(sim))
         sim.close()
     assert np.array_equal(*out)
+
+
+@pytest.mark.parametrize("storage", [pkg.FP32, pkg.FP32_EXACT, pkg.FP16_SHIFT])
+def test_d2q9_rows_of_whole_lines_and_ragged_ones(storage):
+    """The D2Q9 step stores with the streaming hint where a row of stored words
+    is whole cache lines and plainly elsewhere: a field that is uniform in x
+    evolves alike, bit for bit, in boxes of 64 and of 77 columns."""
+    out = []
+    for nx in (64, 77):
+        ny = 41
+        box = WL.Box(nx=nx, ny=ny, nz=1, rho0_r=10.0, rho0_b=1.0, alpha_r=WL.alpha_heavy_2d(10.0),
+                     alpha_b=WL.ALPHA_LIGHT_2D, nu_r=0.1, nu_b=0.1, sigma=0.01, beta=0.7)
+        red = np.zeros(box.shape, bool)
+        red[:, 9:24] = True
+        u = np.zeros((3,) + box.shape, np.float32)
+        u[0], u[1] = 0.03, 0.01 * np.sin(2 * np.pi * np.arange(ny) / ny)[None, :, None]
+        sim = pkg.Simulation([pkg.box_params_of(box)], [np.where(red, 10.0, 0.0)],
+                             [np.where(red, 0.0, 1.0)], [u], storage=storage, lattice="d2q9")
+        sim.step(5)
+        f = sim.moments(0, ("rho_r", "rho_b", "ux", "uy"))
+        out.append({k: v.cpu().numpy()[0, :, :64] for k, v in f.items()})
+        sim.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k

@@ -128,13 +128,16 @@ const EmitFn kEmitX[7] = {nullptr,
 // the compact schedule of the 16-bit formats: the first pull writes the
 // solid nodes' reversed populations decoded into a mass-exact FP32 stash,
 // and the call's end encodes the last stash into the stored format
-const PullFn kPullDec[7] = {nullptr,
-                            k_pull<StoreF16, true, StoreF32X>,
-                            k_pull<StoreBF16, true, StoreF32X>,
-                            nullptr,
-                            nullptr,
-                            k_pull<StoreF16C, true, StoreF32X>,
-                            k_pull<StoreBF16C, true, StoreF32X>};
+// [stash][storage]: the first pull of a compact call
+const PullFn kPullFirst[2][7] = {
+    {k_pull<StoreF32, false, StoreF32, true>, k_pull<StoreF16, false, StoreF16, true>,
+     k_pull<StoreBF16, false, StoreBF16, true>, k_pull<StoreF32X, false, StoreF32X, true>,
+     k_pull<StoreF32P, false, StoreF32P, true>, k_pull<StoreF16C, false, StoreF16C, true>,
+     k_pull<StoreBF16C, false, StoreBF16C, true>},
+    {k_pull<StoreF32, true, StoreF32, true>, k_pull<StoreF16, true, StoreF32X, true>,
+     k_pull<StoreBF16, true, StoreF32X, true>, k_pull<StoreF32X, true, StoreF32X, true>,
+     k_pull<StoreF32P, true, StoreF32P, true>, k_pull<StoreF16C, true, StoreF32X, true>,
+     k_pull<StoreBF16C, true, StoreF32X, true>}};
 const WallCopyFn kWallEncode[7] = {nullptr,
                                    k_wall_encode<StoreF16>,
                                    k_wall_encode<StoreBF16>,
@@ -824,9 +827,7 @@ int launch_emit(cglbm_handle *h, hipStream_t s, int wi = 0) {
 // mass-exact FP32 format for the 16-bit storages).
 int launch_pull_compact(cglbm_handle *h, hipStream_t s) {
   void *stash = h->L.walls ? h->cstash[0] : nullptr;
-  hipLaunchKernelGGL(stash && storage_16bit(h->storage) ? kPullDec[h->storage]
-                                                        : kPull[stash ? 1 : 0][h->storage],
-                     dim3(h->L.nblk_pad), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(kPullFirst[stash ? 1 : 0][h->storage], dim3(h->L.nblk_pad), dim3(kBlock), 0, s,
                      h->d_boxes, h->d_blk_box, h->pop[h->cur], h->pop[1 - h->cur], h->aux,
                      h->L.total, 1, stash, h->L.wtotal, h->L.ctotal);
   return CGLBM_OK;

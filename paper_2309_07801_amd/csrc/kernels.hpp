@@ -563,7 +563,9 @@ struct StashBuf {
 // 16-bit formats) the mass-exact FP32 one, into which the reversed
 // populations go decoded.
 // ---------------------------------------------------------------------------
-template <class S, bool STASH, class SS = S>
+// PADDED: aux in the compact schedule's layout (padded rows, planes of length
+// cplane; the first step of a call).
+template <class S, bool STASH, class SS = S, bool PADDED = false>
 __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxes,
                                                  const int32_t *__restrict__ blk_box,
                                                  void *__restrict__ src_, void *__restrict__ dst_,
@@ -594,13 +596,10 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
     for (int c = 0; c < 3; ++c)
       row[a][c] = (uint32_t)B.base + (uint32_t)nx * ((uint32_t)ys[a] + (uint32_t)ny * (uint32_t)zs[c]);
   const uint32_t node = (uint32_t)(B.base + local);
-  // aux node and plane length: the compact schedule's padded rows (cplane
-  // > 0), or the layout of the populations
-  const uint32_t anode = cplane ? (uint32_t)B.pbase + (uint32_t)x +
+  const uint32_t anode = PADDED ? (uint32_t)B.pbase + (uint32_t)x +
                                       (uint32_t)B.px * ((uint32_t)y + (uint32_t)ny * (uint32_t)z)
                                 : node;
-  const int64_t aplane = cplane ? cplane : plane;
-  double *r64 = aux_rho64(aux, aplane, cplane ? kMoments : (int)A_COUNT);
+  const int64_t aplane = PADDED ? cplane : plane;
 
   typename S::T gr[kQ], gb[kQ];
   constexpr int i0 = S::kExact ? 1 : 0;
@@ -673,6 +672,7 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
 #pragma unroll
     for (int k = 0; k <= A_PYZ; ++k) at(aux + k * aplane, anode) = 0.0f;
     if (S::kExact) {
+      double *r64 = aux_rho64(aux, aplane, PADDED ? kMoments : (int)A_COUNT);
       at(r64, anode) = 0.0;
       at(r64 + aplane, anode) = 0.0;
     }
@@ -706,14 +706,27 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   if (S::kExact) {
     rr = (float)drr;
     rb = (float)drb;
+    double *r64 = aux_rho64(aux, aplane, PADDED ? kMoments : (int)A_COUNT);
     st(&at(r64, anode), drr);
     st(&at(r64 + aplane, anode), drb);
   }
   // the moments stream to the next kernel: stores with the streaming hint
   // (measured faster for both kernels than plain stores)
-  const float m[kMoments] = {rr, rb, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz};
-#pragma unroll
-  for (int k = 0; k < kMoments; ++k) st(&at(aux + k * aplane, anode), m[k]);
+  // (measured faster for both kernels than plain stores).  Written out: looped
+  // over an array of them, the kernel takes 67 registers for 60 and 510 vector
+  // instructions for 388 (addresses in 64 bits a lane), and a 256^3 pull 870 us
+  // for 790
+  st(&at(aux + A_RR * aplane, anode), rr);
+  st(&at(aux + A_RB * aplane, anode), rb);
+  st(&at(aux + A_JX * aplane, anode), jx);
+  st(&at(aux + A_JY * aplane, anode), jy);
+  st(&at(aux + A_JZ * aplane, anode), jz);
+  st(&at(aux + A_PXX * aplane, anode), pxx);
+  st(&at(aux + A_PYY * aplane, anode), pyy);
+  st(&at(aux + A_PZZ * aplane, anode), pzz);
+  st(&at(aux + A_PXY * aplane, anode), pxy);
+  st(&at(aux + A_PXZ * aplane, anode), pxz);
+  st(&at(aux + A_PYZ * aplane, anode), pyz);
 }
 
 // Strength of the CSF force (Eq. 15): half of sigma kappa |grad phi|, which
@@ -1710,9 +1723,12 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   // (its densities and momentum stay from stage C; hs with n gives F again)
   float h_nx = 0.f, h_ny = 0.f, h_nz = 0.f, h_hs = 0.f, h_k = 0.f;
   float h_m[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  // The march runs down: its slab s is the box's slab z0 + z1 - 1 - s, and the
+  // slab before it in the march the one above it.
+  auto zof = [&](int s) { return wrap_any(z0 + z1 - 1 - s, nz); };
   auto slab_solid = [&](int s) {
     if (!zwalls) return false;
-    const int gz = wrap_any(s, nz);
+    const int gz = zof(s);
     return gz == 0 || gz == nz - 1;
   };
   // Every vector memory access of the march is issued on every lane and in
@@ -1728,7 +1744,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   float pc_[C_PER][5];
   const int wave0 = (int)__builtin_amdgcn_readfirstlane(tid);
   auto load_a = [&](int sl, int64_t pl) {
-    const uint32_t zoff = base + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t zoff = base + nxy * (uint32_t)zof(sl);
 #pragma unroll
     for (int k = 0; k < G::A_PER; ++k) {
       // (assigned once, after the branch: assignments in both branches had
@@ -1744,7 +1760,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     }
   };
   auto load_c = [&](int sl, int64_t pl) {
-    const uint32_t zoff = base + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t zoff = base + nxy * (uint32_t)zof(sl);
 #pragma unroll
     for (int kk = 0; kk < C_PER; ++kk) {
       if (kk > 0 && wave0 >= ring) {
@@ -1769,7 +1785,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   double d_rr = 0.0, d_rb = 0.0;
   auto load_d = [&](int sl, int64_t pl) {
     if (EXPORT) return;
-    const uint32_t node = base + c_off[0] + nxy * (uint32_t)wrap_any(sl, nz);
+    const uint32_t node = base + c_off[0] + nxy * (uint32_t)zof(sl);
     // the second moments and FP64 densities are read by stage D only
     if (S::kExact) {
       const double *r64 = aux_rho64(aux, pl, COMPACT ? kMoments : (int)A_COUNT);
@@ -1837,10 +1853,10 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     // ---- B: grad phi and n of slab s-1 (Eqs. 17, 20) ----
     if (s - 1 >= z0 - 2) {
       const int sb = s - 1;
-      const bool sz_m = slab_solid(sb - 1), sz_c = slab_solid(sb), sz_p = slab_solid(sb + 1);
-      const float *pm = s_phi[(sb - 1 + 3) % 3];
+      const bool sz_m = slab_solid(sb + 1), sz_c = slab_solid(sb), sz_p = slab_solid(sb - 1);
+      const float *pm = s_phi[(sb + 1 + 3) % 3];
       const float *pc = s_phi[(sb + 3) % 3];
-      const float *pp = s_phi[(sb + 1 + 3) % 3];
+      const float *pp = s_phi[(sb - 1 + 3) % 3];
       const uint32_t slot = (uint32_t)(sb + 3) % 3u;
       float(*nn)[G::R2] = s_n[slot];
       const bool zero = (pure & (pure >> 2) & (pure >> 4) & 3u) != 0u;
@@ -1907,13 +1923,13 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     float f_m[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
     if (s - 2 >= z0 - 1) {
       const int sc = s - 2;
-      const bool sz_m = slab_solid(sc - 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc + 1);
+      const bool sz_m = slab_solid(sc + 1), sz_c = slab_solid(sc), sz_p = slab_solid(sc - 1);
       // (the exported curvature is wanted next to the interface too)
       const bool curv = EXPORT && (need & NEED_KAPPA) != 0u;
       const bool flat = curv ? n_zero == 7u : ((n_zero >> ((uint32_t)(sc + 3) % 3u)) & 1u) != 0u;
-      float(*nm)[G::R2] = s_n[(sc - 1 + 3) % 3];
+      float(*nm)[G::R2] = s_n[(sc + 1 + 3) % 3];
       float(*nc)[G::R2] = s_n[(sc + 3) % 3];
-      float(*np)[G::R2] = s_n[(sc + 1 + 3) % 3];
+      float(*np)[G::R2] = s_n[(sc - 1 + 3) % 3];
       float(*qq)[G::R1] = s_q[(sc + 3) % 3];
       // first pass: the tile points in thread order, then the halo ring
 #pragma unroll
@@ -2010,11 +2026,11 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     // Runs on every lane; only lanes of a fluid node of the box store.
     if constexpr (kD) {
       const int sd = s - 3;
-      const bool sz_m = slab_solid(sd - 1), sz_p = slab_solid(sd + 1);
+      const bool sz_m = slab_solid(sd + 1), sz_p = slab_solid(sd - 1);
       const bool fluid = in_xy && !(row_bit(10) || slab_solid(sd));
-      float(*qm)[G::R1] = s_q[(sd + 2) % 3];
+      float(*qm)[G::R1] = s_q[(sd + 4) % 3];
       float(*qc)[G::R1] = s_q[(sd + 3) % 3];
-      float(*qp)[G::R1] = s_q[(sd + 4) % 3];
+      float(*qp)[G::R1] = s_q[(sd + 2) % 3];
       const int c1 = c_ri[0];
       // d q_x / dx: pairs along x over (dy, dz); likewise y and z
       float Qx = 0.f, Qy = 0.f, Qz = 0.f;
@@ -2052,7 +2068,7 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
       Qx *= -3.0f;
       Qy *= -3.0f;
       Qz *= -3.0f;
-      const uint32_t node = base + c_off[0] + nxy * (uint32_t)wrap_any(sd, nz);
+      const uint32_t node = base + c_off[0] + nxy * (uint32_t)zof(sd);
       float Fx, Fy, Fz;
       node_force(B, h_hs, h_nx, h_ny, h_nz, h_m[0] + h_m[1], Fx, Fy, Fz);
       if (!EXPORT) {

@@ -1805,16 +1805,12 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     };
     int32_t mbest = cmp ? h->wmode_compact : h->wmode_pop;
     double mbest_ms = 1e300;
-    for (int32_t m = 0; m < 4 && !rc; ++m) {
-      double ms = 0.0;
-      if ((rc = select_mode(h, cmp ? cfbest : best, m, s)) ||
-          (rc = time_graph(h, s, reps, e0, e1, launch, ms)))
-        break;
-      if (ms < mbest_ms) {
-        mbest_ms = ms;
-        mbest = m;
-      }
-    }
+    rc = fastest(4,
+                 [&](int m, double &ms) {
+                   const int r = select_mode(h, cmp ? cfbest : best, m, s);
+                   return r ? r : time_graph(h, s, reps, e0, e1, launch, ms);
+                 },
+                 nullptr, mbest, mbest_ms);
     (cmp ? h->wmode_compact : h->wmode_pop) = mbest;
   }
   (void)hipEventDestroy(e0);

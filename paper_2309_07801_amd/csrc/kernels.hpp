@@ -711,22 +711,32 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
     st(&at(r64 + aplane, anode), drb);
   }
   // the moments stream to the next kernel: stores with the streaming hint
-  // (measured faster for both kernels than plain stores)
   // (measured faster for both kernels than plain stores).  Written out: looped
   // over an array of them, the kernel takes 67 registers for 60 and 510 vector
   // instructions for 388 (addresses in 64 bits a lane), and a 256^3 pull 870 us
-  // for 790
-  st(&at(aux + A_RR * aplane, anode), rr);
-  st(&at(aux + A_RB * aplane, anode), rb);
-  st(&at(aux + A_JX * aplane, anode), jx);
-  st(&at(aux + A_JY * aplane, anode), jy);
-  st(&at(aux + A_JZ * aplane, anode), jz);
-  st(&at(aux + A_PXX * aplane, anode), pxx);
-  st(&at(aux + A_PYY * aplane, anode), pyy);
-  st(&at(aux + A_PZZ * aplane, anode), pzz);
-  st(&at(aux + A_PXY * aplane, anode), pxy);
-  st(&at(aux + A_PXZ * aplane, anode), pxz);
-  st(&at(aux + A_PYZ * aplane, anode), pyz);
+  // for 790.  Into padded rows a wave's stores start inside a cache line: plain
+  // stores let L2 join it (first pull of 190x131x150 nodes in 16 bits
+  // 166 -> 135 us; rows that need no pad keep the hint: 256^3 808 us, 880 plain)
+  const auto emit = [&](auto &&put) {
+    put(&at(aux + A_RR * aplane, anode), rr);
+    put(&at(aux + A_RB * aplane, anode), rb);
+    put(&at(aux + A_JX * aplane, anode), jx);
+    put(&at(aux + A_JY * aplane, anode), jy);
+    put(&at(aux + A_JZ * aplane, anode), jz);
+    put(&at(aux + A_PXX * aplane, anode), pxx);
+    put(&at(aux + A_PYY * aplane, anode), pyy);
+    put(&at(aux + A_PZZ * aplane, anode), pzz);
+    put(&at(aux + A_PXY * aplane, anode), pxy);
+    put(&at(aux + A_PXZ * aplane, anode), pxz);
+    put(&at(aux + A_PYZ * aplane, anode), pyz);
+  };
+  if (PADDED && B.px != nx) {
+    asm volatile("");  // keeps the two forms from being merged into plain stores
+    emit([](float *p, float v) { *p = v; });
+    asm volatile("");
+  } else {
+    emit([](float *p, float v) { st(p, v); });
+  }
 }
 
 // Strength of the CSF force (Eq. 15): half of sigma kappa |grad phi|, which

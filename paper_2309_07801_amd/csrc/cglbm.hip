@@ -60,8 +60,23 @@ int fail(int code, const char *fmt, ...) {
                   __FILE__, __LINE__);                                                  \
   } while (0)
 
-constexpr int kTX = 8, kTY = 8, kTZ = 8;   // interface tile (three-kernel schedule)
-constexpr int kIfaceThreads = 1024;        // and the threads of its block
+// Tiles of k_interface (three-kernel schedule), and the threads of its block.
+// A layout takes the smallest of which all its boxes make no more than one
+// tile a CU: such a launch lasts as long as one tile's chain of loads, stencils
+// and barriers.  Beyond, a smaller tile only reads and computes more of its
+// halo.  Measured, k_interface of 8x4x4, 8x8x4 and 8x8x8 tiles: 32^3 (256, 128
+// and 64 tiles) 10.6, 11.9 and 14.2 us; 40x48x36 (540, 270, 150) 16.1, 15.3 and
+// 14.3 us; 64^3 35.7, 25.9 and 20.4 us.
+constexpr int kIfaceThreads = 1024;
+constexpr int kCUs = 256;
+using IfaceFn = void (*)(const BoxDev *, const int32_t *, float *, int64_t, int);
+struct IfaceTile {
+  int tx, ty, tz;
+  IfaceFn fn;
+};
+const IfaceTile kIfaceTiles[3] = {{8, 4, 4, k_interface<8, 4, 4, kIfaceThreads>},
+                                  {8, 8, 4, k_interface<8, 8, 4, kIfaceThreads>},
+                                  {8, 8, 8, k_interface<8, 8, 8, kIfaceThreads>}};
 
 using EmitFn = void (*)(const BoxDev *, const int32_t *, const float *, void *, int64_t, int64_t);
 constexpr int kNumFused = kNumFusedVariants;
@@ -193,6 +208,7 @@ struct Layout {
   int64_t wtotal = 0;             // wall-node slots of all boxes (stash plane length)
   int64_t total = 0;  // plane length (nodes, all boxes, aligned)
   int64_t ctotal = 0; // plane length of the compact schedule's arrays (padded rows)
+  int32_t itile = 2;  // tile of k_interface (kIfaceTiles)
   int32_t nblk = 0, ntile = 0, ncol = 0, nblk_pad = 0;
   // D3Q27: col_tiles and ccol_tiles hold first the tiles that run the kernel
   // without wall logic (ncol_plain, nccol_plain entries, padded to a
@@ -290,6 +306,15 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
   const double xi = lattice == LATTICE_D2Q9 ? kXi2 : kXi;
   int64_t off = 0;
   int32_t blk = 0, tile = 0;
+  for (L.itile = 0; L.itile < 2; ++L.itile) {
+    const IfaceTile &it = kIfaceTiles[L.itile];
+    int64_t n = 0;
+    for (int b = 0; b < n_boxes; ++b)
+      n += (((int64_t)boxes[b].nx + it.tx - 1) / it.tx) * ((boxes[b].ny + it.ty - 1) / it.ty) *
+           ((boxes[b].nz + it.tz - 1) / it.tz);
+    if (n <= kCUs) break;
+  }
+  const IfaceTile &it = kIfaceTiles[L.itile];
   for (int b = 0; b < n_boxes; ++b) {
     const cglbm_box_params &P = boxes[b];
     BoxDev B;
@@ -309,9 +334,9 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
     B.rch0 = (int32_t)L.rch_box.size();
     for (int64_t k = 0; k < (B.n + kRedChunk - 1) / kRedChunk; ++k) L.rch_box.push_back(b);
     B.tile0 = tile;
-    B.tnx = (P.nx + kTX - 1) / kTX;
-    B.tny = (P.ny + kTY - 1) / kTY;
-    const int32_t tnz = (P.nz + kTZ - 1) / kTZ;
+    B.tnx = (P.nx + it.tx - 1) / it.tx;
+    B.tny = (P.ny + it.ty - 1) / it.ty;
+    const int32_t tnz = (P.nz + it.tz - 1) / it.tz;
     const int32_t nt = B.tnx * B.tny * tnz;
     for (int32_t k = 0; k < nt; ++k) L.tile_box.push_back(b);
     tile += nt;
@@ -727,7 +752,7 @@ int launch_fused(cglbm_handle *h, hipStream_t s, uint32_t need);
 constexpr int64_t kIfaceNodes = 2 << 20;
 int launch_iface(cglbm_handle *h, hipStream_t s, uint32_t need = NEED_N | NEED_F | NEED_Q) {
   if (h->L.total >= kIfaceNodes) return launch_fused(h, s, need);
-  hipLaunchKernelGGL((k_interface<kTX, kTY, kTZ, kIfaceThreads>), dim3(h->L.ntile),
+  hipLaunchKernelGGL(kIfaceTiles[h->L.itile].fn, dim3(h->L.ntile),
                      dim3(kIfaceThreads), 0, s, h->d_boxes, h->d_tile_box, h->aux, h->L.total,
                      (int)(need & NEED_KAPPA));
   return CGLBM_OK;

@@ -805,9 +805,9 @@ __device__ __forceinline__ void lds_gradient(const float *f, int c, Solid solid,
 // Where phi is +1 (or -1) throughout the tile + 3, its gradient is exactly
 // zero there: the block skips the stencils of grad phi and n, as does a
 // wavefront whose nodes all have |grad phi| = 0 those of n (unless the
-// curvature itself is wanted).  A tile is one to eleven rounds of loads and
-// stencils in a block of 256 threads, a chain the few blocks of a small box do
-// not hide: with 1024 threads the 32^3 box takes 14 us instead of 23,
+// curvature itself is wanted).  An 8x8x8 tile is one to eleven rounds of loads
+// and stencils in a block of 256 threads, a chain the few blocks of a small
+// box do not hide: with 1024 threads the 32^3 box takes 14 us instead of 23,
 // 97x80x113 61 instead of 85 (74 with 256 threads and the skips).
 template <int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_interface(const BoxDev *__restrict__ boxes,
@@ -831,6 +831,32 @@ __global__ __launch_bounds__(NT) void k_interface(const BoxDev *__restrict__ box
   const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
 
+  // every load of the tile is issued here: phi's densities of the tile + 3,
+  // and the moments of the tile + 1 that stage 3 takes (one node a thread)
+  static_assert(G::R1 <= NT, "one node of the tile + 1 a thread");
+  constexpr int K3 = (G::R3 + NT - 1) / NT;
+  float rr3[K3], rb3[K3];
+#pragma unroll
+  for (int k = 0; k < K3; ++k) {
+    const int i = min((int)threadIdx.x + k * NT, G::R3 - 1);
+    const int lx = i % G::R3X, ly = (i / G::R3X) % G::R3Y, lz = i / (G::R3X * G::R3Y);
+    const int gx = wrap_any(x0 + lx - 3, nx), gy = wrap_any(y0 + ly - 3, ny),
+              gz = wrap_any(z0 + lz - 3, nz);
+    const uint32_t node =
+        (uint32_t)B.base + (uint32_t)gx + (uint32_t)nx * ((uint32_t)gy + (uint32_t)ny * (uint32_t)gz);
+    rr3[k] = at(PL(aux, A_RR), node);
+    rb3[k] = at(PL(aux, A_RB), node);
+  }
+  const int i1 = min((int)threadIdx.x, G::R1 - 1);
+  const int lx1 = i1 % G::R1X, ly1 = (i1 / G::R1X) % G::R1Y, lz1 = i1 / (G::R1X * G::R1Y);
+  const uint32_t node1 =
+      (uint32_t)B.base + (uint32_t)wrap_any(x0 + lx1 - 1, nx) +
+      (uint32_t)nx * ((uint32_t)wrap_any(y0 + ly1 - 1, ny) +
+                      (uint32_t)ny * (uint32_t)wrap_any(z0 + lz1 - 1, nz));
+  const float rr1 = at(PL(aux, A_RR), node1), rb1 = at(PL(aux, A_RB), node1);
+  const float jx1 = at(PL(aux, A_JX), node1), jy1 = at(PL(aux, A_JY), node1),
+              jz1 = at(PL(aux, A_JZ), node1);
+
   // solid flags of the halo rows
   for (int i = threadIdx.x; i < G::R3Y; i += NT) {
     const int gy = wrap_any(y0 + i - 3, ny);
@@ -844,15 +870,12 @@ __global__ __launch_bounds__(NT) void k_interface(const BoxDev *__restrict__ box
   __syncthreads();
   // stage 1: phi on the tile + 3 (Eq. 14)
   bool red = true, blue = true;
-  for (int i = threadIdx.x; i < G::R3; i += NT) {
-    const int lx = i % G::R3X, ly = (i / G::R3X) % G::R3Y, lz = i / (G::R3X * G::R3Y);
-    const int gx = wrap_any(x0 + lx - 3, nx), gy = wrap_any(y0 + ly - 3, ny),
-              gz = wrap_any(z0 + lz - 3, nz);
-    const uint32_t node =
-        (uint32_t)B.base + (uint32_t)gx + (uint32_t)nx * ((uint32_t)gy + (uint32_t)ny * (uint32_t)gz);
-    const float rr = at(PL(aux, A_RR), node) * B.ir0r;
-    const float rb = at(PL(aux, A_RB), node) * B.ir0b;
-    const float v = phase_field(rr, rb);
+#pragma unroll
+  for (int k = 0; k < K3; ++k) {
+    const int i = (int)threadIdx.x + k * NT;
+    if (i >= G::R3) break;
+    const int ly = (i / G::R3X) % G::R3Y, lz = i / (G::R3X * G::R3Y);
+    const float v = phase_field(rr3[k] * B.ir0r, rb3[k] * B.ir0b);
     s_phi[i] = v;
     const bool any = s_sy[ly] | s_sz[lz];  // (never used at a solid node)
     red = red && (any || v == 1.0f);
@@ -890,13 +913,10 @@ __global__ __launch_bounds__(NT) void k_interface(const BoxDev *__restrict__ box
   __syncthreads();
 
   // stage 3: grad n, kappa, F, u, q on the tile + 1 (Eqs. 11, 15, 16, 65)
-  for (int i = threadIdx.x; i < G::R1; i += NT) {
-    const int lx = i % G::R1X, ly = (i / G::R1X) % G::R1Y, lz = i / (G::R1X * G::R1Y);
+  if (threadIdx.x < G::R1) {
+    const int i = threadIdx.x, lx = lx1, ly = ly1, lz = lz1;
     const int c2 = (lx + 1) + G::R2X * ((ly + 1) + G::R2Y * (lz + 1));
-    const int gx = wrap_any(x0 + lx - 1, nx), gy = wrap_any(y0 + ly - 1, ny),
-              gz = wrap_any(z0 + lz - 1, nz);
-    const uint32_t node =
-        (uint32_t)B.base + (uint32_t)gx + (uint32_t)nx * ((uint32_t)gy + (uint32_t)ny * (uint32_t)gz);
+    const uint32_t node = node1;
     const bool solid = s_sy[ly + 2] | s_sz[lz + 2];
     float qx = 0.f, qy = 0.f, qz = 0.f;
     float kap = 0.f, Fx = 0.f, Fy = 0.f, Fz = 0.f;
@@ -921,15 +941,13 @@ __global__ __launch_bounds__(NT) void k_interface(const BoxDev *__restrict__ box
       kap = proj - div;
     }
     if (!solid) {
-      const float rr = at(PL(aux, A_RR), node);
-      const float rb = at(PL(aux, A_RB), node);
-      const float rho = rr + rb;
+      const float rho = rr1 + rb1;
       node_force(B, csf_strength(B, kap, mag), nxv, nyv, nzv, rho, Fx, Fy, Fz);
       const float irho = rcp(rho);
-      const float ux = fmaf(0.5f, Fx, at(PL(aux, A_JX), node)) * irho;
-      const float uy = fmaf(0.5f, Fy, at(PL(aux, A_JY), node)) * irho;
-      const float uz = fmaf(0.5f, Fz, at(PL(aux, A_JZ), node)) * irho;
-      const float dev = rr * B.cs2r + rb * B.cs2b - rho * kCs2;
+      const float ux = fmaf(0.5f, Fx, jx1) * irho;
+      const float uy = fmaf(0.5f, Fy, jy1) * irho;
+      const float uz = fmaf(0.5f, Fz, jz1) * irho;
+      const float dev = rr1 * B.cs2r + rb1 * B.cs2b - rho * kCs2;
       qx = dev * ux;
       qy = dev * uy;
       qz = dev * uz;

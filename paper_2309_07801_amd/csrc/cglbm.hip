@@ -470,13 +470,52 @@ bool tile_near_walls(const BoxDev &B, int y0, int ty, int z0, int z1, int halo) 
   return yw || zw;
 }
 
-// Plain tiles first, then the tiles near walls, each list padded to a
-// multiple of 8 (the XCD remap); returns the length of the first list.
-int32_t pack_tiles(std::vector<TileEntry> &out, std::vector<TileEntry> &plain,
-                   std::vector<TileEntry> &near) {
+// The tiles of one launch as the XCD remap deals them: eighth k of the list
+// runs on XCD k, in order.  The tiles of one box, and chunks of one length,
+// keep their order; else the chunks go longest first, each to the XCD with the
+// least work so far, in pieces of an eighth of a chunk's tiles (neighbours
+// share halo lines), so that the XCDs end together and the last blocks are
+// short.  24 boxes of 24 to 128 nodes an edge, compact pull and fused kernel:
+// 408 + 427 us in order, 379 + 421 dealt; 50 boxes 757 + 813 and 724 + 779;
+// 9 boxes 157 + 157 and 140 + 146.
+void deal_tiles(std::vector<TileEntry> &t, bool deal) {
   const TileEntry pad = {-1, 0, 0, 0};
-  while (plain.size() % 8) plain.push_back(pad);
-  while (near.size() % 8) near.push_back(pad);
+  auto len = [](const TileEntry &e) { return e.z1 - e.z0; };
+  auto shorter = [&](const TileEntry &a, const TileEntry &b) { return len(a) < len(b); };
+  if (deal && !t.empty() && len(*std::max_element(t.begin(), t.end(), shorter)) >
+                        len(*std::min_element(t.begin(), t.end(), shorter)) + 1) {
+    std::stable_sort(t.begin(), t.end(),
+                     [&](const TileEntry &a, const TileEntry &b) { return len(a) > len(b); });
+    std::vector<TileEntry> xcd[8];
+    int64_t work[8] = {};
+    for (size_t i = 0; i < t.size();) {
+      size_t run = i + 1;  // the chunk's tiles
+      while (run < t.size() && t[run].box == t[i].box && t[run].z0 == t[i].z0) ++run;
+      for (const size_t piece = (run - i + 7) / 8; i < run;) {
+        const size_t n = std::min(piece, run - i);
+        const size_t k = (size_t)(std::min_element(work, work + 8) - work);
+        xcd[k].insert(xcd[k].end(), t.begin() + (int64_t)i, t.begin() + (int64_t)(i + n));
+        work[k] += (int64_t)n * (len(t[i]) + 2);
+        i += n;
+      }
+    }
+    size_t most = 0;
+    for (const auto &x : xcd) most = std::max(most, x.size());
+    t.clear();
+    for (auto &x : xcd) {
+      x.resize(most, pad);
+      t.insert(t.end(), x.begin(), x.end());
+    }
+  }
+  while (t.size() % 8) t.push_back(pad);
+}
+
+// Plain tiles first, then the tiles near walls, each list a multiple of 8
+// long (the XCD remap); returns the length of the first list.
+int32_t pack_tiles(std::vector<TileEntry> &out, std::vector<TileEntry> &plain,
+                   std::vector<TileEntry> &near, bool deal) {
+  deal_tiles(plain, deal);
+  deal_tiles(near, deal);
   out = plain;
   out.insert(out.end(), near.begin(), near.end());
   return (int32_t)plain.size();
@@ -536,8 +575,8 @@ std::vector<std::pair<int, int>> z_chunks(const BoxDev &B, int zc, int edge) {
 }
 
 // Longest chunk to cut the boxes into, at most zc and at least zc / 2: the
-// one with the least estimated time.  The blocks are assigned in order to the
-// places the GPU has for them (256 CUs of 1024 threads, the occupancy of the
+// one with the least estimated time.  The blocks, longest first, are assigned
+// to the places the GPU has for them (256 CUs of 1024 threads, the occupancy of the
 // tiled kernels); a block takes its slabs and `lead` more iterations, and an
 // iteration the longer the more of the places are taken: measured for the
 // compact fused kernel at 192^3, 4.1 us with 216 blocks and 6.3 us with 432
@@ -555,13 +594,17 @@ int fit_chunk(const Layout &L, bool cpull, int zc, int nt, double lead) {
       blocks += (size_t)((B.nx + T.w - 1) / T.w) * ((B.ny + T.h - 1) / T.h) * ((B.nz + z - 1) / z);
     }
     if (blocks > 16 * places) return zc;  // many rounds: the last one matters little
-    busy.assign(places, 0.0);             // a min-heap of the places' end times
+    std::vector<std::pair<double, size_t>> lens;  // blocks of each box
     for (const BoxDev &B : L.boxes) {
       const TileShape &T = cpull ? B.cs : B.fs;
       const size_t cols = (size_t)((B.nx + T.w - 1) / T.w) * ((B.ny + T.h - 1) / T.h);
       const int n = (B.nz + z - 1) / z;
-      const double len = (double)B.nz / n + lead;
-      for (size_t c = 0; c < cols * n; ++c) {
+      lens.push_back({(double)B.nz / n + lead, cols * n});
+    }
+    std::sort(lens.begin(), lens.end(), std::greater<std::pair<double, size_t>>());
+    busy.assign(places, 0.0);             // a min-heap of the places' end times
+    for (const auto &[len, count] : lens) {
+      for (size_t c = 0; c < count; ++c) {
         std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
         busy.back() += len;
         std::push_heap(busy.begin(), busy.end(), std::greater<double>());
@@ -605,7 +648,7 @@ void build_tiles(Layout &L, int zc, int halo, int edge, std::vector<TileEntry> &
           (tile_near_walls(B, cy * T.h, T.h, zr.first, zr.second, halo) ? near : plain).push_back(e);
         }
   }
-  nplain = pack_tiles(out, plain, near);
+  nplain = pack_tiles(out, plain, near, L.boxes.size() > 1);
 }
 
 // Column table of k_cpull variant v.  Its ring reaches one node around the

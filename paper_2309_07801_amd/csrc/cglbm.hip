@@ -1125,29 +1125,31 @@ int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, double &ms_out
   for (hipEvent_t e : ev)
     if (e) (void)hipEventDestroy(e);
   std::sort(t.begin(), t.end());
-  ms_out = (double)t[(size_t)n / 2];
+  ms_out = (double)t[(size_t)(n - 1) / 2];
   return rc;
 }
 
-// The fastest of n candidates by time(v, ms): each once, then those within
-// 6 % of the best once more (single medians of a few launches differ by 3 %).
+// The fastest of n candidates by time(v, reps, ms): each over half the reps,
+// then those within 8 % of the best over all of them (medians of a few
+// launches differ by 3 %, and most candidates are further off than that).
 // ms_out (optional) receives the first times; best_ms the fastest's.
 template <class T>
-int fastest(int n, T &&time, double *ms_out, int &best, double &best_ms) {
+int fastest(int n, int reps, T &&time, double *ms_out, int &best, double &best_ms) {
+  const int few = std::max(1, reps / 2);
   std::vector<double> ms((size_t)n, 0.0);
   for (int v = 0; v < n; ++v) {
-    const int rc = time(v, ms[(size_t)v]);
+    const int rc = time(v, few, ms[(size_t)v]);
     if (rc) return rc;
     if (ms_out) ms_out[v] = ms[(size_t)v];
   }
-  const double limit = 1.06 * *std::min_element(ms.begin(), ms.end());
+  const double limit = 1.08 * *std::min_element(ms.begin(), ms.end());
   best_ms = 1e300;
   for (int v = 0; v < n; ++v) {
     double again = 0.0;
     if (!(ms[(size_t)v] <= limit)) continue;
-    const int rc = time(v, again);
+    const int rc = time(v, reps, again);
     if (rc) return rc;
-    const double t = 0.5 * (ms[(size_t)v] + again);
+    const double t = (few * ms[(size_t)v] + reps * again) / (few + reps);
     if (t < best_ms) {
       best_ms = t;
       best = v;
@@ -1812,11 +1814,11 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   HIP_TRY(hipEventCreate(&e1));
   int best = h->variant;
   double best_ms = 1e300;
-  rc = fastest(kNumFused,
-               [&](int v, double &ms) {
+  rc = fastest(kNumFused, reps,
+               [&](int v, int n, double &ms) {
                  const int r = select_variant(h, v, s);
                  return r ? r
-                          : time_in_step(s, reps, pull, [&] { return launch_fused(h, s, 0); }, ms);
+                          : time_in_step(s, n, pull, [&] { return launch_fused(h, s, 0); }, ms);
                },
                ms_per_variant, best, best_ms);
   // the three-kernel schedule after the same pull
@@ -1840,18 +1842,18 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     int cbest = h->cvariant;
     double c_ms = 1e300;
     if (!rc)
-      rc = fastest(kNumFused,
-                   [&](int v, double &ms) {
+      rc = fastest(kNumFused, reps,
+                   [&](int v, int n, double &ms) {
                      const int r = select_variant(h, v, s);
-                     return r ? r : time_in_step(s, reps, cpull, collide, ms);
+                     return r ? r : time_in_step(s, n, cpull, collide, ms);
                    },
                    nullptr, cfbest, c_ms);
     if (!rc) rc = select_variant(h, cfbest, s);
     if (!rc)
-      rc = fastest(kNumCPull,
-                   [&](int v, double &ms) {
+      rc = fastest(kNumCPull, reps,
+                   [&](int v, int n, double &ms) {
                      const int r = select_cvariant(h, v, s);
-                     return r ? r : time_in_step(s, reps, collide, cpull, ms);
+                     return r ? r : time_in_step(s, n, collide, cpull, ms);
                    },
                    nullptr, cbest, c_ms);
     if (!rc) rc = select_cvariant(h, cbest, s);
@@ -1873,10 +1875,10 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     };
     int32_t mbest = cmp ? h->wmode_compact : h->wmode_pop;
     double mbest_ms = 1e300;
-    rc = fastest(4,
-                 [&](int m, double &ms) {
+    rc = fastest(4, reps,
+                 [&](int m, int n, double &ms) {
                    const int r = select_mode(h, cmp ? cfbest : best, m, s);
-                   return r ? r : time_graph(h, s, reps, e0, e1, launch, ms);
+                   return r ? r : time_graph(h, s, n, e0, e1, launch, ms);
                  },
                  nullptr, mbest, mbest_ms);
     (cmp ? h->wmode_compact : h->wmode_pop) = mbest;

@@ -1181,7 +1181,7 @@ int time_graph(cglbm_handle *h, hipStream_t s, int reps, hipEvent_t e0, hipEvent
   if (el == hipSuccess) el = hipEventRecord(e0, s);
   for (int r = 0; r < reps && el == hipSuccess; ++r) el = hipGraphLaunch(x, s);
   if (el == hipSuccess) el = hipEventRecord(e1, s);
-  if (el == hipSuccess) el = hipEventSynchronize(e1);
+  if (el == hipSuccess) el = hipStreamSynchronize(s);  // the graph is destroyed below
   float ms = 0.f;
   if (el == hipSuccess) el = hipEventElapsedTime(&ms, e0, e1);
   (void)hipGraphExecDestroy(x);
@@ -1935,10 +1935,12 @@ int cglbm_profile_end(cglbm_handle *h, double *total_ms, int64_t *launches, int3
 void cglbm_destroy(cglbm_handle *h) {
   if (!h) return;
   drop_graphs(h);
-  if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
-  if (h->side) (void)hipStreamDestroy(h->side);
+  // events before the streams they were captured on: an event refers to its
+  // capture stream until it is destroyed
   if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
   if (h->join_ev) (void)hipEventDestroy(h->join_ev);
+  if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
+  if (h->side) (void)hipStreamDestroy(h->side);
   for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
   if (h->d_boxes) (void)hipFree(h->d_boxes);
   if (h->d_blk_box) (void)hipFree(h->d_blk_box);

@@ -7,7 +7,7 @@ sigma = 0.005, beta = 0.7, +-1e-6 counter noise on the populations, FP32
 storage and arithmetic.  A step is one full time update of every node
 (pull-streaming, moments, interface stencils, collision, recolouring).  The
 FP32 lines run the compact schedule (the state between the steps of a call
-held as each node's 17-value post-collision state); `--schedule 0` runs the
+held as each node's compact post-collision state); `--schedule 0` runs the
 population schedule.  The K timed steps are one cglbm_step call as the
 library runs it by default (replays of its captured two-step graph), timed
 between two device synchronizations; `repeats` times four more such calls
@@ -92,18 +92,16 @@ def d2q9_bytes(storage: str) -> int:
     return 2 * (8 * (8 if storage == "fp32x" else 4) + 2 * 8)
 
 
-# Compact schedule (FP32, periodic boxes): per node the pull reads the 17
-# floats of the compact post-collision state and writes the 11 moments; the
-# fused kernel reads the moments and writes the compact state; once per
-# call the population pull starts it and the emission (17 in, 54 out) ends it.
-# With the mass-exact FP32 storage the compact state adds the two FP64 colour
-# densities (read by the pull for the node's own rest closure and written by
-# the fused kernel), and the pull writes them beside the 11 moments.
-COMPACT_BYTES_X = {"pull": 17 * 4 + 2 * 8 + 11 * 4 + 2 * 8, "fused": 11 * 4 + 2 * 8 + 17 * 4 + 2 * 8,
-                   "pull_first": 52 * 4 + 2 * 8 + 11 * 4 + 2 * 8, "emit": 17 * 4 + 2 * 8 + 52 * 4 + 2 * 8}
+# Compact schedule: per node the pull reads the compact post-collision state
+# and writes the 11 moments; the fused kernel reads the moments and writes the
+# compact state; once per call the population pull starts it and the emission
+# ends it.  COMPACT_BYTES counts a state of 17 floats (densities, velocity,
+# force, six moments, normal), the interface's full description; the kernels
+# hold it in 15 and move 12 where the normal is zero, the count of
+# compact_bytes and of every rate reported here.
 COMPACT_BYTES = {"pull": 17 * 4 + 11 * 4, "fused": 11 * 4 + 17 * 4,
                  "pull_first": 54 * 4 + 11 * 4, "emit": 17 * 4 + 54 * 4}
-
+STATE = 12 * 4
 
 
 def compact_bytes(storage: str):
@@ -112,12 +110,11 @@ def compact_bytes(storage: str):
     state and the moments; the 16-bit ones decode (pull_first) and encode
     (emit) their own populations: 26 pairs of 16-bit values, the FP64 rest
     populations and, with the colour-fraction shift, a 16-bit fraction."""
-    if storage in ("fp32", "fp32p"):
-        return COMPACT_BYTES
-    if storage == "fp32x":
-        return COMPACT_BYTES_X
-    pops = 26 * 2 * 2 + 2 * 8 + (2 if storage in ("fp16c", "bf16c") else 0)
-    return dict(COMPACT_BYTES_X, pull_first=pops + 11 * 4 + 2 * 8, emit=17 * 4 + 2 * 8 + pops)
+    pops, rho = {"fp32": (54 * 4, 0), "fp32p": (54 * 4, 0), "fp32x": (52 * 4 + 2 * 8, 2 * 8)}.get(
+        storage, (26 * 2 * 2 + 2 * 8 + (2 if storage in ("fp16c", "bf16c") else 0), 2 * 8))
+    step = STATE + rho + 11 * 4 + rho
+    return {"pull": step, "fused": step, "pull_first": pops + 11 * 4 + rho,
+            "emit": STATE + rho + pops}
 
 
 # storage format of the D2Q9 step kernel's template argument
@@ -781,7 +778,7 @@ def main():
         cv = main_r["compact_variant"]
         kname = {"pull": "k_cpull<%d, %d, %d, false, f32, false>" % (cv["tx"], cv["ty"], cv["zc"]),
                  "fused": "k_fused<%d, %d, %d, %d, false, f32, false, true>" % geo}[dom]
-        kb = COMPACT_BYTES
+        kb = compact_bytes(args.storage)
     else:
         kname = ("k_fused<%d, %d, %d, %d, false, f32, false>" % geo if dom == "fused"
                  else "k_%s<f32%s>" % (dom, ", false, f32" if dom == "pull" else ""))
@@ -834,7 +831,7 @@ def main():
                     "median_mlups": round(main_r["mlups_median"], 1)},
         "events_mlups": round(main_r["events_mlups"], 1),
         "step_bytes_per_node": sb,
-        "step_bytes_moved_per_node": (COMPACT_BYTES["pull"] + COMPACT_BYTES["fused"]) if compact
+        "step_bytes_moved_per_node": (compact_bytes(args.storage)["pull"] + compact_bytes(args.storage)["fused"]) if compact
                                      else kernel_bytes(args.storage)["pull"] + kernel_bytes(args.storage)["fused"],
         "kernels": _kern_round(main_r["kernels"]),
         "fused_variant": var,

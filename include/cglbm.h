@@ -309,13 +309,14 @@ int cglbm_load_state(cglbm_handle *h, const void *src, void *stream);
  *   1 three launches: pull, LDS-tiled interface stencils, collision;
  *   2 compact: the same update with the state between the steps of one
  *     cglbm_step call held as each node's compact post-collision state
- *     (17 floats: rho_r, rho_b, u, F, the six relaxed second-order central
- *     moments and n; with unit higher-order rates the collided, recoloured
+ *     (15 floats: rho_r, rho_b, u, the strength of the CSF force, the six
+ *     relaxed second-order central moments and n, which is neither stored
+ *     nor read where it is zero; with unit higher-order rates the collided, recoloured
  *     populations of Eqs. 66-67 and 18-19 are a function of them).  Each
  *     step is a column-marching pull that rebuilds the collided populations
  *     of a column and its ring in registers and sums the streamed moments
- *     (Eq. 5), then the fused kernel writing compact states: about 224 bytes
- *     per node and step instead of 520.  The first step of a call pulls the
+ *     (Eq. 5), then the fused kernel writing compact states: 184 bytes
+ *     per node and step, 208 at the interface, instead of 520.  The first step of a call pulls the
  *     stored populations and the call ends by storing the populations again
  *     (one extra launch per call), so the stored state, the fields, the
  *     diagnostics and checkpoints are those of schedule 0.  Results equal
@@ -326,7 +327,7 @@ int cglbm_load_state(cglbm_handle *h, const void *src, void *stream);
  *     (the fused kernel serves them all; with another family or without Q
  *     one step per call equals schedule 1 bit for bit), or CGLBM_FP32_EXACT storage with
  *     Model D and Q (the compact state then carries the FP64 colour
- *     densities as well, 84 bytes per node, and per-colour mass stays
+ *     densities as well, 76 bytes per node, and per-colour mass stays
  *     exact to FP64 rounding), or one of the 16-bit storages with Model D
  *     and Q: the same compact state, so that within a call the state is
  *     held in FP32 and FP64 and rounded to the 16-bit format only when the

@@ -433,7 +433,7 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
 // Rows of the compact schedule's arrays (the compact state in a population
 // buffer, the moments in aux): padded to 64 bytes if all boxes' padded planes
 // fit the caller's buffers (whose sizes are those of the unpadded populations
-// and of 21 aux planes; the schedule uses 17 and 11, and two FP64 planes with
+// and of 21 aux planes; the schedule uses 15 and 11, and two FP64 planes with
 // the mass-exact formats), else not.  A tile's row segments then start on a
 // sector and its streaming stores fill whole ones: unpadded, the 16-bit
 // 190x131x150 box took 182 + 218 us a step, padded 157 + 171.  (To 128 bytes:
@@ -550,7 +550,6 @@ void fit_tile(int nx, int ny, int tx, int ty, int nt, int r3, int r2, int r1, Ti
   if (nx <= 128)
     for (int h = std::min(48, nt / nx); h >= 1; --h) consider(nx, h);
   T.d0 = make_fastdiv((uint32_t)T.w);
-  T.d2 = make_fastdiv((uint32_t)T.w + 2);
   T.d4 = make_fastdiv((uint32_t)T.w + 4);
   T.d6 = make_fastdiv((uint32_t)T.w + 6);
 }

@@ -18,8 +18,9 @@
 //   F, u, Q) and k_collide (collision, recolouring, local store)
 // or, within one call of many steps (schedule 2, compact):
 //   k_cpull    the moments after streaming, summed from the collided
-//              populations the pull rebuilds from each node's 17-value
-//              compact post-collision state
+//              populations the pull rebuilds from each node's compact
+//              post-collision state (12 values, and the normal next to an
+//              interface)
 //   k_fused    as above, storing compact states instead of populations
 //   (the call's first step runs k_pull, and k_emit stores the populations
 //   at its end)
@@ -43,10 +44,10 @@ enum AuxPlane {
 
 // The column tile of a box in a z-marching kernel (k_fused, k_cpull): w x h
 // nodes, thread t of the block owning node (t mod w, t / w); threads past
-// w h own none.  d0, d2, d4, d6 divide by w, w + 2, w + 4 and w + 6.
+// w h own none.  d0, d4, d6 divide by w, w + 4 and w + 6.
 struct TileShape {
   int32_t w, h;
-  FastDiv d0, d2, d4, d6;
+  FastDiv d0, d4, d6;
 };
 
 // Per-box constants, filled on the host.
@@ -2225,9 +2226,9 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
 // read through plane pointers (two scalar registers a plane) and not
 // descriptors (four): 17 of those had spilled to vector lanes.  A
 // geometry fixes the block's threads and the ring points its LDS array holds.
-template <int NT_, int R1_, int W_ = 0>
+template <int NT_, int R1_>
 struct CPullGeom {
-  static constexpr int NT = NT_, R1 = R1_, W = W_;
+  static constexpr int NT = NT_, R1 = R1_;
   static constexpr int CP = 2;  // ring points per thread: its column node, a halo point
   static_assert(NT % 64 == 0, "whole wavefronts");
 };
@@ -2295,7 +2296,7 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
   const uint32_t cyu = fdiv((uint32_t)te.xy, B.fccx);
   const int cxi = (int)((uint32_t)te.xy - cyu * (uint32_t)B.cncx);
   const int cyi = (int)cyu;
-  const int TW = G::W ? G::W : B.cs.w, TH = G::W ? G::NT / G::W : B.cs.h, R1X = TW + 2;
+  const int TW = B.cs.w, TH = B.cs.h, R1X = TW + 2;
   const int x0 = cxi * TW, y0 = cyi * TH, z0 = te.z0;
   const int nx = B.nx, ny = B.ny, nz = B.nz;
   const int z1 = te.z1;

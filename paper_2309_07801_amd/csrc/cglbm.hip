@@ -643,8 +643,31 @@ void build_tiles(Layout &L, int zc, int halo, int edge, std::vector<TileEntry> &
     for (const auto &zr : z_chunks(B, zc, edge))
       for (int32_t cy = 0; cy < ncy; ++cy)
         for (int32_t cx = 0; cx < ncx; ++cx) {
-          const TileEntry e = {(int32_t)b, cx + ncx * cy, zr.first, zr.second};
-          (tile_near_walls(B, cy * T.h, T.h, zr.first, zr.second, halo) ? near : plain).push_back(e);
+          auto walled = [&](int z0, int z1) {
+            return tile_near_walls(B, cy * T.h, T.h, z0, z1, halo);
+          };
+          const int32_t xy = cx + ncx * cy, len = zr.second - zr.first;
+          if (!walled(zr.first, zr.second)) {
+            plain.push_back({(int32_t)b, xy, zr.first, zr.second});
+            continue;
+          }
+          // near a wall: halves of a full chunk, but what stays clear of the
+          // wall in one piece with the plain tiles.  The few blocks beside a
+          // wall march with wall logic at half the speed, and a launch lasts
+          // as long as they do: 384x192x192 between walls, 10 steps 9.70 ms in
+          // whole chunks, 9.45-9.50 in halves, 9.46-9.73 with the pull's in
+          // quarters, 9.93 with both in quarters; 300x150x170 6.32,
+          // 6.11-6.33, 6.11 ms
+          const int n = std::max(1, len / std::max(8, zc / 2));
+          int open = zr.first;  // first slab of the plain pieces not yet listed
+          for (int k = 0; k < n; ++k) {
+            const int z0 = zr.first + len * k / n, z1 = zr.first + len * (k + 1) / n;
+            if (!walled(z0, z1)) continue;
+            if (open < z0) plain.push_back({(int32_t)b, xy, open, z0});
+            near.push_back({(int32_t)b, xy, z0, z1});
+            open = z1;
+          }
+          if (open < zr.second) plain.push_back({(int32_t)b, xy, open, zr.second});
         }
   }
   nplain = pack_tiles(out, plain, near, L.boxes.size() > 1);

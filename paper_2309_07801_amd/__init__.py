@@ -228,8 +228,8 @@ class Simulation:
         self.stream = stream
         dev = self.device
         self.inplace = bool(inplace)
-        # zeroed, so that the padding between boxes (never read or written by
-        # the kernels) is the same in every run and checkpoints compare bytewise
+        # zeroed, as the kernels leave the padding between boxes (never read)
+        # in the buffer that holds the state: checkpoints compare bytewise
         self.pop_a = torch.zeros(pop_bytes, dtype=torch.uint8, device=dev)
         self.pop_b = None if self.inplace else torch.zeros(pop_bytes, dtype=torch.uint8, device=dev)
         self.aux = torch.empty(aux_bytes, dtype=torch.uint8, device=dev)

@@ -423,6 +423,10 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
   L.total = std::max<int64_t>(off, kAlign);
   if ((L.total / kAlign) % 2 == 0) L.total += kAlign;
   L.ctotal = L.total;
+  for (size_t b = 0; b < L.boxes.size(); ++b) {
+    BoxDev &B = L.boxes[b];
+    B.pad = (int32_t)((b + 1 < L.boxes.size() ? L.boxes[b + 1].base : L.total) - B.base - B.n);
+  }
   L.nblk = blk;
   L.ntile = tile;
   // grids remapped across XCDs are padded to a multiple of 8 idle blocks

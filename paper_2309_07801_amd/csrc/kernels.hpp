@@ -58,6 +58,7 @@ struct BoxDev {
   int64_t n;            // nx*ny*nz
   int64_t pbase;        // first node of the box in the compact schedule's arrays
   int32_t px;           // and the length of their rows (nx, or padded)
+  int32_t pad;          // nodes of padding after the box in the population planes
   int32_t blk0;         // first 256-node block of the box (k_pull, k_collide)
   int32_t tile0;        // first tile of the box (k_interface)
   int32_t tnx, tny;     // tiles along x, y
@@ -566,6 +567,22 @@ struct StashBuf {
 // ---------------------------------------------------------------------------
 // PADDED: aux in the compact schedule's layout (padded rows, planes of length
 // cplane; the first step of a call).
+// A step's pull into a second buffer also zeroes the padding there: the
+// buffer may have held the compact schedule's arrays, whose rows and planes
+// lie elsewhere, and the stored state's bytes are functions of its nodes.
+// (One block a box, at most 127 nodes; stateless, so that replays of a
+// captured step do it as well.)
+template <class S>
+__device__ __forceinline__ void zero_pad(const Pops<S> &dst, uint32_t node) {
+#pragma unroll 1
+  for (int p = 0; p < Pops<S>::kPlanes; ++p)
+    at(dst.pw + (int64_t)p * dst.plane, node) = typename S::W(0);
+  if (S::kExact) {
+    at(dst.restp(0), node) = 0.0;
+    at(dst.restp(1), node) = 0.0;
+  }
+  if constexpr (S::kCShift) at(dst.cfr, node) = typename S::T(0);
+}
 template <class S, bool STASH, class SS = S, bool PADDED = false>
 __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxes,
                                                  const int32_t *__restrict__ blk_box,
@@ -578,8 +595,10 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   if (b < 0) return;
   const BoxDev B = boxes[b];
   const int64_t local = (int64_t)(lb - B.blk0) * kBlock + threadIdx.x;
-  if (local >= B.n) return;
   const Pops<S> src(src_, plane), dst(dst_, plane);
+  if (!STASH && !PADDED && bounce && lb == (uint32_t)B.blk0 && (int)threadIdx.x < B.pad)
+    zero_pad(dst, (uint32_t)(B.base + B.n) + threadIdx.x);
+  if (local >= B.n) return;
   const uint32_t l = (uint32_t)local;
   const uint32_t yz = fdiv(l, B.fdx);
   const int x = (int)(l - yz * (uint32_t)B.nx);

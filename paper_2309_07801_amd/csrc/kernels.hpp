@@ -50,6 +50,18 @@ struct TileShape {
   FastDiv d0, d4, d6;
 };
 
+// Thread t of a block over the column tile at (x0, y0) of an nx x ny box: its
+// tile point (x, y), and whether that is a node of the box, the thread's own.
+// (x and y as they are, not wrapped: a lane past the end of a box narrower
+// than the tile wraps to a node that another lane owns.)
+__host__ __device__ inline bool owned_node(const TileShape &T, int t, int x0, int y0, int nx,
+                                           int ny, int &x, int &y) {
+  const int r = (int)fdiv((uint32_t)t, T.d0);
+  x = x0 + t - r * T.w;
+  y = y0 + r;
+  return r < T.h && x < nx && y < ny;
+}
+
 // Per-box constants, filled on the host.
 struct BoxDev {
   int32_t nx, ny, nz;
@@ -1735,7 +1747,6 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
   constexpr int C_PER = 2;
   const bool c_has[C_PER] = {tid < own, tid < ring};
   uint32_t c_off[C_PER];
-  int gxo = 0, gyo = 0;  // the tile point
   int c_c2[C_PER], c_ri[C_PER];
 #pragma unroll
   for (int kk = 0; kk < C_PER; ++kk) {
@@ -1756,15 +1767,12 @@ __global__ __launch_bounds__(G::NT, MINW) void k_fused(const BoxDev *__restrict_
     }
     if (WALLS)
       for (int d = 0; d < 3; ++d) rows |= solid_row(y0 + ly - 2 + d) << (9 + 3 * kk + d);
-    if (kk == 0) {
-      gxo = x0 + lx - 1;
-      gyo = y0 + ly - 1;
-    }
     c_c2[kk] = (lx + 1) + R2X * (ly + 1);
     c_ri[kk] = lx + R1X * ly;
     c_off[kk] = (uint32_t)wrap_any(x0 + lx - 1, nx) + row * (uint32_t)wrap_any(y0 + ly - 1, ny);
   }
-  const bool in_xy = c_has[0] && gxo < nx && gyo < ny;
+  int ownx, owny;
+  const bool in_xy = owned_node(B.fs, tid, x0, y0, nx, ny, ownx, owny);
   // (lanes without a node of the box load at wrapped, valid addresses and
   // store nowhere)
   // interface values of the tile point, one slab behind the q ring
@@ -2363,8 +2371,8 @@ __global__ __launch_bounds__(G::NT, WALLS ? 3 : 4) void k_cpull(const BoxDev *__
   // LDS slot of the first direction a halo point sends (row c_y = sg, or
   // column c_x = sg, of the nine)
   const int hslot = rls[1] + (sg > 0.f ? (rowwave ? 12 : 4) * G::R1 : 0);
-  // the column node lies in the box (not past its last column or row)
-  const bool in_xy = has[0] && rgx[0] >= x0 && rgy[0] >= y0;
+  int ownx, owny;
+  const bool in_xy = owned_node(B.cs, tid, x0, y0, nx, ny, ownx, owny);
   // moments of slabs s-1, s, s+1 at the column node; those of s+1 begin with
   // the arrivals from s (an assignment: zeroing them and adding cost 20
   // operations a node)

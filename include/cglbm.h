@@ -448,7 +448,8 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
 int cglbm_profile_begin(cglbm_handle *h, int32_t max_launches);
 int cglbm_profile_end(cglbm_handle *h, double *total_ms, int64_t *launches, int32_t n_kinds);
 
-/* Release the handle and library-owned memory (never caller buffers). */
+/* Wait for the handle's device, then release the handle and library-owned
+ * memory (never caller buffers). */
 void cglbm_destroy(cglbm_handle *h);
 
 /* Message of the last failure on the calling thread ("" if none). */

@@ -779,6 +779,7 @@ struct cglbm_handle {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t graphc[2] = {nullptr, nullptr};  // compact schedule: two inner steps
+  std::vector<hipGraphExec_t> retired;  // dropped graphs whose replays may be pending
   // compact schedule with the state resident between calls
   // (cglbm_set_resident): clive is set while the other population buffer
   // holds the compact state of the last step and the state buffer is stale;
@@ -951,23 +952,46 @@ int launch_fused(cglbm_handle *h, hipStream_t s, uint32_t need) {
                       plane, need);
 }
 
-// Select fused variant v: rebuild and upload the column tables.
+// Graphs captured under another geometry, mode or schedule are not replayed
+// again.  Their last replays may still be running, on whatever stream the
+// caller stepped on: they are destroyed only once the device has been waited
+// for (destroy_retired), not here, where a caller expects no wait.
 void drop_graphs(cglbm_handle *h) {
-  for (hipGraphExec_t &g : h->graph)
-    if (g) {
-      (void)hipGraphExecDestroy(g);
-      g = nullptr;
+  for (hipGraphExec_t *g : {&h->graph[0], &h->graph[1], &h->graphc[0], &h->graphc[1]})
+    if (*g) {
+      h->retired.push_back(*g);
+      *g = nullptr;
     }
-  for (hipGraphExec_t &g : h->graphc)
-    if (g) {
-      (void)hipGraphExecDestroy(g);
-      g = nullptr;
-    }
+}
+
+// Wait for all work on the handle's device.
+hipError_t wait_device(const cglbm_handle *h) {
+  int now = h->device;
+  (void)hipGetDevice(&now);
+  if (now != h->device) (void)hipSetDevice(h->device);
+  const hipError_t e = hipDeviceSynchronize();
+  if (now != h->device) (void)hipSetDevice(now);
+  return e;
+}
+
+int destroy_retired(cglbm_handle *h) {
+  if (h->retired.empty()) return CGLBM_OK;
+  HIP_TRY(wait_device(h));
+  for (hipGraphExec_t g : h->retired) (void)hipGraphExecDestroy(g);
+  h->retired.clear();
+  return CGLBM_OK;
+}
+
+// Before a capture: a program that switches schedules back and forth leaves no
+// more than a few graphs behind.
+int bound_retired(cglbm_handle *h) {
+  return h->retired.size() > 8 ? destroy_retired(h) : CGLBM_OK;
 }
 
 // Select k_cpull variant v: rebuild and upload its column table.
 int select_cvariant(cglbm_handle *h, int v, hipStream_t s) {
   drop_graphs(h);
+  if (const int rc = destroy_retired(h)) return rc;
   build_ccolumns(h->L, v);
   for (const BoxDev &B : h->L.boxes)
     if (!fastdiv_ok((uint32_t)B.cncx, 1u << 20) || !fastdiv_ok((uint32_t)B.cncy, 1u << 20))
@@ -987,8 +1011,10 @@ int select_cvariant(cglbm_handle *h, int v, hipStream_t s) {
   return CGLBM_OK;
 }
 
+// Select fused variant v: rebuild and upload the column tables.
 int select_variant(cglbm_handle *h, int v, hipStream_t s) {
   drop_graphs(h);
+  if (const int rc = destroy_retired(h)) return rc;
   if (h->lattice == LATTICE_D2Q9) {
     build_tiles2(h->L, v);
     for (const BoxDev &B : h->L.boxes)
@@ -1104,6 +1130,7 @@ int launch_step(cglbm_handle *h, hipStream_t s) {
 // stays in stored populations: the first step pulls them, the last converts
 // the compact state back, and the state buffer parity is unchanged.
 int capture_compact_pair(cglbm_handle *h) {
+  if (const int rc = bound_retired(h)) return rc;
   if (!h->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
   int rc = CGLBM_OK;
@@ -1207,7 +1234,8 @@ int time_graph(cglbm_handle *h, hipStream_t s, int reps, hipEvent_t e0, hipEvent
   if (el == hipSuccess) el = hipEventRecord(e0, s);
   for (int r = 0; r < reps && el == hipSuccess; ++r) el = hipGraphLaunch(x, s);
   if (el == hipSuccess) el = hipEventRecord(e1, s);
-  if (el == hipSuccess) el = hipStreamSynchronize(s);  // the graph is destroyed below
+  const hipError_t es = hipStreamSynchronize(s);  // the graph is destroyed below
+  if (el == hipSuccess) el = es;
   float ms = 0.f;
   if (el == hipSuccess) el = hipEventElapsedTime(&ms, e0, e1);
   (void)hipGraphExecDestroy(x);
@@ -1275,6 +1303,7 @@ int step_compact(cglbm_handle *h, int32_t n, hipStream_t s) {
 // Capture two steps from the current parity (which they restore) on the
 // handle's private stream and instantiate them as an executable graph.
 int capture_pair(cglbm_handle *h) {
+  if (const int rc = bound_retired(h)) return rc;
   if (!h->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
   const int c0 = h->cur;
   HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -1960,14 +1989,18 @@ int cglbm_profile_end(cglbm_handle *h, double *total_ms, int64_t *launches, int3
 
 void cglbm_destroy(cglbm_handle *h) {
   if (!h) return;
+  // replays of the graphs and launches on the side stream may still be
+  // running: wait first, then graphs, events, and the streams that they were
+  // captured on (an event refers to its capture stream until it is destroyed)
+  (void)wait_device(h);
   drop_graphs(h);
-  // events before the streams they were captured on: an event refers to its
-  // capture stream until it is destroyed
+  for (hipGraphExec_t g : h->retired) (void)hipGraphExecDestroy(g);
   if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
   if (h->join_ev) (void)hipEventDestroy(h->join_ev);
+  for (hipEvent_t e : h->ev)
+    if (e) (void)hipEventDestroy(e);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->side) (void)hipStreamDestroy(h->side);
-  for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
   if (h->d_boxes) (void)hipFree(h->d_boxes);
   if (h->d_blk_box) (void)hipFree(h->d_blk_box);
   if (h->d_tile_box) (void)hipFree(h->d_tile_box);

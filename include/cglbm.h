@@ -420,20 +420,24 @@ int cglbm_get_variant(const cglbm_handle *h);
 int cglbm_set_wall_mode(cglbm_handle *h, int32_t mode, void *stream);
 int cglbm_get_wall_mode(const cglbm_handle *h);
 
-/* Autotuner: time every fused variant and the three-kernel schedule `reps`
- * times on the current state (the stored state is not advanced: the kernels
- * after the pull are re-run on the same inputs; in the in-place layout they
- * all write the next state into the one buffer, so the call advances the
- * state by exactly one step) and select the fastest
- * geometry and schedule (the three-kernel schedule wins on boxes too small to
- * fill the GPU with fused columns).  ms_per_variant (optional, length
- * cglbm_num_variants() + 1) receives the mean milliseconds per launch of
- * each fused variant, then of the interface + collide pair.  For layouts
- * with walls and two buffers it then times the four wall modes with the
- * chosen geometries, as replays of a captured graph (the fused kernel; for
- * schedule 2 k_cpull with the compact collision, advancing only the compact
- * state in the other buffer) and keeps the fastest per schedule.
- * Synchronizes the stream. */
+/* Autotuner: time every fused variant and the three-kernel schedule over
+ * `reps` launches each, on the current state, and select the fastest geometry
+ * and schedule (the three-kernel schedule wins on boxes too small to fill the
+ * GPU with fused columns).  Each launch runs after the pull that precedes it in
+ * a step; the stored state is not advanced (in the in-place layout, where the
+ * candidates write the next state into the one buffer, they run on one pull
+ * and the call advances the state by exactly one step).  ms_per_variant
+ * (optional, length cglbm_num_variants() + 1) receives the mean milliseconds
+ * per launch over the `reps` launches of each fused variant, then of the
+ * interface + collide pair; variants close to the fastest are timed again
+ * before one is chosen.  Layouts that schedule 2 serves then run steps of that
+ * schedule from the current state in the other population buffer, aux and the
+ * wall stashes, for its fused and pull geometries.  For layouts with walls and
+ * two buffers the call last times the four wall modes with the chosen
+ * geometries, as replays of a captured graph (the fused kernel; for schedule 2
+ * k_cpull with the compact collision), and keeps the fastest per schedule.
+ * Synchronizes the stream.  D2Q9: each tile shape, `reps` launches back to
+ * back. */
 int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *stream);
 
 /* Per-kernel timing with HIP events recorded on the caller's stream around

@@ -1154,57 +1154,74 @@ int capture_compact_pair(cglbm_handle *h) {
   return CGLBM_OK;
 }
 
-// Median milliseconds of launch() over `reps` runs of before() and launch() on
-// stream s, after one of each untimed; only launch() is timed.
+// Milliseconds of launch() over `reps` runs of before() and launch() on stream
+// s, after one of each untimed; only launch() is timed.  The median is what
+// candidates are compared by, the mean what callers are told.
+struct Timing {
+  double median = 0.0, mean = 0.0;
+};
 template <class B, class F>
-int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, double &ms_out) {
-  const int n = std::min(reps, 64);
-  std::vector<hipEvent_t> ev(2 * (size_t)n, nullptr);
+int time_in_step(hipStream_t s, int reps, B &&before, F &&launch, Timing &out) {
+  const int kEvents = 64;  // pairs of events, used again after each 64 runs
+  std::vector<hipEvent_t> ev(2 * (size_t)std::min(reps, kEvents), nullptr);
+  std::vector<float> t;
   int rc = CGLBM_OK;
   for (hipEvent_t &e : ev)
     if (!rc && hipEventCreate(&e) != hipSuccess) rc = fail(CGLBM_EHIP, "autotune: event create failed");
-  for (int r = -1; r < n && !rc; ++r) {
-    rc = before();
-    if (!rc && r >= 0) (void)hipEventRecord(ev[2 * (size_t)r], s);
-    if (!rc) rc = launch();
-    if (!rc && r >= 0) (void)hipEventRecord(ev[2 * (size_t)r + 1], s);
+  if (!rc) rc = before();
+  if (!rc) rc = launch();
+  for (int r0 = 0; r0 < reps && !rc; r0 += kEvents) {
+    const int n = std::min(reps - r0, kEvents);
+    for (int r = 0; r < n && !rc; ++r) {
+      if ((rc = before())) break;
+      (void)hipEventRecord(ev[2 * (size_t)r], s);
+      rc = launch();
+      (void)hipEventRecord(ev[2 * (size_t)r + 1], s);
+    }
+    if (!rc) rc = check_launch();
+    if (!rc && hipEventSynchronize(ev[2 * (size_t)n - 1]) != hipSuccess)
+      rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
+    for (int r = 0; r < n && !rc; ++r) {
+      float ms = 0.f;
+      (void)hipEventElapsedTime(&ms, ev[2 * (size_t)r], ev[2 * (size_t)r + 1]);
+      t.push_back(ms);
+    }
   }
-  if (!rc) rc = check_launch();
-  if (!rc && hipEventSynchronize(ev.back()) != hipSuccess)
-    rc = fail(CGLBM_EHIP, "autotune: event synchronize failed");
-  std::vector<float> t((size_t)n, 0.f);
-  for (int r = 0; r < n && !rc; ++r)
-    (void)hipEventElapsedTime(&t[(size_t)r], ev[2 * (size_t)r], ev[2 * (size_t)r + 1]);
   for (hipEvent_t e : ev)
     if (e) (void)hipEventDestroy(e);
-  std::sort(t.begin(), t.end());
-  ms_out = (double)t[(size_t)(n - 1) / 2];
-  return rc;
+  if (rc) return rc;
+  for (float ms : t) out.mean += (double)ms / reps;
+  std::nth_element(t.begin(), t.begin() + (reps - 1) / 2, t.end());
+  out.median = (double)t[(size_t)(reps - 1) / 2];
+  return CGLBM_OK;
 }
 
-// The fastest of n candidates by time(v, reps, ms): each over half the reps,
-// then those within 8 % of the best over all of them (medians of a few
+// The fastest of n candidates by time(v, reps, Timing): each over `first`
+// launches, then those close to the best once more (medians of a few
 // launches differ by 3 %, and most candidates are further off than that).
-// ms_out (optional) receives the first times; best_ms the fastest's.
+// ms_out (optional) receives the means of the first launches; best_ms the
+// fastest's time.  (Candidates timed over all `reps` at first are looked at
+// again over half as many.)
 template <class T>
-int fastest(int n, int reps, T &&time, double *ms_out, int &best, double &best_ms) {
-  const int few = std::max(1, reps / 2);
-  std::vector<double> ms((size_t)n, 0.0);
+int fastest(int n, int first, int reps, T &&time, double *ms_out, int &best, double &best_ms) {
+  std::vector<Timing> t((size_t)n);
+  double limit = 1e300;
   for (int v = 0; v < n; ++v) {
-    const int rc = time(v, few, ms[(size_t)v]);
+    const int rc = time(v, first, t[(size_t)v]);
     if (rc) return rc;
-    if (ms_out) ms_out[v] = ms[(size_t)v];
+    if (ms_out) ms_out[v] = t[(size_t)v].mean;
+    limit = std::min(limit, (first < reps ? 1.08 : 1.04) * t[(size_t)v].median);
   }
-  const double limit = 1.08 * *std::min_element(ms.begin(), ms.end());
+  if (first == reps) reps = std::max(1, reps / 2);
   best_ms = 1e300;
   for (int v = 0; v < n; ++v) {
-    double again = 0.0;
-    if (!(ms[(size_t)v] <= limit)) continue;
+    if (!(t[(size_t)v].median <= limit)) continue;
+    Timing again;
     const int rc = time(v, reps, again);
     if (rc) return rc;
-    const double t = (few * ms[(size_t)v] + reps * again) / (few + reps);
-    if (t < best_ms) {
-      best_ms = t;
+    const double ms = (first * t[(size_t)v].median + reps * again.median) / (first + reps);
+    if (ms < best_ms) {
+      best_ms = ms;
       best = v;
     }
   }
@@ -1215,7 +1232,7 @@ int fastest(int n, int reps, T &&time, double *ms_out, int &best, double &best_m
 // captures launch(stream, 0) and launch(stream, 1) on the capture stream.
 template <class F>
 int time_graph(cglbm_handle *h, hipStream_t s, int reps, hipEvent_t e0, hipEvent_t e1, F &&launch,
-               double &ms_out) {
+               Timing &out) {
   if (!h->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
   int rc = launch(h->cap_stream, 0);
@@ -1240,7 +1257,7 @@ int time_graph(cglbm_handle *h, hipStream_t s, int reps, hipEvent_t e0, hipEvent
   if (el == hipSuccess) el = hipEventElapsedTime(&ms, e0, e1);
   (void)hipGraphExecDestroy(x);
   if (el != hipSuccess) return fail(CGLBM_EHIP, "autotune: %s", hipGetErrorString(el));
-  ms_out = (double)ms / (2.0 * reps);
+  out.median = out.mean = (double)ms / (2.0 * reps);
   return CGLBM_OK;
 }
 
@@ -1867,48 +1884,58 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
+  const int few = std::max(1, (int)reps / 2);
   int best = h->variant;
   double best_ms = 1e300;
-  rc = fastest(kNumFused, reps,
-               [&](int v, int n, double &ms) {
+  rc = fastest(kNumFused, reps, reps,
+               [&](int v, int n, Timing &t) {
                  const int r = select_variant(h, v, s);
-                 return r ? r
-                          : time_in_step(s, n, pull, [&] { return launch_fused(h, s, 0); }, ms);
+                 return r ? r : time_in_step(s, n, pull, [&] { return launch_fused(h, s, 0); }, t);
                },
                ms_per_variant, best, best_ms);
   // the three-kernel schedule after the same pull
-  double three_ms = 1e300;
+  Timing three;
   if (!rc && !(rc = select_variant(h, best, s)))
     rc = time_in_step(s, reps, pull,
                       [&] {
                         const int r = launch_iface(h, s);
                         return r ? r : launch_collide(h, s);
                       },
-                      three_ms);
-  if (!rc && ms_per_variant) ms_per_variant[kNumFused] = three_ms;
+                      three);
+  if (!rc && ms_per_variant) ms_per_variant[kNumFused] = three.mean;
   // the compact schedule's fused kernel (its own best geometry), then its
   // pull, in steps of that schedule: they advance only the compact state in
-  // the other buffer, which the first collision writes from the pull above
+  // the other buffer, which the first collision writes from the pull above,
+  // and the wall stashes, each pull from the one that the pull before it wrote
   int cfbest = best;
+  auto compact_start = [&] {
+    const int r = launch_pull_compact(h, s);
+    return r ? r : launch_fused_compact(h, s);
+  };
   if (!rc && compact_ok(h)) {
-    if (!(rc = launch_pull_compact(h, s))) rc = launch_fused_compact(h, s);
-    auto cpull = [&] { return launch_cpull(h, s); };
+    rc = compact_start();
+    int stash = 0;
+    auto cpull = [&] {
+      const int rd = stash;
+      stash = 1 - stash;
+      return launch_cpull(h, s, rd);
+    };
     auto collide = [&] { return launch_fused_compact(h, s); };
     int cbest = h->cvariant;
     double c_ms = 1e300;
     if (!rc)
-      rc = fastest(kNumFused, reps,
-                   [&](int v, int n, double &ms) {
+      rc = fastest(kNumFused, few, reps,
+                   [&](int v, int n, Timing &t) {
                      const int r = select_variant(h, v, s);
-                     return r ? r : time_in_step(s, n, cpull, collide, ms);
+                     return r ? r : time_in_step(s, n, cpull, collide, t);
                    },
                    nullptr, cfbest, c_ms);
     if (!rc) rc = select_variant(h, cfbest, s);
     if (!rc)
-      rc = fastest(kNumCPull, reps,
-                   [&](int v, int n, double &ms) {
+      rc = fastest(kNumCPull, few, reps,
+                   [&](int v, int n, Timing &t) {
                      const int r = select_cvariant(h, v, s);
-                     return r ? r : time_in_step(s, n, collide, cpull, ms);
+                     return r ? r : time_in_step(s, n, collide, cpull, t);
                    },
                    nullptr, cbest, c_ms);
     if (!rc) rc = select_cvariant(h, cbest, s);
@@ -1920,9 +1947,14 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   // launches): the fused kernel alone for the population schedule (its pull
   // does not depend on the mode; layouts with the three-kernel schedule have
   // no tiled launch there), k_cpull with the compact collision for the
-  // compact one (which advance only the compact state in the other buffer)
+  // compact one (which advance only the compact state in the other buffer and
+  // the stashes).  Each starts from a pull of the stored state, which leaves
+  // the moments in its schedule's layout.
   for (int cmp = 0; cmp < 2 && !rc && h->L.walls && !h->inplace; ++cmp) {
     if (cmp ? !compact_ok(h) : h->L.general) continue;
+    rc = select_variant(h, cmp ? cfbest : best, s);
+    if (!rc) rc = cmp ? compact_start() : launch_pull(h, s, 1);
+    if (rc) break;
     auto launch = [&](hipStream_t cs, int k) {
       int r = cmp ? launch_cpull(h, cs, k) : CGLBM_OK;
       if (!r) r = cmp ? launch_fused_compact(h, cs) : launch_fused(h, cs, 0);
@@ -1930,10 +1962,10 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
     };
     int32_t mbest = cmp ? h->wmode_compact : h->wmode_pop;
     double mbest_ms = 1e300;
-    rc = fastest(4, reps,
-                 [&](int m, int n, double &ms) {
+    rc = fastest(4, few, reps,
+                 [&](int m, int n, Timing &t) {
                    const int r = select_mode(h, cmp ? cfbest : best, m, s);
-                   return r ? r : time_graph(h, s, n, e0, e1, launch, ms);
+                   return r ? r : time_graph(h, s, n, e0, e1, launch, t);
                  },
                  nullptr, mbest, mbest_ms);
     (cmp ? h->wmode_compact : h->wmode_pop) = mbest;
@@ -1943,7 +1975,7 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   if (rc) return rc;
   if (!rc) rc = select_mode(h, best, h->wmode_pop, s);
   if (rc) return rc;
-  const int32_t sched = three_ms < best_ms ? 1 : 0;
+  const int32_t sched = three.median < best_ms ? 1 : 0;
   if (sched != h->schedule) drop_graphs(h);
   h->schedule = sched;
   if (h->inplace) h->cur = 1 - h->cur;

@@ -3,9 +3,11 @@
 // run, and work stays pending on its stream until something waits for it.
 // It notes what a program must not do: destroy a graph whose replay is
 // pending, a stream with pending work, or a stream before an event that was
-// recorded on it.  Every launch takes a millisecond of its stream's time, plus
-// a tenth for each launch of the same kernel before it.
+// recorded on it; run a kernel on moments that the last writer left in the other
+// schedules' layout; pull from a wall stash that the step before did not write.
+// The k-th launch of a kernel takes 1 + k^2 / 1000 ms of its stream's time.
 #define __HIP_PLATFORM_AMD__
+#include <cxxabi.h>
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -43,13 +45,47 @@ std::set<Event *> events;
 std::map<Stream *, double> captured_cost;
 std::map<const void *, std::string> names;
 std::map<std::string, long> launches;
-std::vector<std::string> faults;
+std::set<std::string> faults;
 std::vector<double> elapsed;
 struct Config {
   dim3 g, b;
   size_t shared;
   hipStream_t s;
 } config;
+
+// The moments' layout in each aux array (0 populations', 1 compact), and the
+// wall stashes that hold the last step's arrivals.
+std::map<const void *, int> layout;
+std::set<const void *> fresh, used;
+
+void look(const std::string &name, void **args) {
+  auto arg = [&](int i) { return *(const void **)args[i]; };
+  std::vector<bool> flags;  // the kernel's truth-valued template arguments, in order
+  const std::string t = name.substr(0, name.find('('));
+  for (size_t i = 0; i < t.size(); ++i) {
+    if (t.compare(i, 4, "true") == 0) flags.push_back(true);
+    if (t.compare(i, 5, "false") == 0) flags.push_back(false);
+  }
+  auto reads = [&](const void *aux, int as) {
+    if (layout.count(aux) && layout[aux] != as)
+      faults.insert(t + " on moments of the other layout");
+  };
+  if (t.find("k_pull<") != std::string::npos) {
+    layout[arg(4)] = flags.back() ? 1 : 0;
+    if (arg(7)) fresh.insert(arg(7));
+  } else if (t.find("k_cpull<") != std::string::npos) {
+    layout[arg(3)] = 1;
+    if (arg(5) && !fresh.count(arg(5))) faults.insert(t + " from a stale wall stash");
+    used.insert(arg(5));
+    fresh.insert(arg(6));
+  } else if (t.find("k_fused<") != std::string::npos) {
+    reads(arg(2), flags[2] ? 1 : 0);  // WALLS, EXPORT, COMPACT, PLAIN
+    for (const void *p : used) fresh.erase(p);
+    used.clear();
+  } else if (t.find("k_interface<") != std::string::npos) {
+    reads(arg(2), 0);
+  }
+}
 
 Stream *of(hipStream_t s) { return s ? (Stream *)s : &null_stream; }
 void work(Stream *s, double cost) {
@@ -93,7 +129,9 @@ void **__hipRegisterFatBinary(const void *) {
 void __hipUnregisterFatBinary(void **) {}
 void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *,
                            void *, void *, void *, int *) {
-  names[host] = name;
+  char *plain = abi::__cxa_demangle(name, nullptr, nullptr, nullptr);
+  names[host] = plain ? plain : name;
+  std::free(plain);
 }
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t shared, hipStream_t s) {
@@ -107,9 +145,11 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *shared, hipStream
   *s = config.s;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t s) {
   long &k = launches[names[f]];
-  work(of(s), 1.0 + 0.1 * (double)k++);
+  work(of(s), 1.0 + 1e-3 * (double)k * (double)k);
+  ++k;
+  look(names[f], args);
   return hipSuccess;
 }
 
@@ -143,9 +183,9 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
   return *s = (hipStream_t)n, hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t s) {
-  if (of(s)->done < of(s)->issued) faults.push_back("stream destroyed with pending work");
+  if (of(s)->done < of(s)->issued) faults.insert("stream destroyed with pending work");
   for (Event *e : events)
-    if (e->stream == of(s)) faults.push_back("stream destroyed before an event recorded on it");
+    if (e->stream == of(s)) faults.insert("stream destroyed before an event recorded on it");
   streams.erase(of(s));
   delete of(s);
   return hipSuccess;
@@ -213,7 +253,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s) {
 hipError_t hipGraphExecDestroy(hipGraphExec_t x) {
   for (const auto &r : ((Exec *)x)->replays)
     if (streams.count(r.first) && r.first->done < r.second)
-      faults.push_back("graph destroyed with a pending replay");
+      faults.insert("graph destroyed with a pending replay");
   return delete (Exec *)x, hipSuccess;
 }
 

@@ -24,7 +24,7 @@ def run(lib, code, timeout=300):
     env = dict(os.environ, HIP_STANDIN=lib, PYTHONPATH=HERE + os.pathsep + ROOT)
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True,
                        timeout=timeout)
-    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    assert r.returncode == 0, (r.stdout + r.stderr)[-1500:]
     return r.stdout
 
 

@@ -210,6 +210,9 @@ struct Layout {
   int64_t ctotal = 0; // plane length of the compact schedule's arrays (padded rows)
   int32_t itile = 2;  // tile of k_interface (kIfaceTiles)
   int32_t nblk = 0, ntile = 0, ncol = 0, nblk_pad = 0;
+  // longest z chunk of each geometry (fit_chunk; 0 until it was selected once:
+  // the autotuner selects each several times)
+  int32_t cchunk[kNumCPull] = {}, fchunk[kNumFused] = {};
   // D3Q27: col_tiles and ccol_tiles hold first the tiles that run the kernel
   // without wall logic (ncol_plain, nccol_plain entries, padded to a
   // multiple of 8), then those whose stencils or rings reach a solid layer
@@ -607,7 +610,12 @@ int fit_chunk(const Layout &L, bool cpull, int zc, int nt, double lead) {
     std::sort(lens.begin(), lens.end(), std::greater<std::pair<double, size_t>>());
     busy.assign(places, 0.0);             // a min-heap of the places' end times
     for (const auto &[len, count] : lens) {
-      for (size_t c = 0; c < count; ++c) {
+      // (end times within one block of each other: whole rounds give each
+      // place one block)
+      const auto [lo, hi] = std::minmax_element(busy.begin(), busy.end());
+      const size_t rounds = *hi - *lo <= len ? count / places : 0;
+      for (double &t : busy) t += (double)rounds * len;
+      for (size_t c = rounds * places; c < count; ++c) {
         std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
         busy.back() += len;
         std::push_heap(busy.begin(), busy.end(), std::greater<double>());
@@ -682,8 +690,8 @@ void build_tiles(Layout &L, int zc, int halo, int edge, std::vector<TileEntry> &
 void build_ccolumns(Layout &L, int v) {
   const CPullVariant &C = cpull_variant(v);
   for (BoxDev &B : L.boxes) fit_tile(B.nx, B.ny, C.tx, C.ty, C.k->nt, 0, 0, C.k->r1, B.cs);
-  build_tiles(L, fit_chunk(L, true, C.zc, C.k->nt, 2.0), 1, L.zedge ? 3 : 0, L.ccol_tiles,
-              L.nccol_plain, true);
+  if (!L.cchunk[v]) L.cchunk[v] = fit_chunk(L, true, C.zc, C.k->nt, 2.0);
+  build_tiles(L, L.cchunk[v], 1, L.zedge ? 3 : 0, L.ccol_tiles, L.nccol_plain, true);
 }
 
 // Column table of fused variant v.  Its stencils reach three nodes around
@@ -693,8 +701,8 @@ void build_columns(Layout &L, int v) {
   const FusedVariant &F = fused_variant(v);
   for (BoxDev &B : L.boxes)
     fit_tile(B.nx, B.ny, F.tx, F.ty, F.k->nt, F.k->r3, F.k->r2, F.k->r1, B.fs);
-  build_tiles(L, fit_chunk(L, false, F.zc, F.k->nt, 3.0), 4, L.zedge ? 6 : 0, L.col_tiles,
-              L.ncol_plain, false);
+  if (!L.fchunk[v]) L.fchunk[v] = fit_chunk(L, false, F.zc, F.k->nt, 3.0);
+  build_tiles(L, L.fchunk[v], 4, L.zedge ? 6 : 0, L.col_tiles, L.ncol_plain, false);
   L.ncol = (int32_t)L.col_tiles.size();
 }
 

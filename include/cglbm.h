@@ -434,8 +434,8 @@ int cglbm_get_wall_mode(const cglbm_handle *h);
  * schedule from the current state in the other population buffer, aux and the
  * wall stashes, for its fused and pull geometries.  For layouts with walls and
  * two buffers the call last times the four wall modes with the chosen
- * geometries, as replays of a captured graph (the fused kernel; for schedule 2
- * k_cpull with the compact collision), and keeps the fastest per schedule.
+ * geometries in the same way (the fused kernel; for schedule 2 k_cpull with the
+ * compact collision) and keeps the fastest per schedule.
  * Synchronizes the stream.  D2Q9: each tile shape, `reps` launches back to
  * back. */
 int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *stream);

@@ -1236,39 +1236,6 @@ int fastest(int n, int first, int reps, T &&time, double *ms_out, int &best, dou
   return CGLBM_OK;
 }
 
-// Mean milliseconds per launch(k) over `reps` replays of a graph that
-// captures launch(stream, 0) and launch(stream, 1) on the capture stream.
-template <class F>
-int time_graph(cglbm_handle *h, hipStream_t s, int reps, hipEvent_t e0, hipEvent_t e1, F &&launch,
-               Timing &out) {
-  if (!h->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-  HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-  int rc = launch(h->cap_stream, 0);
-  if (!rc) rc = launch(h->cap_stream, 1);
-  hipGraph_t g = nullptr;
-  const hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
-  if (!rc && e != hipSuccess) rc = fail(CGLBM_EHIP, "graph capture: %s", hipGetErrorString(e));
-  hipGraphExec_t x = nullptr;
-  if (!rc) {
-    const hipError_t ei = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
-    if (ei != hipSuccess) rc = fail(CGLBM_EHIP, "graph instantiate: %s", hipGetErrorString(ei));
-  }
-  if (g) (void)hipGraphDestroy(g);
-  if (rc) return rc;
-  hipError_t el = hipGraphLaunch(x, s);
-  if (el == hipSuccess) el = hipEventRecord(e0, s);
-  for (int r = 0; r < reps && el == hipSuccess; ++r) el = hipGraphLaunch(x, s);
-  if (el == hipSuccess) el = hipEventRecord(e1, s);
-  const hipError_t es = hipStreamSynchronize(s);  // the graph is destroyed below
-  if (el == hipSuccess) el = es;
-  float ms = 0.f;
-  if (el == hipSuccess) el = hipEventElapsedTime(&ms, e0, e1);
-  (void)hipGraphExecDestroy(x);
-  if (el != hipSuccess) return fail(CGLBM_EHIP, "autotune: %s", hipGetErrorString(el));
-  out.median = out.mean = (double)ms / (2.0 * reps);
-  return CGLBM_OK;
-}
-
 // Resident compact state (cglbm_set_resident): store it as populations in the
 // state buffer if the last call left it in compact form.  The next compact
 // call then starts from the populations again.
@@ -1889,9 +1856,6 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   auto pull = [&] { return h->inplace ? CGLBM_OK : launch_pull(h, s, 1); };
   int rc = launch_pull(h, s, 1);
   if (rc || (rc = check_launch())) return rc;
-  hipEvent_t e0, e1;
-  HIP_TRY(hipEventCreate(&e0));
-  HIP_TRY(hipEventCreate(&e1));
   const int few = std::max(1, (int)reps / 2);
   int best = h->variant;
   double best_ms = 1e300;
@@ -1951,36 +1915,35 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   h->fvar_pop = best;
   h->fvar_compact = cfbest;
   // boxes with walls: the wall mode of each schedule with its chosen
-  // geometries, timed as the steps run (replays of a captured graph of two
-  // launches): the fused kernel alone for the population schedule (its pull
-  // does not depend on the mode; layouts with the three-kernel schedule have
-  // no tiled launch there), k_cpull with the compact collision for the
-  // compact one (which advance only the compact state in the other buffer and
-  // the stashes).  Each starts from a pull of the stored state, which leaves
-  // the moments in its schedule's layout.
+  // geometries, in steps as well: the fused kernel after a pull for the
+  // population schedule (layouts with the three-kernel schedule have no tiled
+  // launch there), the pull and the fused kernel for the compact one.  (Direct
+  // launches: replays of throw-away graphs with the fork and join had timed
+  // them closer to what a step's graph does, but processes that made many of
+  // those ended in a damaged heap.)
   for (int cmp = 0; cmp < 2 && !rc && h->L.walls && !h->inplace; ++cmp) {
     if (cmp ? !compact_ok(h) : h->L.general) continue;
     rc = select_variant(h, cmp ? cfbest : best, s);
-    if (!rc) rc = cmp ? compact_start() : launch_pull(h, s, 1);
+    if (!rc && cmp) rc = compact_start();
     if (rc) break;
-    auto launch = [&](hipStream_t cs, int k) {
-      int r = cmp ? launch_cpull(h, cs, k) : CGLBM_OK;
-      if (!r) r = cmp ? launch_fused_compact(h, cs) : launch_fused(h, cs, 0);
-      return r;
+    int stash = 0;
+    auto before = [&] { return cmp ? CGLBM_OK : launch_pull(h, s, 1); };
+    auto launch = [&] {
+      if (!cmp) return launch_fused(h, s, 0);
+      const int r = launch_cpull(h, s, stash);
+      stash = 1 - stash;
+      return r ? r : launch_fused_compact(h, s);
     };
     int32_t mbest = cmp ? h->wmode_compact : h->wmode_pop;
     double mbest_ms = 1e300;
     rc = fastest(4, few, reps,
                  [&](int m, int n, Timing &t) {
                    const int r = select_mode(h, cmp ? cfbest : best, m, s);
-                   return r ? r : time_graph(h, s, n, e0, e1, launch, t);
+                   return r ? r : time_in_step(s, n, before, launch, t);
                  },
                  nullptr, mbest, mbest_ms);
     (cmp ? h->wmode_compact : h->wmode_pop) = mbest;
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  if (rc) return rc;
   if (!rc) rc = select_mode(h, best, h->wmode_pop, s);
   if (rc) return rc;
   const int32_t sched = three.median < best_ms ? 1 : 0;

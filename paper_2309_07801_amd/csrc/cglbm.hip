@@ -223,6 +223,9 @@ struct Layout {
   // most nodes lie in boxes whose rows of stored words are not whole 128-byte
   // lines: the fused kernel's population stores are plain ones
   bool ragged = false;
+  // share of the fused kernel's slabs (over its columns) that lie near solid
+  // layers in boxes with y walls
+  double near_y = 0.0;
   bool walls = false;
   bool general = false;  // a box with Model A, B or C or without Q: three-kernel schedule
   bool full_rates = false;  // a box with a higher-order rate other than 1
@@ -704,6 +707,14 @@ void build_columns(Layout &L, int v) {
   if (!L.fchunk[v]) L.fchunk[v] = fit_chunk(L, false, F.zc, F.k->nt, 3.0);
   build_tiles(L, L.fchunk[v], 4, L.zedge ? 6 : 0, L.col_tiles, L.ncol_plain, false);
   L.ncol = (int32_t)L.col_tiles.size();
+  double all = 0.0, near = 0.0;
+  for (int32_t k = 0; k < L.ncol; ++k) {
+    const TileEntry &e = L.col_tiles[(size_t)k];
+    if (e.box < 0) continue;
+    all += e.z1 - e.z0;
+    if (k >= L.ncol_plain && (L.boxes[(size_t)e.box].walls & 1u)) near += e.z1 - e.z0;
+  }
+  L.near_y = near / all;
 }
 
 // Tile table of the D2Q9 step kernel for variant v (kept in the column
@@ -823,13 +834,20 @@ int launch_pull(cglbm_handle *h, hipStream_t s, int bounce) {
 int launch_fused(cglbm_handle *h, hipStream_t s, uint32_t need);
 
 // Interface fields of every node into aux (those in `need` at least): the
-// tiled kernel, or from
-// kIfaceNodes nodes on the fused kernel's field export (the same bits), whose
-// columns share their halos along z.  Measured: 64x64x64 21 us against 45,
-// 97x80x113 61 against 75, 200x180x160 283 against 188.
+// tiled kernel, or from kIfaceNodes nodes on the fused kernel's field export
+// (the same bits), whose columns share their halos along z.  Measured, the
+// kernels: 64x64x64 21 us against 45, 97x80x113 61 against 75, 200x180x160 283
+// against 188; a step of the three-kernel schedule: 64 boxes of 32^3 330 us
+// against 292, 300 of 20^3 489 and 413, 24 of 24 to 128 nodes an edge 1980 and
+// 1740.  The export's kernel with wall logic takes a select per stencil point
+// for rows in solid layers: with more than a quarter of the slabs near those of
+// y walls the tiled kernel stays (near share 0.14: 2341 against 1962 us,
+// 0.21: 639 and 587, 0.27: 301 and 340, 0.39: 323 and 371, 0.67: 416 and 458,
+// 1.0: 328 and 364; z walls alone: 394 and 380, 418 and 393).
 constexpr int64_t kIfaceNodes = 2 << 20;
+bool iface_fused(const Layout &L) { return L.total >= kIfaceNodes && L.near_y <= 0.25; }
 int launch_iface(cglbm_handle *h, hipStream_t s, uint32_t need = NEED_N | NEED_F | NEED_Q) {
-  if (h->L.total >= kIfaceNodes) return launch_fused(h, s, need);
+  if (iface_fused(h->L)) return launch_fused(h, s, need);
   hipLaunchKernelGGL(kIfaceTiles[h->L.itile].fn, dim3(h->L.ntile),
                      dim3(kIfaceThreads), 0, s, h->d_boxes, h->d_tile_box, h->aux, h->L.total,
                      (int)(need & NEED_KAPPA));
@@ -1857,12 +1875,16 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   int rc = launch_pull(h, s, 1);
   if (rc || (rc = check_launch())) return rc;
   const int few = std::max(1, (int)reps / 2);
+  // (layouts that the fused kernel does not step use it, if at all, for the
+  // fields of large boxes)
+  const bool fields = h->L.general && h->L.total >= kIfaceNodes;
+  auto fused = [&] { return launch_fused(h, s, fields ? NEED_N | NEED_F | NEED_Q : 0); };
   int best = h->variant;
   double best_ms = 1e300;
   rc = fastest(kNumFused, reps, reps,
                [&](int v, int n, Timing &t) {
                  const int r = select_variant(h, v, s);
-                 return r ? r : time_in_step(s, n, pull, [&] { return launch_fused(h, s, 0); }, t);
+                 return r ? r : time_in_step(s, n, pull, fused, t);
                },
                ms_per_variant, best, best_ms);
   // the three-kernel schedule after the same pull
@@ -1916,20 +1938,21 @@ int cglbm_autotune(cglbm_handle *h, int32_t reps, double *ms_per_variant, void *
   h->fvar_compact = cfbest;
   // boxes with walls: the wall mode of each schedule with its chosen
   // geometries, in steps as well: the fused kernel after a pull for the
-  // population schedule (layouts with the three-kernel schedule have no tiled
-  // launch there), the pull and the fused kernel for the compact one.  (Direct
+  // population schedule (layouts with the three-kernel schedule may run it for
+  // the fields of large boxes, else they have no launch in parts there), the
+  // pull and the fused kernel for the compact one.  (Direct
   // launches: replays of throw-away graphs with the fork and join had timed
   // them closer to what a step's graph does, but processes that made many of
   // those ended in a damaged heap.)
   for (int cmp = 0; cmp < 2 && !rc && h->L.walls && !h->inplace; ++cmp) {
-    if (cmp ? !compact_ok(h) : h->L.general) continue;
+    if (cmp ? !compact_ok(h) : h->L.general && !iface_fused(h->L)) continue;
     rc = select_variant(h, cmp ? cfbest : best, s);
     if (!rc && cmp) rc = compact_start();
     if (rc) break;
     int stash = 0;
     auto before = [&] { return cmp ? CGLBM_OK : launch_pull(h, s, 1); };
     auto launch = [&] {
-      if (!cmp) return launch_fused(h, s, 0);
+      if (!cmp) return fused();
       const int r = launch_cpull(h, s, stash);
       stash = 1 - stash;
       return r ? r : launch_fused_compact(h, s);

@@ -15,12 +15,16 @@ and reports the median; one more call of K steps launches every kernel
 directly between HIP events for the per-kernel times (`kernels`, the
 roofline) and `events_mlups`.
 
-Prints ONE JSON line: MLUPS of the timed steps, the roofline of the dominant
+Prints ONE JSON line on stdout: MLUPS of the timed steps, the roofline of the dominant
 kernel (against HBM: algorithmic bytes per launch / average launch time from
 the HIP events; against the FP32 vector issue rate: the committed
 SQ_INSTS_VALU count per launch x 64 lanes / the same time; reported against
 the closer ceiling) and the FP64 CPU oracle timed on a bounded sample of the
 same workload (all host threads and one thread, with the host's CPU model).
+
+The line is short enough to survive where only the end of a program's output
+is kept: it carries each form's MLUPS alone.  Everything measured goes to
+stderr, as one line `bench: detail {...}`, before it.
 
 `forms` reports, beside the main line:
   * the population schedule and the other storage formats on the same
@@ -95,10 +99,10 @@ def d2q9_bytes(storage: str) -> int:
 # Compact schedule: per node the pull reads the compact post-collision state
 # and writes the 11 moments; the fused kernel reads the moments and writes the
 # compact state; once per call the population pull starts it and the emission
-# ends it.  COMPACT_BYTES counts a state of 17 floats (densities, velocity,
-# force, six moments, normal), the interface's full description; the kernels
-# hold it in 15 and move 12 where the normal is zero, the count of
-# compact_bytes and of every rate reported here.
+# ends it.  The kernels hold the state in 15 floats and move 12 of them where
+# the normal is zero (STATE, what compact_bytes and every reported rate count).
+# COMPACT_BYTES is a reference size that no rate here uses: the state written
+# out in full, 17 floats (densities, velocity, force, six moments, normal).
 COMPACT_BYTES = {"pull": 17 * 4 + 11 * 4, "fused": 11 * 4 + 17 * 4,
                  "pull_first": 54 * 4 + 11 * 4, "emit": 17 * 4 + 54 * 4}
 STATE = 12 * 4
@@ -734,6 +738,34 @@ def parity_form():
     return out
 
 
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+             "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config", "roofline",
+             "step_roofline_frac", "step_bytes_per_node", "step_bytes_moved_per_node",
+             "events_mlups", "nonresident_mlups", "mass_drift", "mass_drift_steps", "nonfinite",
+             "cpu_baseline")
+
+
+def short_line(line):
+    """The printed line: the contract's keys and the main line's results as
+    they are, of each form what it runs at, of the parity runs what failed."""
+    def rates(d):
+        out = {k: rates(v) for k, v in d.items() if isinstance(v, dict)}
+        out = {k: v for k, v in out.items() if v}
+        if "mlups" in d and out:
+            out["mlups"] = d["mlups"]
+        return out or d.get("mlups")
+
+    short = {k: line[k] for k in LINE_KEYS if k in line}
+    short["repeats_median_mlups"] = line["repeats"]["median_mlups"]
+    forms = {k: rates(v) for k, v in line.get("forms", {}).items()}
+    if any(forms.values()):
+        short["forms_mlups"] = {k: v for k, v in forms.items() if v}
+    if "parity_status" in line:
+        runs = [(c + "/" + k, s) for c, e in line["parity_status"].items() for k, s in e.items()]
+        short["parity"] = {"runs": len(runs), "failed": [k for k, s in runs if s != "pass"]}
+    return short
+
+
 def main():
     T0 = time.perf_counter()
     args = parse()
@@ -967,7 +999,8 @@ def main():
         line["cpu_baseline"] = cpu_baseline(w, args.cpu_seconds)
         print("bench: cpu baseline done (%.1f s)" % (time.perf_counter() - T0), file=sys.stderr,
               flush=True)
-    print(json.dumps(line), flush=True)
+    print("bench: detail " + json.dumps(line), file=sys.stderr, flush=True)
+    print(json.dumps(short_line(line)), flush=True)
 
 
 if __name__ == "__main__":

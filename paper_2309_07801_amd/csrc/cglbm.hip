@@ -221,7 +221,8 @@ struct Layout {
   // own (else the first and last chunks of every column are near walls)
   bool zedge = true;
   // most nodes lie in boxes whose rows of stored words are not whole 128-byte
-  // lines: the fused kernel's population stores are plain ones
+  // lines (or sectors, see build_layout): the fused kernel's population stores
+  // are plain ones
   bool ragged = false;
   // share of the fused kernel's slabs (over its columns) that lie near solid
   // layers in boxes with y walls
@@ -416,10 +417,17 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
   const int64_t word = storage == CGLBM_FP32 && lattice == LATTICE_D3Q27
                            ? 4
                            : 2 * (int64_t)storage_bytes(storage);
+  // D3Q27 rows of whole 64-byte sectors but not of whole lines keep the hint
+  // beyond 128 nodes, where a row is cut into tiles that start on sectors: pull
+  // and fused kernel of 200x144x177 nodes in words of 8 bytes 592 us with it,
+  // 614 plain, 272x144x200 in words of 4 bytes 981 and 1027; 112x144x200 in words
+  // of 4 bytes 477 and 430, 88x144x200 in words of 8 323 and 311.  D2Q9 does not
+  // (1544x1203 in words of 8 bytes 80.9 us a step with it, 61.2 plain).
   int64_t ragged = 0, nodes = 0;
   for (const BoxDev &B : L.boxes) {
+    const int64_t row = B.nx * word, unit = lattice == LATTICE_D3Q27 && B.nx > 128 ? 64 : 128;
     nodes += B.n;
-    if (B.nx * word % 128) ragged += B.n;
+    if (row % unit) ragged += B.n;
   }
   L.ragged = 2 * ragged > nodes;
   // Plane length: an odd multiple of kAlign nodes, so that consecutive

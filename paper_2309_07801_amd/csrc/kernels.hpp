@@ -190,11 +190,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *base, i
       (int)(uint32_t)plane_bytes, 0x00020000);
 }
 // Population stores carry the non-temporal hint where a box's rows are whole
-// cache lines: the stored state is read only by the next step's pull, and
-// keeping it out of the caches measured faster for both kernels of the step
-// than plain stores (256^3: fused kernel 476 us against 501).  Where rows
-// start inside lines, neighbouring tiles write each line in parts, and plain
-// stores let L2 join them (200x144x177: 511 us against 782 with the hint).
+// cache lines: the stored state is read only by the next step's pull (256^3 in
+// FP32, the population schedule's pull and fused kernel 1697 us, 1724 with plain
+// stores).  Where rows start inside lines, neighbouring tiles write each line in
+// parts, and plain stores let L2 join them (200x144x177: 863 us with the hint,
+// 683 plain).
 constexpr int kNonTemporal = 2;  // cache policy bit of a streaming access
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float buf_ld_f32(__amdgpu_buffer_rsrc_t r, uint32_t off) {

@@ -228,7 +228,7 @@ class Simulation:
         self.stream = stream
         dev = self.device
         self.inplace = bool(inplace)
-        # zeroed, as the kernels leave the padding between boxes (never read)
+        # zeroed, as the library leaves the padding between boxes (never read)
         # in the buffer that holds the state: checkpoints compare bytewise
         self.pop_a = torch.zeros(pop_bytes, dtype=torch.uint8, device=dev)
         self.pop_b = None if self.inplace else torch.zeros(pop_bytes, dtype=torch.uint8, device=dev)

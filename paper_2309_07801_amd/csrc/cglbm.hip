@@ -123,6 +123,11 @@ const PullFn kPull[2][7] = {{k_pull<StoreF32, false>, k_pull<StoreF16, false>,
                              k_pull<StoreBF16, true>, k_pull<StoreF32X, true>,
                              k_pull<StoreF32P, true>, k_pull<StoreF16C, true>,
                              k_pull<StoreBF16C, true>}};
+using ZeroPadFn = void (*)(const BoxDev *, void *, int64_t);
+const ZeroPadFn kZeroPad[7] = {k_zero_pad<StoreF32>,  k_zero_pad<StoreF16>,
+                               k_zero_pad<StoreBF16>, k_zero_pad<StoreF32X>,
+                               k_zero_pad<StoreF32P>, k_zero_pad<StoreF16C>,
+                               k_zero_pad<StoreBF16C>};
 const CollideFn kCollide[7] = {k_collide<StoreF32>,  k_collide<StoreF16>,  k_collide<StoreBF16>,
                                k_collide<StoreF32X>, k_collide<StoreF32P>, k_collide<StoreF16C>,
                                k_collide<StoreBF16C>};
@@ -437,10 +442,6 @@ void build_layout(int32_t n_boxes, const cglbm_box_params *boxes, int32_t storag
   L.total = std::max<int64_t>(off, kAlign);
   if ((L.total / kAlign) % 2 == 0) L.total += kAlign;
   L.ctotal = L.total;
-  for (size_t b = 0; b < L.boxes.size(); ++b) {
-    BoxDev &B = L.boxes[b];
-    B.pad = (int32_t)((b + 1 < L.boxes.size() ? L.boxes[b + 1].base : L.total) - B.base - B.n);
-  }
   L.nblk = blk;
   L.ntile = tile;
   // grids remapped across XCDs are padded to a multiple of 8 idle blocks
@@ -812,6 +813,10 @@ struct cglbm_handle {
   // holds the compact state of the last step and the state buffer is stale;
   // cwi is the wall stash that step wrote, cstream the stream it ran on
   bool resident = false, clive = false;
+  // population buffer whose padding the compact schedule's arrays have
+  // overwritten (-1: neither); zeroed before a step may make it the state
+  int pad_dirty = -1;
+  bool pad_replayed = false;  // a caller's graph holds such writes: never clean for good
   int32_t cwi = 0;
   hipStream_t cstream = nullptr;
   // profiling
@@ -903,6 +908,7 @@ int launch_split(cglbm_handle *h, int32_t ncol, int32_t nplain, const FusedFn *f
 // other population buffer; k_cpull turns it into the moments of the next
 // step; k_emit stores it as populations in the state buffer.
 int launch_fused_compact(cglbm_handle *h, hipStream_t s) {
+  h->pad_dirty = 1 - h->cur;
   const FusedVariant &F = fused_variant(h->variant);
   const BoxDev *boxes = h->d_boxes;
   const TileEntry *cols = h->d_col_tiles;
@@ -1114,6 +1120,12 @@ int timed(cglbm_handle *h, hipStream_t s, int kind, F &&launch) {
   return launch();
 }
 
+// The caller is capturing stream s.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 int check_launch() {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(CGLBM_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -1274,6 +1286,7 @@ int flush_compact(cglbm_handle *h, hipStream_t s) {
 
 int step_compact(cglbm_handle *h, int32_t n, hipStream_t s) {
   if (n == 0) return CGLBM_OK;
+  if (!h->pad_replayed) h->pad_replayed = capturing(s);
   // wall stashes (boxes with solid layers): step k's solid points emit from
   // stash wi, its arrivals at solid nodes go to 1 - wi; the first step
   // (the population pull) writes stash 0
@@ -1656,6 +1669,12 @@ int cglbm_step(cglbm_handle *h, int32_t n_steps, void *stream) {
   if (h->clive) {
     const int rc = flush_compact(h, s);
     if (rc) return rc;
+  }
+  if (h->pad_dirty >= 0 && n_steps > 0) {
+    hipLaunchKernelGGL(kZeroPad[h->storage], dim3((unsigned)h->n_boxes), dim3(kPadBlock), 0, s,
+                       h->d_boxes, h->pop[h->pad_dirty], h->L.total);
+    // (captured by the caller, it has not run yet)
+    if (!h->pad_replayed && !capturing(s)) h->pad_dirty = -1;
   }
   int32_t k = 0;
   if (h->use_graph && !h->prof && n_steps >= 2) {

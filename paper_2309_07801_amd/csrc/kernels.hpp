@@ -70,7 +70,6 @@ struct BoxDev {
   int64_t n;            // nx*ny*nz
   int64_t pbase;        // first node of the box in the compact schedule's arrays
   int32_t px;           // and the length of their rows (nx, or padded)
-  int32_t pad;          // nodes of padding after the box in the population planes
   int32_t blk0;         // first 256-node block of the box (k_pull, k_collide)
   int32_t tile0;        // first tile of the box (k_interface)
   int32_t tnx, tny;     // tiles along x, y
@@ -579,22 +578,6 @@ struct StashBuf {
 // ---------------------------------------------------------------------------
 // PADDED: aux in the compact schedule's layout (padded rows, planes of length
 // cplane; the first step of a call).
-// A step's pull into a second buffer also zeroes the padding there: the
-// buffer may have held the compact schedule's arrays, whose rows and planes
-// lie elsewhere, and the stored state's bytes are functions of its nodes.
-// (One block a box, at most 127 nodes; stateless, so that replays of a
-// captured step do it as well.)
-template <class S>
-__device__ __forceinline__ void zero_pad(const Pops<S> &dst, uint32_t node) {
-#pragma unroll 1
-  for (int p = 0; p < Pops<S>::kPlanes; ++p)
-    at(dst.pw + (int64_t)p * dst.plane, node) = typename S::W(0);
-  if (S::kExact) {
-    at(dst.restp(0), node) = 0.0;
-    at(dst.restp(1), node) = 0.0;
-  }
-  if constexpr (S::kCShift) at(dst.cfr, node) = typename S::T(0);
-}
 template <class S, bool STASH, class SS = S, bool PADDED = false>
 __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxes,
                                                  const int32_t *__restrict__ blk_box,
@@ -607,10 +590,8 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   if (b < 0) return;
   const BoxDev B = boxes[b];
   const int64_t local = (int64_t)(lb - B.blk0) * kBlock + threadIdx.x;
-  const Pops<S> src(src_, plane), dst(dst_, plane);
-  if (!STASH && !PADDED && bounce && lb == (uint32_t)B.blk0 && (int)threadIdx.x < B.pad)
-    zero_pad(dst, (uint32_t)(B.base + B.n) + threadIdx.x);
   if (local >= B.n) return;
+  const Pops<S> src(src_, plane), dst(dst_, plane);
   const uint32_t l = (uint32_t)local;
   const uint32_t yz = fdiv(l, B.fdx);
   const int x = (int)(l - yz * (uint32_t)B.nx);
@@ -769,6 +750,23 @@ __global__ __launch_bounds__(kBlock) void k_pull(const BoxDev *__restrict__ boxe
   } else {
     emit([](float *p, float v) { st(p, v); });
   }
+}
+
+// Zeroes the padding of a population buffer, one block a box: before the first
+// step into a buffer that held the compact schedule's arrays, whose rows and
+// planes lie elsewhere, so that the stored state's bytes are functions of its
+// nodes.  (Not in k_pull: a branch for it there, though no pulling block took
+// it, changed the code of the rest, and the 256^3 pull took 831 us for 789.)
+constexpr int kPadBlock = 128;  // a box has at most 127 nodes of padding
+template <class S>
+__global__ __launch_bounds__(kPadBlock) void k_zero_pad(const BoxDev *__restrict__ boxes,
+                                                        void *__restrict__ buf_, int64_t plane) {
+  const int64_t node = boxes[blockIdx.x].base + boxes[blockIdx.x].n + threadIdx.x;
+  if (node >= (blockIdx.x + 1 < gridDim.x ? boxes[blockIdx.x + 1].base : plane)) return;
+  const Pops<S> p(buf_, plane);
+  for (int i = 0; i < Pops<S>::kPlanes; ++i) p.pw[i * plane + node] = typename S::W(0);
+  if (S::kExact) p.rest[node] = p.rest[plane + node] = 0.0;
+  if constexpr (S::kCShift) p.cfr[node] = typename S::T(0);
 }
 
 // Strength of the CSF force (Eq. 15): half of sigma kappa |grad phi|, which

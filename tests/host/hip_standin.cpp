@@ -227,6 +227,10 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e_, unsigned) {
   return hipSuccess;
 }
 
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) {
+  *st = of(s)->capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   of(s)->capture = of(s);
   captured_cost[of(s)] = 0.0;

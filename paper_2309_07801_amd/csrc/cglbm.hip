@@ -1120,8 +1120,9 @@ int timed(cglbm_handle *h, hipStream_t s, int kind, F &&launch) {
   return launch();
 }
 
-// The caller is capturing stream s.
+// The caller is capturing stream s (the null stream cannot be captured).
 bool capturing(hipStream_t s) {
+  if (!s) return false;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
 }
